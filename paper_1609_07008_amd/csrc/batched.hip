@@ -394,7 +394,7 @@ static ArcSrc host_arc_src(const Csr &c) {
     return r;
 }
 
-static int host_arc_mode(const Csr &c) { return c.w == nullptr ? 0 : (c.pk ? 1 : 2); }
+static int host_arc_mode(const Csr &c) { return c.pk ? 1 : (c.w ? 2 : 0); }
 
 int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const int32_t *> &d_src,
                    const std::vector<int64_t> &n_src, const std::vector<double *> &d_bc,
@@ -411,29 +411,29 @@ int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const in
         d.n = g->n;
         d.nwords = (g->n + 31) / 32;
         d.mb = g->mb;
-        d.am = host_arc_mode(g->in);
-        if (host_arc_mode(g->out) != d.am || d.am != host_arc_mode(graphs[0]->in)) {
+        d.am = host_arc_mode(g->core.in);
+        if (host_arc_mode(g->core.out) != d.am || d.am != host_arc_mode(graphs[0]->core.in)) {
             err = "graphs of one launch must share one arc encoding";
             return MFBC_EINVAL;
         }
-        d.ntasks_in = g->plan_in.ntasks;
-        d.nhubs_in = g->plan_in.nhubs;
-        d.nslots_in = g->plan_in.nslots;
-        d.ntasks_out = g->plan_out.ntasks;
-        d.nhubs_out = g->plan_out.nhubs;
-        d.nslots_out = g->plan_out.nslots;
-        d.rp_in = g->in.rp;
-        d.rp_out = g->out.rp;
-        d.arcs_in = host_arc_src(g->in);
-        d.arcs_out = host_arc_src(g->out);
-        d.tasks_in = g->plan_in.tasks;
-        d.tasks_out = g->plan_out.tasks;
-        d.hubs_in = g->plan_in.hubs;
-        d.hubs_out = g->plan_out.hubs;
+        d.ntasks_in = g->core.plan_in.ntasks;
+        d.nhubs_in = g->core.plan_in.nhubs;
+        d.nslots_in = g->core.plan_in.nslots;
+        d.ntasks_out = g->core.plan_out.ntasks;
+        d.nhubs_out = g->core.plan_out.nhubs;
+        d.nslots_out = g->core.plan_out.nslots;
+        d.rp_in = g->core.in.rp;
+        d.rp_out = g->core.out.rp;
+        d.arcs_in = host_arc_src(g->core.in);
+        d.arcs_out = host_arc_src(g->core.out);
+        d.tasks_in = g->core.plan_in.tasks;
+        d.tasks_out = g->core.plan_out.tasks;
+        d.hubs_in = g->core.plan_in.hubs;
+        d.hubs_out = g->core.plan_out.hubs;
         d.perm = g->perm;
         n_max = std::max(n_max, g->n);
-        slots_max = std::max({slots_max, g->plan_in.nslots, g->plan_out.nslots});
-        arcs_max = std::max<int64_t>(arcs_max, g->arcs);
+        slots_max = std::max(slots_max, max_slots(g));
+        arcs_max = std::max<int64_t>(arcs_max, g->core.arcs);
     }
     // jobs: 64 w sources each; scheduled largest first (longest-processing-time
     // order) so that small jobs fill in at the end
@@ -442,7 +442,7 @@ int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const in
     std::vector<double> cost;
     int64_t lam_total = 0;
     for (int i = 0; i < G; i++) {
-        const double c = (double)graphs[(size_t)i]->n * (double)(graphs[(size_t)i]->arcs + 1);
+        const double c = (double)graphs[(size_t)i]->n * (double)(graphs[(size_t)i]->core.arcs + 1);
         for (int64_t b0 = 0; b0 < n_src[(size_t)i]; b0 += per_job) {
             JobDesc jd{};
             jd.g = i;

@@ -346,30 +346,30 @@ static ArcSrc arc_src(const Csr &c) {
     return r;
 }
 
-static int arc_mode(const Csr &c) { return c.w == nullptr ? 0 : (c.pk ? 1 : 2); }
+static int arc_mode(const Csr &c) { return c.pk ? 1 : (c.w ? 2 : 0); }
 
 // Batches of two or more column groups run the forward product on pairs of
 // them (the workspace holds an even number of groups); a single group runs
 // alone.
 static int fwd_wide_groups(int ncg) { return ncg >= 2 ? (ncg + kWide - 1) / kWide : 0; }
 
-static FwdArgs fwd_args(mfbc_graph *g, int ncg, int j) {
+static FwdArgs fwd_args(mfbc_graph *g, const View &vw, int ncg, int j) {
     Workspace &ws = g->ws;
     const int b = (j - 1) & 1;  // buffer holding F_{j-1}
     FwdArgs a{};
-    a.tasks = g->plan_in.tasks;
-    a.hubs = g->plan_in.hubs;
-    a.ntasks = g->plan_in.ntasks;
-    a.nhubs = g->plan_in.nhubs;
-    a.nslots = g->plan_in.nslots;
+    a.tasks = vw.plan_in.tasks;
+    a.hubs = vw.plan_in.hubs;
+    a.ntasks = vw.plan_in.ntasks;
+    a.nhubs = vw.plan_in.nhubs;
+    a.nslots = vw.plan_in.nslots;
     a.ncg = ncg;
     a.ncg_all = ncg;
     a.n = g->n;
     a.j = j;
     a.nwords = (g->n + 31) / 32;
     a.mb = g->mb;
-    a.rp = g->in.rp;
-    a.arcs = arc_src(g->in);
+    a.rp = vw.in.rp;
+    a.arcs = arc_src(vw.in);
     a.abits = ws.abits[b];
     a.ftup = (const uint32_t *)ws.fdist[b];
     a.fsig = ws.fsig[b];
@@ -425,12 +425,12 @@ void launch_fwd_init(mfbc_graph *g, int ncg, int nb, hipStream_t s) {
                        nwords, ws.tdist, ws.tsig, (uint32_t *)ws.fdist[0], ws.abits[0]);
 }
 
-void launch_fwd_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
-    FwdArgs a = fwd_args(g, ncg, j);
+void launch_fwd_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
+    FwdArgs a = fwd_args(g, vw, ncg, j);
     if (a.nwide) {
         if (ev) (void)hipEventRecord(ev[0], s);
         const int grid = blocks_for((size_t)a.ntasks * a.nwide, kWavesPerBlock, 0x7fffffff);
-        switch (arc_mode(g->in)) {
+        switch (arc_mode(vw.in)) {
             case 0: hipLaunchKernelGGL((k_fwd_pull_w<0, kWide, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
             case 1: hipLaunchKernelGGL((k_fwd_pull_w<1, kWide, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
             default: hipLaunchKernelGGL((k_fwd_pull_w<2, kWide, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
@@ -446,7 +446,7 @@ void launch_fwd_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t
     if (ev) (void)hipEventRecord(ev[0], s);
     const size_t waves = (size_t)a.ntasks * ncg;
     const int grid = blocks_for(waves, kWavesPerBlock, 0x7fffffff);
-    switch (arc_mode(g->in)) {
+    switch (arc_mode(vw.in)) {
         case 0: hipLaunchKernelGGL((k_fwd_pull<0, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
         case 1: hipLaunchKernelGGL((k_fwd_pull<1, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
         default: hipLaunchKernelGGL((k_fwd_pull<2, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
@@ -460,23 +460,23 @@ void launch_fwd_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
 
-static BwdArgs bwd_args(mfbc_graph *g, int ncg, int k) {
+static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
     Workspace &ws = g->ws;
     // k = 0: counting product writes B_0 into buffer 0; product k reads
     // B_{k-1} from buffer (k-1)&1 and writes B_k into buffer k&1.
     const int bn = k & 1, b = bn ^ 1;
     BwdArgs a{};
-    a.tasks = g->plan_out.tasks;
-    a.hubs = g->plan_out.hubs;
-    a.ntasks = g->plan_out.ntasks;
-    a.nhubs = g->plan_out.nhubs;
-    a.nslots = g->plan_out.nslots;
+    a.tasks = vw.plan_out.tasks;
+    a.hubs = vw.plan_out.hubs;
+    a.ntasks = vw.plan_out.ntasks;
+    a.nhubs = vw.plan_out.nhubs;
+    a.nslots = vw.plan_out.nslots;
     a.ncg = ncg;
     a.ncg_all = ncg;
     a.n = g->n;
     a.k = k;
-    a.rp = g->out.rp;
-    a.arcs = arc_src(g->out);
+    a.rp = vw.out.rp;
+    a.arcs = arc_src(vw.out);
     a.src = ws.src;
     a.tdist = ws.tdist;
     a.tsig = ws.tsig;
@@ -490,7 +490,7 @@ static BwdArgs bwd_args(mfbc_graph *g, int ncg, int k) {
     a.step = g->trace_step ? ws.fdist[1] : nullptr;   // frontier indices only when traced
     a.lam = ws.lam;
     a.dag = ws.dag;
-    a.narcs = g->arcs;
+    a.narcs = vw.arcs;
     a.pd = ws.pd;
     a.pm = ws.pm;
     a.ctr = ws.counters + (size_t)(k % kCounterRing) * 4 * kCounterSlots;
@@ -506,12 +506,12 @@ static BwdArgs bwd_args(mfbc_graph *g, int ncg, int k) {
     // per-arc value gathers dominate: there the pair form, at two arcs per
     // round and five waves per SIMD, measured slower (rmat16: 15.9 against
     // 13.4 ms per step) and one group per wave is kept.
-    a.nwide = arc_mode(g->out) != 0 ? fwd_wide_groups(ncg) : 0;
+    a.nwide = arc_mode(vw.out) != 0 ? fwd_wide_groups(ncg) : 0;
     a.nwide_all = a.nwide;
     return a;
 }
 
-hipError_t launch_bwd_count(mfbc_graph *g, int ncg, hipStream_t s, hipEvent_t *ev) {
+hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t s, hipEvent_t *ev) {
     Workspace &ws = g->ws;
     // the counting product writes B_0 into buffer 0: clear its bitmap and
     // this product's counters first
@@ -525,7 +525,7 @@ hipError_t launch_bwd_count(mfbc_graph *g, int ncg, hipStream_t s, hipEvent_t *e
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, (uint32_t *)ws.flags + 1, (size_t)1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    BwdArgs a = bwd_args(g, ncg, 0);
+    BwdArgs a = bwd_args(g, vw, ncg, 0);
     if (ev) (void)hipEventRecord(ev[0], s);
     if (ncg >= 2) {
         // pairs of groups: tau interleaved per pair, then one wave per (pair, task)
@@ -534,7 +534,7 @@ hipError_t launch_bwd_count(mfbc_graph *g, int ncg, hipStream_t s, hipEvent_t *e
         hipLaunchKernelGGL(k_pair_tau, dim3(blocks_for((size_t)npairs * plane, 256, 65536)), dim3(256),
                            0, s, (const int32_t *)ws.tdist, (uint32_t *)ws.tau2, plane, ncg, npairs, ws.flags + 1);
         const int grid = blocks_for((size_t)a.ntasks * npairs, kWavesPerBlock, 0x7fffffff);
-        switch (arc_mode(g->out)) {
+        switch (arc_mode(vw.out)) {
             case 0:
                 hipLaunchKernelGGL((k_bwd_count_w<0, false, false>), dim3(grid), dim3(kBlock), 0, s, a);
                 hipLaunchKernelGGL((k_bwd_count_w<0, false, true>), dim3(grid), dim3(kBlock), 0, s, a);
@@ -551,7 +551,7 @@ hipError_t launch_bwd_count(mfbc_graph *g, int ncg, hipStream_t s, hipEvent_t *e
     } else {
         const size_t waves = (size_t)a.ntasks * ncg;
         const int grid = blocks_for(waves, kWavesPerBlock, 0x7fffffff);
-        switch (arc_mode(g->out)) {
+        switch (arc_mode(vw.out)) {
             case 0: hipLaunchKernelGGL((k_bwd_count<0, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
             case 1: hipLaunchKernelGGL((k_bwd_count<1, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
             default: hipLaunchKernelGGL((k_bwd_count<2, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
@@ -566,12 +566,12 @@ hipError_t launch_bwd_count(mfbc_graph *g, int ncg, hipStream_t s, hipEvent_t *e
     return hipGetLastError();
 }
 
-void launch_bwd_product(mfbc_graph *g, int ncg, int k, hipStream_t s, hipEvent_t *ev) {
-    BwdArgs a = bwd_args(g, ncg, k);
+void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, int k, hipStream_t s, hipEvent_t *ev) {
+    BwdArgs a = bwd_args(g, vw, ncg, k);
     if (a.nwide) {
         if (ev) (void)hipEventRecord(ev[0], s);
         const int grid = blocks_for((size_t)a.ntasks * a.nwide, kWavesPerBlock, 0x7fffffff);
-        switch (arc_mode(g->out)) {
+        switch (arc_mode(vw.out)) {
             case 0: hipLaunchKernelGGL((k_bwd_pull_w<0, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
             case 1: hipLaunchKernelGGL((k_bwd_pull_w<1, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
             default: hipLaunchKernelGGL((k_bwd_pull_w<2, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
@@ -587,7 +587,7 @@ void launch_bwd_product(mfbc_graph *g, int ncg, int k, hipStream_t s, hipEvent_t
     if (ev) (void)hipEventRecord(ev[0], s);
     const size_t waves = (size_t)a.ntasks * ncg;
     const int grid = blocks_for(waves, kWavesPerBlock, 0x7fffffff);
-    switch (arc_mode(g->out)) {
+    switch (arc_mode(vw.out)) {
         case 0: hipLaunchKernelGGL((k_bwd_pull<0, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
         case 1: hipLaunchKernelGGL((k_bwd_pull<1, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
         default: hipLaunchKernelGGL((k_bwd_pull<2, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
@@ -653,7 +653,7 @@ void launch_trace_fwd(mfbc_graph *g, int ncg, int nb, int j, uint64_t *d_rows, h
     hipLaunchKernelGGL(k_trace_fwd, dim3(blocks_for(waves, kWavesPerBlock, 0x7fffffff)), dim3(kBlock),
                        0, s, (const uint32_t *)ws.abits[b], (const uint32_t *)ws.fdist[b], g->n,
                        (g->n + 31) / 32, nb, fwd_wide_groups(ncg) ? 1 : 0, (const int32_t *)g->perm,
-                       (const int64_t *)g->out.rp, d_rows, words64, ws.trace_relax + j);
+                       (const int64_t *)g->full.out.rp, d_rows, words64, ws.trace_relax + j);
 }
 
 void launch_export_tiles_i32(mfbc_graph *g, int ncg, int nb, const int32_t *tiles, int32_t *d_rows,

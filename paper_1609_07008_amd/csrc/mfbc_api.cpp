@@ -82,17 +82,21 @@ void dfree(T *&p) {
     p = nullptr;
 }
 
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
 // Every array of the per-batch workspace for `ncg` column groups, in a fixed
 // order: f(pointer, element count).  Used both to allocate the arrays and to
 // carve them out of one block of memory.
 // (g == nullptr: every count is 0, for walks that need only the pointers.)
+// full_dag: the stored DAG sized for every arc rather than the core's (the
+// size mfbc_bc_noalloc admits calls by, which does not depend on the weights).
 template <typename F>
-void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f) {
+void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool full_dag = false) {
     const size_t n = g ? (size_t)g->n : 0;
     const size_t tile = n * kWave * (size_t)ncg;
     const size_t nwords = (n + 31) / 32;
     const size_t slots =
-        g ? (size_t)std::max(g->plan_in.nslots, g->plan_out.nslots) * kWave * (size_t)ncg : 0;
+        g ? (size_t)max_slots(g) * kWave * (size_t)ncg : 0;
     f(ws.tdist, tile);
     f(ws.tsig, tile);
     for (int b = 0; b < 2; b++) {
@@ -106,7 +110,7 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f) {
     f(ws.counters, (size_t)kCounterRing * 4 * kCounterSlots);
     f(ws.flags, (size_t)4);
     f(ws.lam, n * ncg);
-    f(ws.dag, (size_t)std::max<int64_t>(g ? g->arcs : 0, 1) * ncg);
+    f(ws.dag, (size_t)std::max<int64_t>(g ? (full_dag ? g->arcs : g->core.arcs) : 0, 1) * ncg);
     f(ws.src, (size_t)ncg * kWave);
     f(ws.tau2, ncg >= 2 ? tile / 2 : (size_t)1);   // the paired counting product's 16-bit tau
 }
@@ -116,8 +120,6 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f) {
 // to whole pairs; a single group runs alone.
 int ws_groups(int ncg) { return ncg <= 1 ? 1 : (ncg + 1) & ~1; }
 
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
 // Bytes of the workspace of `ncg` groups when carved from one block.
 size_t ws_bytes(const mfbc_graph *g, int ncg) {
     Workspace tmp;
@@ -125,7 +127,7 @@ size_t ws_bytes(const mfbc_graph *g, int ncg) {
     ws_arrays(g, tmp, ws_groups(ncg), [&](auto *&p, size_t count) {
         (void)p;
         off = align256(off + std::max<size_t>(count, 1) * sizeof(*p));
-    });
+    }, true);
     return off;
 }
 
@@ -141,6 +143,23 @@ void free_plan(Plan &p) {
     p.ntasks = p.nhubs = p.nslots = 0;
 }
 
+void free_csr(Csr &c) {
+    dfree(c.rp);
+    dfree(c.col);
+    dfree(c.w);
+    dfree(c.pk);
+    c = Csr{};
+}
+
+// (an undirected view holds one orientation and one plan, twice)
+void free_view(View &v) {
+    if (v.plan_in.tasks != v.plan_out.tasks) free_plan(v.plan_in);
+    free_plan(v.plan_out);
+    if (v.in.rp != v.out.rp) free_csr(v.in);
+    free_csr(v.out);
+    v = View{};
+}
+
 int upload_plan(int32_t n, const int64_t *h_rp, const TaskParams &prm, Plan &plan) {
     std::vector<Task> tasks;
     std::vector<Hub> hubs;
@@ -149,7 +168,7 @@ int upload_plan(int32_t n, const int64_t *h_rp, const TaskParams &prm, Plan &pla
     free_plan(plan);
     int rc;
     if ((rc = dalloc(&plan.tasks, tasks.size()))) return rc;
-    if ((rc = dalloc(&plan.hubs, hubs.size()))) return rc;
+    if (!hubs.empty() && (rc = dalloc(&plan.hubs, hubs.size()))) return rc;
     if (!tasks.empty())
         HIP_TRY(hipMemcpy(plan.tasks, tasks.data(), tasks.size() * sizeof(Task), hipMemcpyHostToDevice));
     if (!hubs.empty())
@@ -253,7 +272,7 @@ int check_sources(mfbc_graph *g, const int32_t *d_sources, int64_t count, hipStr
 // Trace (d_rows non-null or h_relax non-null): frontier membership of F_j
 // after every product j <= max_products, as vertex bitmaps per column
 // (d_rows + (j-1) * nb * words), and the relaxations of every product.
-int run_forward(mfbc_graph *g, int ncg, int nb, bool trace, uint64_t *d_rows, int64_t *h_nnz,
+int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, bool trace, uint64_t *d_rows, int64_t *h_nnz,
                 int64_t *h_relax, int max_products, int32_t *products, hipStream_t s) {
     launch_fwd_init(g, ncg, nb, s);
     if (trace) launch_trace_fwd(g, ncg, nb, 0, nullptr, s);
@@ -266,7 +285,7 @@ int run_forward(mfbc_graph *g, int ncg, int nb, bool trace, uint64_t *d_rows, in
         if (j > g->n + 1) return fail(MFBC_EDEVICE, "forward products did not converge");
         for (int i = 0; i < kWindow; i++) {
             const int jj = j + 1 + i;
-            launch_fwd_product(g, ncg, jj, s, window_events(g, i, true));
+            launch_fwd_product(g, vw, ncg, jj, s, window_events(g, i, true));
             if (trace)
                 launch_trace_fwd(g, ncg, nb, jj,
                                  d_rows && jj <= max_products ? d_rows + (size_t)(jj - 1) * nb * words
@@ -313,7 +332,7 @@ int run_forward(mfbc_graph *g, int ncg, int nb, bool trace, uint64_t *d_rows, in
 // Algorithm 2 on the batch whose T is in the workspace: the counting
 // product (window position 0 of the first window), then backward products
 // in windows as in run_forward, until one produces no frontier entry.
-int run_backward(mfbc_graph *g, int ncg, int nb, int32_t *products, hipStream_t s) {
+int run_backward(mfbc_graph *g, const View &vw, int ncg, int nb, int32_t *products, hipStream_t s) {
     const double arc_bytes = g->weighted ? 8.0 : 4.0;
     mfbc_stats &st = g->stats;
     int64_t prev = 0;
@@ -323,11 +342,11 @@ int run_backward(mfbc_graph *g, int ncg, int nb, int32_t *products, hipStream_t 
         for (int i = 0; i < kWindow; i++) {
             const int kk = k + i;
             if (kk == 0) {
-                const hipError_t e = launch_bwd_count(g, ncg, s, window_events(g, i, false));
+                const hipError_t e = launch_bwd_count(g, vw, ncg, s, window_events(g, i, false));
                 if (e != hipSuccess)
                     return fail(MFBC_EDEVICE, std::string("counting product: ") + hipGetErrorString(e));
             } else {
-                launch_bwd_product(g, ncg, kk, s, window_events(g, i, false));
+                launch_bwd_product(g, vw, ncg, kk, s, window_events(g, i, false));
             }
         }
         int rc = read_ring(g, s);
@@ -344,9 +363,9 @@ int run_backward(mfbc_graph *g, int ncg, int nb, int32_t *products, hipStream_t 
                 // initialised (counter 4 B, zeta 8 B, frontier index 4 B
                 // when traced), and each leaf's sigma read and 1/sigma written
                 const double state = g->trace_step ? 16.0 : 12.0;
-                st.count_alg_bytes += arc_bytes * (double)g->arcs + 8.0 * g->n +
+                st.count_alg_bytes += arc_bytes * (double)vw.arcs + 8.0 * g->n +
                                       (8.0 + state) * (double)g->n * nb +
-                                      8.0 * (double)g->arcs * ncg + 16.0 * (double)c.produced;
+                                      8.0 * (double)vw.arcs * ncg + 16.0 * (double)c.produced;
                 if (g->timing == 1) {
                     float t = 0.f;
                     if (hipEventElapsedTime(&t, g->ev[0], g->ev[2]) == hipSuccess) st.count_ms += t;
@@ -406,7 +425,7 @@ int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d
     }
     g->stats = mfbc_stats{};
     launch_set_sources(g, ncg, nb, d_sources, s);
-    if ((rc = run_forward(g, ncg, nb, trace, d_rows, h_nnz, h_relax, max_products, h_products, s)))
+    if ((rc = run_forward(g, g->full, ncg, nb, trace, d_rows, h_nnz, h_relax, max_products, h_products, s)))
         return rc;
     g->stats.batches = 1;
     launch_export_forward(g, ncg, nb, d_dist, d_sigma, s);
@@ -431,7 +450,7 @@ int backward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, const int
     launch_set_sources(g, ncg, nb, d_sources, s);
     launch_import_forward(g, ncg, nb, d_dist, d_sigma, s);
     g->trace_step = d_step != nullptr;
-    rc = run_backward(g, ncg, nb, h_products, s);
+    rc = run_backward(g, g->core, ncg, nb, h_products, s);
     g->trace_step = false;
     if (rc) return rc;
     g->stats.batches = 1;
@@ -476,6 +495,170 @@ int upload_csr(int32_t n, int64_t arcs, const int64_t *rp, const int32_t *col, c
     return MFBC_OK;
 }
 
+// The plans of one view (one for both orientations of an undirected graph).
+int plan_view(int32_t n, bool directed, const std::vector<int64_t> &rp_out, const std::vector<int64_t> &rp_in,
+              const TaskParams &p, View &v) {
+    if (!directed) v.plan_in = Plan{};
+    int rc = upload_plan(n, rp_out.data(), p, v.plan_out);
+    if (!rc && directed) rc = upload_plan(n, rp_in.data(), p, v.plan_in);
+    if (!rc && !directed) v.plan_in = v.plan_out;
+    return rc;
+}
+
+// Work decompositions of both views; knobs <= 0 take the default of the
+// view's own size.
+int plan_views(mfbc_graph *g, const TaskParams &knobs) {
+    auto params = [&](bool core) {
+        TaskParams p = core ? core_params(g->n, g->core.arcs) : default_params(g->n, g->full.arcs);
+        if (knobs.run_arcs > 0) p.run_arcs = knobs.run_arcs;
+        if (knobs.run_verts > 0) p.run_verts = knobs.run_verts;
+        if (knobs.heavy > 0) p.heavy = knobs.heavy;
+        if (knobs.slice > 0) p.slice = knobs.slice;
+        return p;
+    };
+    g->params = params(false);
+    const int rc = plan_view(g->n, g->directed, g->h_rp_out, g->h_rp_in, g->params, g->full);
+    if (!g->has_core) {
+        g->core = g->full;       // also after a failure: no stale pointers
+        return rc;
+    }
+    if (rc) return rc;
+    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, params(true), g->core);
+}
+
+// One block of device memory, handed out in parts and freed at the end of
+// the scope: take() before alloc() adds up the sizes, after it places them.
+struct Scratch {
+    char *base = nullptr;
+    size_t off = 0;
+    template <typename T>
+    void take(T **p, size_t count) {
+        *p = base ? (T *)(base + off) : nullptr;
+        off = align256(off + std::max<size_t>(count, 1) * sizeof(T));
+    }
+    bool alloc() {
+        const size_t need = off;
+        off = 0;
+        if (hipMalloc((void **)&base, need) == hipSuccess) return true;
+        (void)hipGetLastError();
+        base = nullptr;
+        return false;
+    }
+    ~Scratch() {
+        if (base) (void)hipFree(base);
+    }
+};
+
+// Upper bounds of the distances from the landmarks (ws.src) to every vertex
+// along the arcs of t.full.in, in t.ws.tdist: the walks of at most kWindow
+// arcs.  Longer ones drop few arcs more (uniform graph of degree 256: 6.91%
+// kept against 6.90%; R-MAT scale 16: the same 8.71%).
+void landmark_bounds(mfbc_graph &t, int count, hipStream_t s) {
+    launch_mono_init(&t, MFBC_OP_SSSP, 1, count, s);
+    for (int j = 1; j <= kWindow; j++) launch_mono_product(&t, MFBC_OP_SSSP, 1, j, s, nullptr);
+}
+
+// The core of one orientation: rows of bounds `near` for the row vertices,
+// `far` for the others.  Leaves c2 empty if too few arcs go.
+int core_csr(mfbc_graph *g, const Csr &c, const Plan &pl, const int32_t *near, const int32_t *far,
+             uint8_t *keep, int32_t *cnt, Csr &c2, std::vector<int64_t> &rp2, hipStream_t s) {
+    std::vector<int32_t> h((size_t)g->n);
+    launch_core_zero(cnt, g->n, s);
+    launch_core_mark(c, pl, near, far, keep, cnt, s);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(h.data(), cnt, (size_t)g->n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    rp2.resize((size_t)g->n + 1);
+    rp2[0] = 0;
+    for (int32_t v = 0; v < g->n; v++) rp2[(size_t)v + 1] = rp2[(size_t)v] + h[(size_t)v];
+    const int64_t arcs = rp2.back();
+    // a core of nearly every arc saves little and costs its memory
+    if ((double)arcs > 0.75 * (double)g->arcs) return MFBC_OK;
+    int rc;
+    // packed arcs are all that the products read
+    if ((rc = dalloc(&c2.rp, rp2.size())) || (c.pk && (rc = dalloc(&c2.pk, (size_t)arcs))) ||
+        (!c.pk && ((rc = dalloc(&c2.col, (size_t)arcs)) || (rc = dalloc(&c2.w, (size_t)arcs)))))
+        return rc;
+    c2.cb = c.cb;
+    HIP_TRY(hipMemcpyAsync(c2.rp, rp2.data(), rp2.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
+    launch_core_compact(g->n, c, keep, c2, s);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(s));
+    return MFBC_OK;
+}
+
+// Builds g->core (core.hip).  The graph stays without one where memory for
+// the bounds is short or too few arcs go; both are no error.
+int build_core(mfbc_graph *g, hipStream_t s) {
+    const size_t n = (size_t)g->n, tile = n * kWave;
+    // landmarks: the vertices of highest degree
+    const int count = (int)std::min<size_t>(n, (size_t)kLandmarks);
+    std::vector<int32_t> v(n);
+    for (size_t i = 0; i < n; i++) v[i] = (int32_t)i;
+    auto deg = [&](int32_t x) {
+        return g->h_rp_out[(size_t)x + 1] - g->h_rp_out[(size_t)x] + g->h_rp_in[(size_t)x + 1] -
+               g->h_rp_in[(size_t)x];
+    };
+    if (g->h_perm.empty())     // else the numbering is by descending degree already
+        std::partial_sort(v.begin(), v.begin() + count, v.end(), [&](int32_t a, int32_t b) {
+            return deg(a) != deg(b) ? deg(a) > deg(b) : a < b;
+        });
+    Scratch mem;
+    mfbc_graph t;
+    t.device = g->device;
+    t.n = g->n;
+    t.arcs = g->arcs;
+    t.maxw = g->maxw;
+    t.weighted = true;
+    t.full = g->full;
+    Workspace &ws = t.ws;
+    const size_t words = (n + 31) / 32;
+    int32_t *from = nullptr, *to = nullptr, *cnt = nullptr;
+    uint8_t *keep = nullptr;
+    for (int pass = 0; pass < 2; pass++) {
+        mem.take(&from, tile);
+        if (g->directed) mem.take(&to, tile);
+        for (int i = 0; i < 2; i++) {
+            mem.take(&ws.fdist[i], tile);
+            mem.take(&ws.abits[i], words);
+        }
+        mem.take(&ws.pd, (size_t)max_slots(g) * kWave);
+        mem.take(&ws.counters, (size_t)kCounterRing * 4 * kCounterSlots);
+        mem.take(&ws.src, (size_t)kWave);
+        mem.take(&keep, (size_t)g->arcs);
+        mem.take(&cnt, n);
+        if (pass == 0 && !mem.alloc()) return MFBC_OK;
+    }
+    HIP_TRY(hipMemcpyAsync(ws.src, v.data(), (size_t)count * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    int rc;
+    ws.tdist = from;
+    landmark_bounds(t, count, s);
+    if (g->directed) {
+        std::swap(t.full.in, t.full.out);
+        std::swap(t.full.plan_in, t.full.plan_out);
+        ws.tdist = to;
+        landmark_bounds(t, count, s);
+    } else {
+        to = from;
+    }
+    View c;
+    rc = core_csr(g, g->full.out, g->full.plan_out, to, from, keep, cnt, c.out, g->h_core_rp_out, s);
+    if (!rc && c.out.rp && g->directed)
+        rc = core_csr(g, g->full.in, g->full.plan_in, from, to, keep, cnt, c.in, g->h_core_rp_in, s);
+    if (rc || !c.out.rp) {
+        free_view(c);
+        return rc == MFBC_ENOMEM ? MFBC_OK : rc;
+    }
+    if (!g->directed) {
+        c.in = c.out;
+        g->h_core_rp_in = g->h_core_rp_out;
+    }
+    c.arcs = g->h_core_rp_out.back();
+    g->core = c;
+    g->has_core = true;
+    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs), g->core);
+}
+
 // Release a lane view: its workspace, counters and events (the device graph
 // it shares stays with its owner).
 void free_shadow(mfbc_graph *sh) {
@@ -503,20 +686,10 @@ void free_graph_memory(mfbc_graph *g) {
     }
     g->timing = false;
     free_workspace(g->ws);
-    free_plan(g->plan_in);
-    free_plan(g->plan_out);
-    const bool alias = g->in.rp == g->out.rp;
-    dfree(g->out.rp);
-    dfree(g->out.col);
-    dfree(g->out.w);
-    dfree(g->out.pk);
-    if (!alias) {
-        dfree(g->in.rp);
-        dfree(g->in.col);
-        dfree(g->in.w);
-        dfree(g->in.pk);
-    }
-    g->in = Csr{};
+    if (g->has_core) free_view(g->core);
+    g->core = View{};
+    g->has_core = false;
+    free_view(g->full);
     dfree(g->perm);
     g->h_perm.clear();
     if (g->h_ctr) (void)hipHostFree(g->h_ctr);
@@ -539,9 +712,9 @@ int bc_batches(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32
         const int nb = (int)std::min<int64_t>(batch, n_sources - b0);
         const int bcg = (nb + kWave - 1) / kWave;
         launch_set_sources(g, bcg, nb, d_sources + b0, s);
-        if ((rc = run_forward(g, bcg, nb, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
+        if ((rc = run_forward(g, g->core, bcg, nb, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
             return rc;
-        if ((rc = run_backward(g, bcg, nb, nullptr, s))) return rc;
+        if ((rc = run_backward(g, g->core, bcg, nb, nullptr, s))) return rc;
         g->stats.batches++;
     }
     launch_lambda_reduce(g, ncg, d_bc, s);
@@ -557,7 +730,7 @@ int bc_batches(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32
 int lanes_for(const mfbc_graph *g, int64_t n_batches, int ncg) {
     int S = g->lanes;
     // by default only where a product is too small to fill the device
-    if (S <= 0) S = (double)g->arcs * (double)ncg <= (double)(1 << 24) ? kMaxLanes : 1;
+    if (S <= 0) S = (double)g->core.arcs * (double)ncg <= (double)(1 << 24) ? kMaxLanes : 1;
     return (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)S, (int64_t)kMaxLanes, n_batches}));
 }
 
@@ -588,10 +761,9 @@ int lane_graph(mfbc_graph *g, int i, mfbc_graph **out) {
     sh->maxw = g->maxw;
     sh->weighted = g->weighted;
     sh->directed = g->directed;
-    sh->out = g->out;
-    sh->in = g->in;
-    sh->plan_out = g->plan_out;
-    sh->plan_in = g->plan_in;
+    sh->full = g->full;
+    sh->core = g->core;
+    sh->has_core = g->has_core;
     sh->mb = g->mb;
     sh->params = g->params;
     sh->perm = g->perm;
@@ -647,8 +819,8 @@ int bc_lanes(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t
             const int nb = (int)std::min<int64_t>(batch, n_sources - b0);
             const int bcg = (nb + kWave - 1) / kWave;
             launch_set_sources(x, bcg, nb, d_sources + b0, ls[i]);
-            if (!r) r = run_forward(x, bcg, nb, false, nullptr, nullptr, nullptr, 0, nullptr, ls[i]);
-            if (!r) r = run_backward(x, bcg, nb, nullptr, ls[i]);
+            if (!r) r = run_forward(x, x->core, bcg, nb, false, nullptr, nullptr, nullptr, 0, nullptr, ls[i]);
+            if (!r) r = run_backward(x, x->core, bcg, nb, nullptr, ls[i]);
             x->stats.batches++;
         }
         if (!r && hipStreamSynchronize(ls[i]) != hipSuccess) r = fail(MFBC_EDEVICE, "lane stream failed");
@@ -774,13 +946,13 @@ int mfbc_load_graph(int32_t n, int64_t n_arcs, const int64_t *h_row_ptr, const i
     // packed frontier tuples: weight bits for (n - 1) * max weight (+1 so that
     // no tuple equals the all-ones "absent" marker), the rest for multiplicities
     g->mb = 32 - bits_for((int64_t)(n - 1) * maxw + 1);
-    int rc = upload_csr(n, n_arcs, rp_o, col_o, w_o, maxw, g->out);
+    int rc = upload_csr(n, n_arcs, rp_o, col_o, w_o, maxw, g->full.out);
     if (!rc) {
         if (directed)
             rc = upload_csr(n, n_arcs, rpt.data(), colt.data(), h_weight ? wt.data() : nullptr,
-                            maxw, g->in);
+                            maxw, g->full.in);
         else
-            g->in = g->out;
+            g->full.in = g->full.out;
     }
     if (!rc && !perm.empty()) {
         if (!(rc = dalloc(&g->perm, (size_t)n))) {
@@ -790,7 +962,6 @@ int mfbc_load_graph(int32_t n, int64_t n_arcs, const int64_t *h_row_ptr, const i
             g->h_perm = std::move(perm);
         }
     }
-    g->params = default_params(n, n_arcs);
     g->h_rp_out.assign(rp_o, rp_o + (size_t)n + 1);
     g->h_rp_in = directed ? rpt : g->h_rp_out;
     if (!rc && hipHostMalloc((void **)&g->h_ctr,
@@ -799,14 +970,14 @@ int mfbc_load_graph(int32_t n, int64_t n_arcs, const int64_t *h_row_ptr, const i
         g->h_ctr = nullptr;
         rc = fail(MFBC_ENOMEM, "pinned host allocation failed");
     }
-    if (!rc) rc = upload_plan(n, g->h_rp_out.data(), g->params, g->plan_out);
-    if (!rc) rc = upload_plan(n, g->h_rp_in.data(), g->params, g->plan_in);
+    g->full.arcs = n_arcs;
+    if (!rc) rc = plan_views(g, TaskParams{0, 0, 0, 0});
+    if (!rc && core_worth_trying(g)) rc = build_core(g, (hipStream_t)hip_stream);
     if (rc) {
         free_graph_memory(g);
         delete g;
         return rc;
     }
-    (void)hip_stream;
     *out = g;
     return MFBC_OK;
 }
@@ -967,9 +1138,9 @@ int mfbc_bc_requests(mfbc_graph *g, const int32_t *d_sources, const int64_t *h_f
         launch_set_sources_spans(g, bcg, d_sources, sp, s);
         launch_lambda_zero(g, bcg, s);
         // padding columns (source -1) seed nothing and reach nothing
-        if ((rc = run_forward(g, bcg, bcg * kWave, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
+        if ((rc = run_forward(g, g->core, bcg, bcg * kWave, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
             return rc;
-        if ((rc = run_backward(g, bcg, bcg * kWave, nullptr, s))) return rc;
+        if ((rc = run_backward(g, g->core, bcg, bcg * kWave, nullptr, s))) return rc;
         launch_lambda_add_groups(g, bcg, o, s);
         g->stats.batches++;
     }
@@ -1029,19 +1200,12 @@ int mfbc_set_plan(mfbc_graph *g, int32_t run_arcs, int32_t run_verts, int32_t he
         return fail(MFBC_EINVAL, "the graph has live servers (mfbc_server_create); free them "
                                  "before changing its plan");
     DeviceGuard dg(g->device);
-    TaskParams p = default_params(g->n, g->arcs);
-    if (run_arcs > 0) p.run_arcs = run_arcs;
-    if (run_verts > 0) p.run_verts = run_verts;
-    if (heavy > 0) p.heavy = heavy;
-    if (slice > 0) p.slice = slice;
     HIP_TRY(hipDeviceSynchronize());
-    const int32_t old_slots = std::max(g->plan_in.nslots, g->plan_out.nslots);
-    g->params = p;
-    int rc = upload_plan(g->n, g->h_rp_out.data(), p, g->plan_out);
-    if (!rc) rc = upload_plan(g->n, g->h_rp_in.data(), p, g->plan_in);
+    const int32_t old_slots = max_slots(g);
+    const int rc = plan_views(g, TaskParams{run_arcs, run_verts, heavy, slice});
     if (rc) return rc;
     // the partial buffers are sized by the slot count: regrow on next use
-    if (std::max(g->plan_in.nslots, g->plan_out.nslots) > old_slots) {
+    if (max_slots(g) > old_slots) {
         free_workspace(g->ws);
         for (auto *sh : g->shadow)
             if (sh) free_workspace(sh->ws);
@@ -1105,8 +1269,8 @@ int mfbc_bc_many(int32_t n_graphs, mfbc_graph *const *graphs, const int32_t *con
     int64_t arcs_max = 1;
     for (auto *g : gs) {
         n_max = std::max(n_max, g->n);
-        slots_max = std::max({slots_max, g->plan_in.nslots, g->plan_out.nslots});
-        arcs_max = std::max<int64_t>(arcs_max, g->arcs);
+        slots_max = std::max(slots_max, max_slots(g));
+        arcs_max = std::max<int64_t>(arcs_max, g->core.arcs);
     }
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
@@ -1125,8 +1289,8 @@ int mfbc_bc_many(int32_t n_graphs, mfbc_graph *const *graphs, const int32_t *con
         std::vector<int64_t> n2;
         std::vector<double *> o2;
         for (size_t i = 0; i < gs.size(); i++) {
-            const Csr &c = gs[i]->in;
-            const int m = c.w == nullptr ? 0 : (c.pk ? 1 : 2);
+            const Csr &c = gs[i]->core.in;
+            const int m = c.pk ? 1 : (c.w ? 2 : 0);
             if (m != mode) continue;
             g2.push_back(gs[i]);
             s2.push_back(src[i]);

@@ -73,6 +73,14 @@ struct Csr {
     int cb = 32;             // bits of a column index in pk
 };
 
+// The arcs a call's products run over and their work decomposition.
+struct View {
+    Csr out;                 // out-arcs (backward products, counting product)
+    Csr in;                  // in-arcs (forward products); aliases `out` if undirected
+    Plan plan_out, plan_in;
+    int64_t arcs = 0;
+};
+
 struct Workspace {
     int ncg = 0;                       // capacity in column groups
     int32_t *tdist = nullptr;          // T.w      [cg][n][64]
@@ -104,14 +112,18 @@ struct mfbc_graph {
     int32_t maxw = 1;
     bool weighted = false;
     bool directed = false;
-    mfbc::Csr out;          // out-arcs (backward products, counting product)
-    mfbc::Csr in;           // in-arcs (forward products); aliases `out` if undirected
-    mfbc::Plan plan_out, plan_in;
+    // full: every arc (calls whose results depend on the frontiers themselves:
+    // mfbc_forward, the traces, the fixpoints).  core: the arcs that can lie on
+    // a shortest path (core.hip), for every call whose result is a function of
+    // distances and path counts; the same arrays as `full` unless has_core.
+    mfbc::View full, core;
+    bool has_core = false;
     int mb = 1;             // inline multiplicity bits of a packed frontier tuple
     mfbc::TaskParams params;
     mfbc::Workspace ws;
     mfbc_stats stats{};
     std::vector<int64_t> h_rp_out, h_rp_in;   // host copies for re-planning
+    std::vector<int64_t> h_core_rp_out, h_core_rp_in;
     // Vertex order of the device copy: caller id v is stored as vertex perm[v]
     // (null / empty when the caller's order is kept).  Every entry point maps
     // sources through it and gathers per-vertex outputs back.
@@ -143,9 +155,9 @@ void launch_fwd_init(mfbc_graph *g, int ncg, int nb, hipStream_t s);
 // `ev` (nullable): three events recorded before the product kernel, between
 // it and the merge kernel, and after the merge.  Product j (k) skips itself
 // on the device when product j-1 (k-1) produced no frontier entry.
-void launch_fwd_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev);
-hipError_t launch_bwd_count(mfbc_graph *g, int ncg, hipStream_t s, hipEvent_t *ev);
-void launch_bwd_product(mfbc_graph *g, int ncg, int k, hipStream_t s, hipEvent_t *ev);
+void launch_fwd_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s, hipEvent_t *ev);
+hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t s, hipEvent_t *ev);
+void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, int k, hipStream_t s, hipEvent_t *ev);
 // Trace: membership of forward frontier F_j (j = 0: the sources) as
 // per-column vertex bitmaps in caller order (d_rows: nb rows of (n+63)/64
 // words; nullable), and the out-degrees of its members added to
@@ -196,6 +208,26 @@ int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const in
                    int block_threads, int blocks, int w, hipStream_t s, ManyWorkspace &ws,
                    unsigned long long *h_stats, int32_t *h_flags, std::string &err);
 ManyWorkspace &many_workspace(int device);
+
+// ---- shortest-path core (core.hip) ----
+constexpr int kLandmarks = kWave;        // one per lane
+bool core_worth_trying(const mfbc_graph *g);
+TaskParams core_params(int32_t n, int64_t arcs);   // default decomposition of a core
+// Flags of the arcs of one orientation that pass the landmark test (byte per
+// arc) and their number per row.  `near`[v][64], `far`[v][64]: see core.hip.
+void launch_core_mark(const Csr &c, const Plan &pl, const int32_t *near, const int32_t *far, uint8_t *keep,
+                      int32_t *cnt, hipStream_t s);
+void launch_core_zero(int32_t *cnt, int n, hipStream_t s);
+// The kept arcs of every row, in order, at rows rp2.
+void launch_core_compact(int32_t n, const Csr &c, const uint8_t *keep, const Csr &out, hipStream_t s);
+// Hub partial slots the workspace must hold for any plan of the graph.
+inline int32_t max_slots(const mfbc_graph *g) {
+    int32_t m = 0;
+    for (const View *v : {&g->full, &g->core})
+        for (const Plan *p : {&v->plan_in, &v->plan_out})
+            if (p->nslots > m) m = p->nslots;
+    return m;
+}
 
 // Record the message of a failure for mfbc_last_error(); returns `code`.
 int set_error(int code, const std::string &msg);

@@ -299,7 +299,7 @@ ArcSrc mono_arcs(const Csr &c) {
     return r;
 }
 
-int mono_mode(const Csr &c) { return c.w == nullptr ? 0 : (c.pk ? 1 : 2); }
+int mono_mode(const Csr &c) { return c.pk ? 1 : (c.w ? 2 : 0); }
 
 template <class Op, int W>
 void launch_pull(int mode, int grid, hipStream_t s, const MonoArgs &a) {
@@ -341,16 +341,16 @@ void mono_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev) 
     Workspace &ws = g->ws;
     const int b = (j - 1) & 1;      // buffer holding F_{j-1}
     MonoArgs a{};
-    a.tasks = g->plan_in.tasks;
-    a.hubs = g->plan_in.hubs;
-    a.ntasks = g->plan_in.ntasks;
-    a.nhubs = g->plan_in.nhubs;
-    a.nslots = g->plan_in.nslots;
+    a.tasks = g->full.plan_in.tasks;
+    a.hubs = g->full.plan_in.hubs;
+    a.ntasks = g->full.plan_in.ntasks;
+    a.nhubs = g->full.plan_in.nhubs;
+    a.nslots = g->full.plan_in.nslots;
     a.ncg = ncg;
     a.n = g->n;
     a.nwords = (g->n + 31) / 32;
-    a.rp = g->in.rp;
-    a.arcs = mono_arcs(g->in);
+    a.rp = g->full.in.rp;
+    a.arcs = mono_arcs(g->full.in);
     a.abits = ws.abits[b];
     a.fval = ws.fdist[b];
     a.tval = ws.tdist;
@@ -365,8 +365,8 @@ void mono_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev) 
     const int waves_per_task = a.nwide ? a.nwide : ncg;
     if (ev) (void)hipEventRecord(ev[0], s);
     const int grid = nblk((size_t)a.ntasks * waves_per_task, kWavesPerBlock);
-    if (a.nwide) launch_pull<Op, 2>(mono_mode(g->in), grid, s, a);
-    else launch_pull<Op, 1>(mono_mode(g->in), grid, s, a);
+    if (a.nwide) launch_pull<Op, 2>(mono_mode(g->full.in), grid, s, a);
+    else launch_pull<Op, 1>(mono_mode(g->full.in), grid, s, a);
     if (ev) (void)hipEventRecord(ev[1], s);
     const int mgrid = std::max(nblk((size_t)a.nhubs * waves_per_task, kWavesPerBlock),
                                nblk((size_t)a.nwords, kBlock, 1024));

@@ -313,7 +313,7 @@ ArcSrc srv_arc_src(const Csr &c) {
     return r;
 }
 
-int srv_mode(const Csr &c) { return c.w == nullptr ? 0 : (c.pk ? 1 : 2); }
+int srv_mode(const Csr &c) { return c.pk ? 1 : (c.w ? 2 : 0); }
 
 int stage(mfbc_server *s, size_t bytes) {
     if (s->meta_bytes >= bytes) return MFBC_OK;
@@ -346,12 +346,12 @@ extern "C" {
 int mfbc_server_footprint(const mfbc_graph *g, int32_t width, int64_t *bytes) {
     if (!g || !bytes || width < 64 || width % 64) return sfail(MFBC_EINVAL, "bad arguments");
     const int64_t n = g->n, ncg = width / 64, ncg2 = (ncg + 1) & ~1;
-    const int64_t slots = std::max(g->plan_in.nslots, g->plan_out.nslots);
+    const int64_t slots = max_slots(g);
     const int64_t nw = (n + 31) / 32;
     // tiles: T (4 + 8), frontier tuples (2 x (4 + 8)), counters, zeta, q
     // (4 + 8 + 8) and the counting product's 16-bit tau copy (2), per (column, vertex)
     *bytes = n * 64 * ncg2 * (4 + 8 + 2 * 4 + 2 * 8 + 4 + 8 + 8 + 2) + 2 * ncg2 * n * 8 +
-             4 * ncg * nw * 4 + slots * 64 * ncg2 * 12 + ncg * std::max<int64_t>(g->arcs, 1) * 8;
+             4 * ncg * nw * 4 + slots * 64 * ncg2 * 12 + ncg * std::max<int64_t>(g->core.arcs, 1) * 8;
     return MFBC_OK;
 }
 
@@ -372,7 +372,7 @@ int mfbc_server_create(mfbc_graph *g, int32_t width, mfbc_server **out) {
     // per-(column, vertex) tiles and hub slots cover whole pairs
     const size_t n = (size_t)g->n, ncg = (size_t)s->ncg, ncg2 = (size_t)s->npair * kWide;
     const size_t tile = n * kWave * ncg2;
-    const size_t slots = (size_t)std::max(g->plan_in.nslots, g->plan_out.nslots) * kWave * ncg2;
+    const size_t slots = (size_t)max_slots(g) * kWave * ncg2;
     int rc = MFBC_OK;
     if (salloc(&s->tdist, tile) || salloc(&s->tsig, tile) || salloc(&s->ftup[0], tile) ||
         salloc(&s->ftup[1], tile) || salloc(&s->fsig[0], tile) || salloc(&s->fsig[1], tile) ||
@@ -383,7 +383,7 @@ int mfbc_server_create(mfbc_graph *g, int32_t width, mfbc_server **out) {
         salloc(&s->pd, slots) || salloc(&s->pm, slots) || salloc(&s->src, (size_t)width) ||
         salloc(&s->ctr, kCtrWords) || salloc(&s->colmask, (size_t)kMaxRounds * 3 * 32 * ncg) ||
         salloc(&s->cmask, ncg) || salloc(&s->newmask, ncg) || salloc(&s->cglists, 4 * ncg) ||
-        salloc(&s->flags, 4) || salloc(&s->dag, ncg * (size_t)std::max<int64_t>(g->arcs, 1)))
+        salloc(&s->flags, 4) || salloc(&s->dag, ncg * (size_t)std::max<int64_t>(g->core.arcs, 1)))
         rc = MFBC_ENOMEM;
     if (!rc && hipHostMalloc((void **)&s->h_colmask, 2 * 3 * 32 * ncg * 8) != hipSuccess) rc = MFBC_ENOMEM;
     if (!rc && hipHostMalloc((void **)&s->h_stage, 4 * ncg * 4 + ncg * 8) != hipSuccess) rc = MFBC_ENOMEM;
@@ -411,7 +411,7 @@ int mfbc_server_create(mfbc_graph *g, int32_t width, mfbc_server **out) {
         delete s;
         return sfail(rc, rc == MFBC_ENOMEM ? "device allocation failed" : "initialisation failed");
     }
-    s->slot_cap = std::max(g->plan_in.nslots, g->plan_out.nslots);
+    s->slot_cap = max_slots(g);
     g->servers++;              // the graph's plan is frozen while servers are attached
     s->h_src.assign((size_t)width, -1);
     s->phase.assign((size_t)width, kFree);
@@ -518,7 +518,7 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
     if (s->launched) return sfail(MFBC_EINVAL, "a step is already in flight");
     hipStream_t st = (hipStream_t)hip_stream;
     mfbc_graph *g = s->g;
-    if (std::max(g->plan_in.nslots, g->plan_out.nslots) > s->slot_cap)
+    if (max_slots(g) > s->slot_cap)
         return sfail(MFBC_EINVAL, "the graph's plan needs more hub partial slots than the server holds");
     int prev = -1;
     (void)hipGetDevice(&prev);
@@ -575,17 +575,17 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
     const int nw = s->nwords;
     const size_t cmw = 3 * 32 * ncg;                 // colmask words of one round
     BwdArgs c{};
-    c.tasks = g->plan_out.tasks;
-    c.hubs = g->plan_out.hubs;
-    c.ntasks = g->plan_out.ntasks;
-    c.nhubs = g->plan_out.nhubs;
-    c.nslots = g->plan_out.nslots;
+    c.tasks = g->core.plan_out.tasks;
+    c.hubs = g->core.plan_out.hubs;
+    c.ntasks = g->core.plan_out.ntasks;
+    c.nhubs = g->core.plan_out.nhubs;
+    c.nslots = g->core.plan_out.nslots;
     c.ncg_all = s->ncg;
     c.nwide_all = s->npair;                          // backward state interleaved per pair
     c.n = g->n;
     c.nwords = nw;
-    c.rp = g->out.rp;
-    c.arcs = srv_arc_src(g->out);
+    c.rp = g->core.out.rp;
+    c.arcs = srv_arc_src(g->core.out);
     c.src = s->src;
     c.tdist = s->tdist;
     c.tsig = s->tsig;
@@ -602,8 +602,8 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
     // admission), so its DAG masks are written whole and stay valid for its
     // backward loop
     c.dag = s->dag;
-    c.narcs = g->arcs;
-    const int mode = srv_mode(g->out);
+    c.narcs = g->core.arcs;
+    const int mode = srv_mode(g->core.out);
     if (s->any_c) {
         // counting product of the pairs whose forward loop ended; their first
         // backward frontier joins the buffer the first backward round reads
@@ -656,11 +656,11 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
         if (s->any_f) {
             const int b = s->cur_f;
             FwdArgs a{};
-            a.tasks = g->plan_in.tasks;
-            a.hubs = g->plan_in.hubs;
-            a.ntasks = g->plan_in.ntasks;
-            a.nhubs = g->plan_in.nhubs;
-            a.nslots = g->plan_in.nslots;
+            a.tasks = g->core.plan_in.tasks;
+            a.hubs = g->core.plan_in.hubs;
+            a.ntasks = g->core.plan_in.ntasks;
+            a.nhubs = g->core.plan_in.nhubs;
+            a.nslots = g->core.plan_in.nslots;
             a.ncg = nf * kWide;
             a.ncg_all = s->ncg;
             a.nwide = nf;
@@ -670,8 +670,8 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
             a.j = ++s->kfwd;
             a.nwords = nw;
             a.mb = g->mb;
-            a.rp = g->in.rp;
-            a.arcs = srv_arc_src(g->in);
+            a.rp = g->core.in.rp;
+            a.arcs = srv_arc_src(g->core.in);
             a.abits = s->abf[b];
             a.ftup = s->ftup[b];
             a.fsig = s->fsig[b];
@@ -689,7 +689,7 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
             a.clear_ctr = s->ctr + ctr_slot(0, r + 1);
             a.colmask = s->colmask + (size_t)r * cmw;
             const int grid = nblocks((size_t)a.ntasks * nf, kWavesPerBlock, 0x7fffffff);
-            switch (srv_mode(g->in)) {
+            switch (srv_mode(g->core.in)) {
                 case 0: hipLaunchKernelGGL((k_fwd_pull_w<0, kWide, true>), dim3(grid), dim3(kBlock), 0, st, a); break;
                 case 1: hipLaunchKernelGGL((k_fwd_pull_w<1, kWide, true>), dim3(grid), dim3(kBlock), 0, st, a); break;
                 default: hipLaunchKernelGGL((k_fwd_pull_w<2, kWide, true>), dim3(grid), dim3(kBlock), 0, st, a); break;
