@@ -14,7 +14,7 @@
 //
 // The landmarks are the vertices of highest degree, one per lane, and the
 // bounds one 64-column run of the fixpoint product (min, a + w) stopped after
-// one window of products: an unfinished run leaves weights of walks, which
+// six products: an unfinished run leaves weights of walks, which
 // are upper bounds all the same.
 #include <algorithm>
 
@@ -128,13 +128,15 @@ bool core_worth_trying(const mfbc_graph *g) {
 // these: directed R-MAT n = 100,003, 300 sources 3.84 / 2.92; dependencies of
 // 130 sources at R-MAT scale 18 2.43 / 2.26; 256 sources at scale 20 the same
 // 16.5, where a run has 64 rows either way.
-TaskParams core_params(int32_t n, int64_t arcs) {
+TaskParams core_params(int32_t n, int64_t arcs, int64_t full_arcs) {
     constexpr int64_t kTarget = 16384;
     TaskParams p;
     p.run_verts = (int)std::min<int64_t>(64, std::max<int64_t>(16, (n + kTarget - 1) / kTarget));
     p.run_arcs = (int)std::min<int64_t>(256, std::max<int64_t>(64, (arcs + kTarget - 1) / kTarget));
-    p.heavy = 256;
-    p.slice = 128;
+    // (longer slices for a core of most arcs: its DAG masks and partials stay
+    // within the memory of the whole graph's masks)
+    p.slice = 15 * full_arcs < 32 * arcs ? 256 : 128;
+    p.heavy = 2 * p.slice;
     return p;
 }
 

@@ -20,6 +20,15 @@ TaskParams default_params(int32_t n, int64_t arcs) {
     TaskParams p;
     p.run_verts = (int)std::min<int64_t>(64, std::max<int64_t>(1, (n + kTarget - 1) / kTarget));
     p.run_arcs = (int)std::min<int64_t>(512, std::max<int64_t>(64, (arcs + kTarget - 1) / kTarget));
+    // A slice is one wave's serial walk and so the tail of a product: short
+    // where the whole product is, up to 512 arcs where the partials of more
+    // slices cost more than the tail.  Distances and path counts of 256 sources
+    // on weighted R-MAT graphs, ms with slices of 512 / 256 / 128 / 64 arcs
+    // (rows cut from twice that on): scale 10 1.43 / 1.43 / 0.96 / 0.69, 12
+    // 1.99 / 1.18 / 0.78 / 0.77, 14 2.72 / 1.73 / 1.67 / 1.58, 16 3.65 / 3.23
+    // / 3.44 / 4.10, 18 10.9 / 11.6 / 12.1 / 14.8.
+    p.slice = (int)std::min<int64_t>(512, std::max<int64_t>(64, arcs / 4096));
+    p.heavy = 2 * p.slice;
     return p;
 }
 

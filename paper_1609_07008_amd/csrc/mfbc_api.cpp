@@ -26,8 +26,14 @@ using namespace mfbc;
 // Scratch of mfbc_bc_noalloc: one file-scope device array per GPU (the code
 // object's copy on each device), holding the workspace of one call.  Calls on
 // one device share it; each call initialises what it reads.
+// Calls are admitted by a fixed formula (ws_arrays) against kScratchBytes; the
+// array is larger, since the default row cut of a small graph takes up to
+// 4.7 MB more hub partials per group than the formula counts (rows cut into
+// slices of max(64, arcs / 4096) arcs, 768 B each), and a core's partials and
+// DAG masks up to 1.4 B per arc more than the masks of every arc.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchSize = (size_t)76 << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchSize];
 
 namespace {
 
@@ -88,15 +94,16 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // order: f(pointer, element count).  Used both to allocate the arrays and to
 // carve them out of one block of memory.
 // (g == nullptr: every count is 0, for walks that need only the pointers.)
-// full_dag: the stored DAG sized for every arc rather than the core's (the
-// size mfbc_bc_noalloc admits calls by, which does not depend on the weights).
+// admit: the sizes mfbc_bc_noalloc admits calls by -- the stored DAG of every
+// arc, the hub partials of the plain row cut -- which depend on neither the
+// weights nor the default decomposition.
 template <typename F>
-void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool full_dag = false) {
+void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool admit = false) {
     const size_t n = g ? (size_t)g->n : 0;
     const size_t tile = n * kWave * (size_t)ncg;
     const size_t nwords = (n + 31) / 32;
     const size_t slots =
-        g ? (size_t)max_slots(g) * kWave * (size_t)ncg : 0;
+        g ? (size_t)(admit ? g->scratch_slots : max_slots(g)) * kWave * (size_t)ncg : 0;
     f(ws.tdist, tile);
     f(ws.tsig, tile);
     for (int b = 0; b < 2; b++) {
@@ -110,7 +117,7 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool full_dag
     f(ws.counters, (size_t)kCounterRing * 4 * kCounterSlots);
     f(ws.flags, (size_t)4);
     f(ws.lam, n * ncg);
-    f(ws.dag, (size_t)std::max<int64_t>(g ? (full_dag ? g->arcs : g->core.arcs) : 0, 1) * ncg);
+    f(ws.dag, (size_t)std::max<int64_t>(g ? (admit ? g->arcs : g->core.arcs) : 0, 1) * ncg);
     f(ws.src, (size_t)ncg * kWave);
     f(ws.tau2, ncg >= 2 ? tile / 2 : (size_t)1);   // the paired counting product's 16-bit tau
 }
@@ -121,13 +128,13 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool full_dag
 int ws_groups(int ncg) { return ncg <= 1 ? 1 : (ncg + 1) & ~1; }
 
 // Bytes of the workspace of `ncg` groups when carved from one block.
-size_t ws_bytes(const mfbc_graph *g, int ncg) {
+size_t ws_bytes(const mfbc_graph *g, int ncg, bool admit) {
     Workspace tmp;
     size_t off = 0;
     ws_arrays(g, tmp, ws_groups(ncg), [&](auto *&p, size_t count) {
         (void)p;
         off = align256(off + std::max<size_t>(count, 1) * sizeof(*p));
-    }, true);
+    }, admit);
     return off;
 }
 
@@ -140,6 +147,7 @@ void free_workspace(Workspace &ws) {
 void free_plan(Plan &p) {
     dfree(p.tasks);
     dfree(p.hubs);
+    dfree(p.owner);
     p.ntasks = p.nhubs = p.nslots = 0;
 }
 
@@ -496,12 +504,19 @@ int upload_csr(int32_t n, int64_t arcs, const int64_t *rp, const int32_t *col, c
 }
 
 // The plans of one view (one for both orientations of an undirected graph).
+// owners: with the in-arcs' rows (Plan::owner).
 int plan_view(int32_t n, bool directed, const std::vector<int64_t> &rp_out, const std::vector<int64_t> &rp_in,
-              const TaskParams &p, View &v) {
+              const TaskParams &p, View &v, bool owners) {
     if (!directed) v.plan_in = Plan{};
     int rc = upload_plan(n, rp_out.data(), p, v.plan_out);
     if (!rc && directed) rc = upload_plan(n, rp_in.data(), p, v.plan_in);
-    if (!rc && !directed) v.plan_in = v.plan_out;
+    Plan &pi = directed ? v.plan_in : v.plan_out;
+    if (!rc && owners && !(rc = dalloc(&pi.owner, (size_t)rp_in.back()))) {
+        launch_plan_owner(v.in, pi, nullptr);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(nullptr));
+    }
+    if (!directed) v.plan_in = v.plan_out;
     return rc;
 }
 
@@ -509,7 +524,7 @@ int plan_view(int32_t n, bool directed, const std::vector<int64_t> &rp_out, cons
 // view's own size.
 int plan_views(mfbc_graph *g, const TaskParams &knobs) {
     auto params = [&](bool core) {
-        TaskParams p = core ? core_params(g->n, g->core.arcs) : default_params(g->n, g->full.arcs);
+        TaskParams p = core ? core_params(g->n, g->core.arcs, g->full.arcs) : default_params(g->n, g->full.arcs);
         if (knobs.run_arcs > 0) p.run_arcs = knobs.run_arcs;
         if (knobs.run_verts > 0) p.run_verts = knobs.run_verts;
         if (knobs.heavy > 0) p.heavy = knobs.heavy;
@@ -517,13 +532,27 @@ int plan_views(mfbc_graph *g, const TaskParams &knobs) {
         return p;
     };
     g->params = params(false);
-    const int rc = plan_view(g->n, g->directed, g->h_rp_out, g->h_rp_in, g->params, g->full);
+    // slots of a decomposition with the plain row cut (or the caller's): what
+    // mfbc_bc_noalloc counts, whatever the default cut is
+    const int64_t heavy = knobs.heavy > 0 ? knobs.heavy : kPlainHeavy;
+    const int64_t slice = knobs.slice > 0 ? knobs.slice : kPlainSlice;
+    g->scratch_slots = 0;
+    for (const auto *rp : {&g->h_rp_out, &g->h_rp_in}) {
+        int64_t t = 0;
+        for (int32_t v = 0; v < g->n; v++) {
+            const int64_t d = (*rp)[(size_t)v + 1] - (*rp)[(size_t)v];
+            if (d > heavy) t += (d + slice - 1) / slice;
+        }
+        g->scratch_slots = std::max(g->scratch_slots, t);
+        if (!g->directed) break;
+    }
+    const int rc = plan_view(g->n, g->directed, g->h_rp_out, g->h_rp_in, g->params, g->full, true);
     if (!g->has_core) {
         g->core = g->full;       // also after a failure: no stale pointers
         return rc;
     }
     if (rc) return rc;
-    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, params(true), g->core);
+    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, params(true), g->core, false);
 }
 
 // One block of device memory, handed out in parts and freed at the end of
@@ -550,12 +579,13 @@ struct Scratch {
 };
 
 // Upper bounds of the distances from the landmarks (ws.src) to every vertex
-// along the arcs of t.full.in, in t.ws.tdist: the walks of at most kWindow
-// arcs.  Longer ones drop few arcs more (uniform graph of degree 256: 6.91%
-// kept against 6.90%; R-MAT scale 16: the same 8.71%).
+// along the arcs of t.full.in, in t.ws.tdist: the walks of at most six
+// arcs.  Longer ones drop few arcs more (arcs kept by walks of up to 6 / any:
+// uniform graphs of degree 256 7.1% / 6.9%, of degree 40 33% / 31%; R-MAT
+// scale 16 8.7% / 8.7%).
 void landmark_bounds(mfbc_graph &t, int count, hipStream_t s) {
     launch_mono_init(&t, MFBC_OP_SSSP, 1, count, s);
-    for (int j = 1; j <= kWindow; j++) launch_mono_product(&t, MFBC_OP_SSSP, 1, j, s, nullptr);
+    for (int j = 1; j <= 6; j++) launch_mono_product(&t, MFBC_OP_SSSP, 1, j, s, nullptr);
 }
 
 // The core of one orientation: rows of bounds `near` for the row vertices,
@@ -656,7 +686,7 @@ int build_core(mfbc_graph *g, hipStream_t s) {
     c.arcs = g->h_core_rp_out.back();
     g->core = c;
     g->has_core = true;
-    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs), g->core);
+    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs, g->full.arcs), g->core, false);
 }
 
 // Release a lane view: its workspace, counters and events (the device graph
@@ -1015,7 +1045,10 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
     if ((rc = ensure_workspace(g, ncg))) return rc;
     g->stats = mfbc_stats{};
     launch_set_sources(g, ncg, nb, d_sources, s);
-    launch_mono_init(g, op, ncg, nb, s);
+    const bool bits = bits_fit(g, op);
+    if (bits) launch_bits_init(g, ncg, nb, s);
+    else launch_mono_init(g, op, ncg, nb, s);
+    int planes = 0;              // planes of the product number cleared so far
     const double arc_bytes = g->weighted && op != MFBC_OP_BFS ? 8.0 : 4.0;
     mfbc_stats &st = g->stats;
     int64_t prev = nb;
@@ -1023,7 +1056,15 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
     // windows of products with one counter read-back each, as in MFBF
     while (!last) {
         if (j > g->n + 1) return fail(MFBC_EDEVICE, "fixpoint products did not converge");
-        for (int i = 0; i < kWindow; i++) launch_mono_product(g, op, ncg, j + 1 + i, s, window_events(g, i, true));
+        if (bits) {
+            const int need = bits_for(j + kWindow);
+            launch_bits_planes(g, ncg, planes, need, s);
+            planes = need;
+        }
+        for (int i = 0; i < kWindow; i++) {
+            if (bits) launch_bits_product(g, ncg, j + 1 + i, s, window_events(g, i, true));
+            else launch_mono_product(g, op, ncg, j + 1 + i, s, window_events(g, i, true));
+        }
         if ((rc = read_ring(g, s))) return rc;
         for (int i = 0; i < kWindow; i++) {
             const int jj = j + 1 + i;
@@ -1049,7 +1090,8 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
     st.batches = 1;
     if (h_products) *h_products = j;
     // 4-byte values whatever their type: the tile export copies them as int32
-    launch_export_tiles_i32(g, ncg, nb, g->ws.tdist, (int32_t *)d_out, s);
+    if (bits) launch_bits_export(g, op, ncg, nb, bits_for(last), d_out, s);
+    else launch_export_tiles_i32(g, ncg, nb, g->ws.tdist, (int32_t *)d_out, s);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(s));
     return MFBC_OK;
@@ -1166,12 +1208,20 @@ int mfbc_bc_noalloc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, 
     if (n_sources > 0 && !d_sources) return fail(MFBC_EINVAL, "sources pointer is NULL");
     DeviceGuard dg(g->device);
     hipStream_t s = (hipStream_t)hip_stream;
-    const int ncg = bc_groups(n_sources, batch);
-    const size_t need = ws_bytes(g, ncg);
+    int ncg = bc_groups(n_sources, batch);
+    const size_t need = ws_bytes(g, ncg, true);
     if (need > kScratchBytes)
         return fail(MFBC_ENOMEM, "mfbc_bc_noalloc: this graph and batch need " + std::to_string(need) +
                                      " bytes of workspace; the static scratch holds " +
                                      std::to_string(kScratchBytes));
+    // where the finer row cut's partials do not fit beside the batch, it runs in
+    // parts (lambda is a sum over sources)
+    while (ncg > 1 && ws_bytes(g, ncg, false) > kScratchSize) {
+        ncg /= 2;
+        batch = ncg * kWave;
+    }
+    if (ws_bytes(g, ncg, false) > kScratchSize)
+        return fail(MFBC_ENOMEM, "mfbc_bc_noalloc: the hub partials of this graph's plan do not fit the scratch");
     char *base = nullptr;
     int rc = scratch_base(g->device, &base);
     if (rc) return rc;

@@ -50,17 +50,20 @@ struct Hub {
 
 // Tunables of the work decomposition (chosen by the autotuner; defaults
 // are used when none is set).
+constexpr int kPlainHeavy = 1024, kPlainSlice = 512;
+
 struct TaskParams {
     int run_arcs = 512;   // arcs per light run
     int run_verts = 64;   // vertices per light run (<= 64)
-    int heavy = 1024;     // degree above which a row is split
-    int slice = 512;      // arcs per slice of a split row
+    int heavy = kPlainHeavy;   // degree above which a row is split
+    int slice = kPlainSlice;   // arcs per slice of a split row
 };
 
 // Work decomposition of one CSR orientation.
 struct Plan {
     Task *tasks = nullptr;   // device
     Hub *hubs = nullptr;     // device
+    uint8_t *owner = nullptr;  // device: row of each arc within its task (in-arcs of the full view)
     int32_t ntasks = 0, nhubs = 0, nslots = 0;
 };
 
@@ -118,6 +121,7 @@ struct mfbc_graph {
     // distances and path counts; the same arrays as `full` unless has_core.
     mfbc::View full, core;
     bool has_core = false;
+    int64_t scratch_slots = 0;  // hub partial slots mfbc_bc_noalloc admits calls by
     int mb = 1;             // inline multiplicity bits of a packed frontier tuple
     mfbc::TaskParams params;
     mfbc::Workspace ws;
@@ -209,10 +213,18 @@ int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const in
                    unsigned long long *h_stats, int32_t *h_flags, std::string &err);
 ManyWorkspace &many_workspace(int device);
 
+// ---- fixpoints on bit masks (bits.hip) ----
+bool bits_fit(const mfbc_graph *g, int op);
+void launch_plan_owner(const Csr &c, const Plan &pl, hipStream_t s);
+void launch_bits_init(mfbc_graph *g, int ncg, int nb, hipStream_t s);
+void launch_bits_planes(mfbc_graph *g, int ncg, int from, int to, hipStream_t s);
+void launch_bits_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev);
+void launch_bits_export(mfbc_graph *g, int op, int ncg, int nb, int planes, void *out, hipStream_t s);
+
 // ---- shortest-path core (core.hip) ----
 constexpr int kLandmarks = kWave;        // one per lane
 bool core_worth_trying(const mfbc_graph *g);
-TaskParams core_params(int32_t n, int64_t arcs);   // default decomposition of a core
+TaskParams core_params(int32_t n, int64_t arcs, int64_t full_arcs);   // default decomposition of a core
 // Flags of the arcs of one orientation that pass the landmark test (byte per
 // arc) and their number per row.  `near`[v][64], `far`[v][64]: see core.hip.
 void launch_core_mark(const Csr &c, const Plan &pl, const int32_t *near, const int32_t *far, uint8_t *keep,
