@@ -23,8 +23,9 @@
  *   - Status: every int-returning call returns MFBC_OK (0) or a negative
  *     MFBC_E* code; mfbc_last_error() then describes the failure (a
  *     thread-local string, valid until the next call on that thread).
- *     Arguments are validated before any device work; on an error no output
- *     has been written.
+ *     Arguments are validated before any device work, except that source lists
+ *     (device memory) are checked by the kernels that read them; on an error
+ *     no output has been written.
  *   - Device pointers ("d_") are caller-owned device memory of the current
  *     HIP device (for example torch tensors); host pointers ("h_") are plain
  *     host memory.  The library owns only the graph and its workspace.
@@ -147,11 +148,13 @@ int mfbc_backward(mfbc_graph *g, const int32_t *d_sources, int32_t nb,
  *                  rounding.
  *   d_bc[n]        device out, overwritten.
  *   The batches are independent (Algorithm 3 sums their contributions), so
- *   up to four of them run at once on separate streams ("lanes", see
- *   mfbc_set_lanes), each lane with its own workspace; lane 0 uses
- *   hip_stream, the others library-owned streams ordered after the work
- *   already on hip_stream.  Lambda is summed in a fixed lane and batch order,
- *   so repeated calls with the same lane count are bitwise identical.
+ *   where their products are small several run as one wide batch, one launch
+ *   and one read-back for all of them; with a lane count set (mfbc_set_lanes)
+ *   that many run at once on separate streams instead, each lane with its own
+ *   workspace; lane 0 uses hip_stream, the others library-owned streams
+ *   ordered after the work already on hip_stream.  Lambda is summed in a
+ *   fixed order, so repeated calls with the same lane count are bitwise
+ *   identical.
  * Errors: EINVAL (n_sources < 0, batch < 1, bad source), EOVERFLOW,
  * ENOMEM, EDEVICE.
  */
@@ -161,8 +164,10 @@ int mfbc_bc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources,
 /*
  * mfbc_set_lanes -- how many batches of one mfbc_bc call run at once (a
  * tuning knob; results differ only in floating-point summation order).
- *   lanes  1..4, or 0 (the default): four where a product of one batch is
- *          too small to fill the device (arcs * column groups <= 2^24), else one.
+ *   lanes  1..4, or 0 (the default), by the arcs * column groups of a batch:
+ *          up to 2^21 four batches, or as many as keep the state within 256
+ *          MB, run as one wide batch; up to 2^24 four run at once; else one at
+ *          a time.
  * Each lane holds its own workspace (see the workspace note above).
  * Errors: EINVAL (lanes outside [0, 4]).
  */

@@ -81,7 +81,7 @@ def _time(fn, reps: int) -> float:
     return best
 
 
-LANE_CANDIDATES = (1, 2, 4)
+LANE_CANDIDATES = (0, 1, 2, 4)       # 0: several batches as one wide one
 # lanes are tuned only where one product of a batch is small next to the
 # device (arcs x column groups below this): on large products concurrent
 # batches only share the memory bandwidth, and each kernel's own duration --
@@ -116,10 +116,10 @@ def tune_plan(dg, g, sources, batch: int, reps: int = 2, cache: dict = None, ver
             if verbose:
                 print(f"[tune] {g.name} lanes={L}: {lres[L] * 1e3:.2f} ms", file=sys.stderr, flush=True)
         lanes = min(lres, key=lres.get)
-    dg.set_lanes(lanes if lanes else 1)
+    dg.set_lanes(lanes)
     if cache is not None:
         cache.setdefault("plan", {})[graph_bucket(g)] = {"run_arcs": best[0], "run_verts": best[1],
-                                                         "lanes": lanes if lanes else 1,
+                                                         "lanes": lanes,
                                                          "ms": res[best] * 1e3}
     return best, res
 

@@ -44,6 +44,9 @@ struct BitArgs {
     const unsigned long long *prev_ctr;
     uint32_t *clear_bits;
     unsigned long long *clear_ctr;
+    uint32_t *next_bits;         // no split rows: F_{j+1}'s bitmaps and counters (close_product)
+    unsigned long long *next_ctr;
+    const int64_t *rp;
 };
 
 template <int W>
@@ -124,10 +127,13 @@ __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int W>
+template <int W, bool C>
 __global__ __launch_bounds__(kBlock) void k_bits_pull(BitArgs a) {
     __shared__ unsigned long long s_acc[kWavesPerBlock][kWave * W];
-    if (!live_prev(a.prev_ctr)) return;
+    if (!live_prev(a.prev_ctr)) {
+        if constexpr (C) close_skipped(a.next_ctr);
+        return;
+    }
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = uni((int)(threadIdx.x >> 6));
     const int wid = blockIdx.x * kWavesPerBlock + wv;
@@ -178,20 +184,22 @@ __global__ __launch_bounds__(kBlock) void k_bits_pull(BitArgs a) {
             if (lane == 0 && run) or_run_bits(a.bits_n + (size_t)q * a.nwords, v0, run);
         }
     }
-    flush_counts(wave_add(produced), wave_add(outs), 0, 0, a.ctr);
+    unsigned long long nv = 0, na = 0;
+    if constexpr (C) close_product(a.bits, a.next_bits, a.nwords, a.nq, a.rp, a.next_ctr, nv, na);
+    flush_counts(wave_add(produced), wave_add(outs), nv, na, a.ctr);
 }
 
 // The split rows, one thread each; also clears F_{j-1}'s bitmaps (counting its
 // vertices and their arcs) and the counters of product j+1.
 template <int W>
-__global__ __launch_bounds__(kBlock) void k_bits_merge(BitArgs a, const int64_t *rp) {
+__global__ __launch_bounds__(kBlock) void k_bits_merge(BitArgs a) {
     const int gtid = blockIdx.x * kBlock + threadIdx.x;
     if (!live_prev(a.prev_ctr)) {
         if (gtid < 4 * kCounterSlots) a.clear_ctr[gtid] = 0ull;
         return;
     }
     unsigned long long nv = 0, na = 0;
-    clear_and_count(a.clear_bits, a.nwords, a.nq, rp, nv, na);
+    clear_and_count(a.clear_bits, a.nwords, a.nq, a.rp, nv, na);
     if (gtid < 4 * kCounterSlots) a.clear_ctr[gtid] = 0ull;
     unsigned produced = 0, outs = 0;
     for (int i = gtid; i < a.nq * a.nhubs; i += gridDim.x * kBlock) {
@@ -214,7 +222,7 @@ __global__ void k_bits_zero(unsigned long long *p, size_t count) {
 }
 
 // Nothing reached, no frontier, counters and hub words at zero.
-__global__ void k_bits_init(unsigned long long *seen, size_t nseen, uint32_t *ab0, uint32_t *ab1, size_t nab,
+__global__ void k_bits_init(unsigned long long *seen, size_t nseen, uint32_t *ab0, uint32_t *ab1, uint32_t *ab2, size_t nab,
                             unsigned long long *hub, size_t nhub, unsigned long long *ctr, int nctr) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -222,33 +230,32 @@ __global__ void k_bits_init(unsigned long long *seen, size_t nseen, uint32_t *ab
     for (size_t i = t0; i < nab; i += stride) {
         ab0[i] = 0u;
         ab1[i] = 0u;
+        ab2[i] = 0u;
     }
     for (size_t i = t0; i < nhub; i += stride) hub[i] = 0ull;
     for (size_t i = t0; i < (size_t)nctr; i += stride) ctr[i] = 0ull;
 }
 
-// The sources' rows of the first frontier start empty ...
+// Seeds (launch_seed): the sources' rows of the first frontier start empty,
+// then each column reaches its source.
 template <int W>
-__global__ void k_bits_seed_rows(const int32_t *src, int nb, int n, unsigned long long *f) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb) return;
-    const size_t at = ((size_t)(c / (W * kWave)) * n + src[c]) * W;
-    for (int k = 0; k < W; k++) f[at + k] = 0ull;
-}
-
-// ... then each column reaches its source.
-template <int W>
-__global__ void k_bits_seed(const int32_t *src, int nb, int n, int nwords, unsigned long long *f,
-                            unsigned long long *seen, uint32_t *abits) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb) return;
-    const int v = src[c], q = c / (W * kWave), k = (c / kWave) % W;
-    const size_t at = ((size_t)q * n + v) * W + k;
-    const unsigned long long m = 1ull << (c % kWave);
-    atomicOr(f + at, m);
-    atomicOr(seen + at, m);
-    atomicOr(abits + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
-}
+struct BitSeed {
+    static constexpr int kGroups = W;
+    int n, nwords;
+    unsigned long long *f, *seen;
+    uint32_t *abits;
+    __device__ void row(int v, int q, int lane) const {
+        if (lane < W) f[((size_t)q * n + v) * W + lane] = 0ull;
+    }
+    __device__ void entry(int v, int c) const {
+        const int q = c / (W * kWave), k = (c / kWave) % W;
+        const size_t at = ((size_t)q * n + v) * W + k;
+        const unsigned long long m = 1ull << (c % kWave);
+        atomicOr(f + at, m);
+        atomicOr(seen + at, m);
+        atomicOr(abits + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
+    }
+};
 
 // Values of 64 caller vertices (one per lane) for the wave's 16 columns of
 // group cg: the bits of the product number from `planes` words per vertex.
@@ -324,8 +331,8 @@ BitArgs bit_args(mfbc_graph *g, int ncg, int j) {
     a.owner = vw.plan_in.owner;
     a.arc = vw.in.pk ? vw.in.pk : (const uint32_t *)vw.in.col;
     a.cmask = vw.in.pk && vw.in.cb < 32 ? (1u << vw.in.cb) - 1u : 0xffffffffu;
-    a.bits = ws.abits[b];
-    a.bits_n = ws.abits[b ^ 1];
+    a.bits = ws.abits[(j - 1) % 3];
+    a.bits_n = ws.abits[j % 3];
     a.f = (const unsigned long long *)ws.fbits[b];
     a.f_n = (unsigned long long *)ws.fbits[b ^ 1];
     a.seen = (unsigned long long *)ws.lam;       // 8 B per vertex and group, as the masks
@@ -334,33 +341,36 @@ BitArgs bit_args(mfbc_graph *g, int ncg, int j) {
     a.hub = (unsigned long long *)ws.pd;
     a.ctr = ws.counters + (size_t)(j % kCounterRing) * 4 * kCounterSlots;
     a.prev_ctr = j > 1 ? ws.counters + (size_t)((j - 1) % kCounterRing) * 4 * kCounterSlots : nullptr;
-    a.clear_bits = ws.abits[b];
+    a.clear_bits = ws.abits[(j - 1) % 3];
     a.clear_ctr = ws.counters + (size_t)((j + 1) % kCounterRing) * 4 * kCounterSlots;
+    if (a.nhubs == 0) {
+        a.next_bits = ws.abits[(j + 1) % 3];
+        a.next_ctr = a.clear_ctr;
+    }
+    a.rp = vw.in.rp;
     return a;
 }
 
 template <int W>
-void bits_init(const BitArgs &a, mfbc_graph *g, int nb, hipStream_t s) {
+void bits_init(const BitArgs &a, mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
     Workspace &ws = g->ws;
-    unsigned long long *f = (unsigned long long *)ws.fbits[0];
     hipLaunchKernelGGL(k_bits_init, dim3(grid_for(a.plane, 256, 8192)), dim3(256), 0, s, a.seen, a.plane,
-                       ws.abits[0], ws.abits[1], (size_t)a.nq * a.nwords, a.hub, (size_t)a.nq * a.nhubs * W,
-                       ws.counters, kCounterRing * 4 * kCounterSlots);
-    hipLaunchKernelGGL(k_bits_seed_rows<W>, dim3(grid_for(nb, 256, 1 << 20)), dim3(256), 0, s, ws.src, nb, g->n,
-                       f);
-    hipLaunchKernelGGL(k_bits_seed<W>, dim3(grid_for(nb, 256, 1 << 20)), dim3(256), 0, s, ws.src, nb, g->n,
-                       a.nwords, f, a.seen, ws.abits[0]);
+                       ws.abits[0], ws.abits[1], ws.abits[2], (size_t)a.nq * a.nwords, a.hub,
+                       (size_t)a.nq * a.nhubs * W, ws.counters, (int)kRingWords);
+    const BitSeed<W> seed{g->n, a.nwords, (unsigned long long *)ws.fbits[0], a.seen, ws.abits[0]};
+    launch_seed(g, seed, ncg, nb, d_sources, s);
 }
 
 template <int W>
-void bits_product(const BitArgs &a, mfbc_graph *g, hipStream_t s, hipEvent_t *ev) {
+void bits_product(const BitArgs &a, hipStream_t s, hipEvent_t *ev) {
     if (ev) (void)hipEventRecord(ev[0], s);
-    hipLaunchKernelGGL(k_bits_pull<W>, dim3(grid_for((size_t)a.ntasks * a.nq, kWavesPerBlock, 0x7fffffff)),
-                       dim3(kBlock), 0, s, a);
+    const int grid = grid_for((size_t)a.ntasks * a.nq, kWavesPerBlock, 0x7fffffff);
+    if (a.next_bits) hipLaunchKernelGGL((k_bits_pull<W, true>), dim3(grid), dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_bits_pull<W, false>), dim3(grid), dim3(kBlock), 0, s, a);
     if (ev) (void)hipEventRecord(ev[1], s);
     const size_t work = std::max((size_t)a.nhubs * a.nq, (size_t)a.nwords);
-    hipLaunchKernelGGL(k_bits_merge<W>, dim3(grid_for(work, kBlock, 1024)), dim3(kBlock), 0, s, a,
-                       (const int64_t *)g->full.in.rp);
+    if (a.nhubs)
+        hipLaunchKernelGGL(k_bits_merge<W>, dim3(grid_for(work, kBlock, 1024)), dim3(kBlock), 0, s, a);
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
 
@@ -411,12 +421,12 @@ bool bits_fit(const mfbc_graph *g, int op) {
     return g->maxw == 1 && (op != MFBC_OP_RESIST || g->n < (1 << 24));
 }
 
-void launch_bits_init(mfbc_graph *g, int ncg, int nb, hipStream_t s) {
+void launch_bits_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
     const BitArgs a = bit_args(g, ncg, 1);
     switch (bits_width(ncg)) {
-        case 1: bits_init<1>(a, g, nb, s); break;
-        case 2: bits_init<2>(a, g, nb, s); break;
-        default: bits_init<4>(a, g, nb, s); break;
+        case 1: bits_init<1>(a, g, ncg, nb, d_sources, s); break;
+        case 2: bits_init<2>(a, g, ncg, nb, d_sources, s); break;
+        default: bits_init<4>(a, g, ncg, nb, d_sources, s); break;
     }
 }
 
@@ -432,9 +442,9 @@ void launch_bits_planes(mfbc_graph *g, int ncg, int from, int to, hipStream_t s)
 void launch_bits_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
     const BitArgs a = bit_args(g, ncg, j);
     switch (bits_width(ncg)) {
-        case 1: bits_product<1>(a, g, s, ev); break;
-        case 2: bits_product<2>(a, g, s, ev); break;
-        default: bits_product<4>(a, g, s, ev); break;
+        case 1: bits_product<1>(a, s, ev); break;
+        case 2: bits_product<2>(a, s, ev); break;
+        default: bits_product<4>(a, s, ev); break;
     }
 }
 

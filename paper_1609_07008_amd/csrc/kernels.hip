@@ -36,6 +36,8 @@
 // or more column groups run the forward product (and on weighted graphs the
 // backward products) on pairs of groups: one 8-byte (16-byte) gather per
 // lane and one bitmap test per arc serve both groups (products.h).
+#include <algorithm>
+
 #include "products.h"
 
 namespace mfbc {
@@ -44,12 +46,6 @@ namespace {
 // In every kernel here `perm` (nullable) maps a caller vertex id to the
 // device numbering; the products themselves only see device ids.
 __device__ __forceinline__ int dev_id(const int32_t *perm, int v) { return perm ? perm[v] : v; }
-
-__global__ void k_set_sources(int32_t *src, int total, int nb, const int32_t *in,
-                              const int32_t *perm) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < total) src[i] = i < nb ? dev_id(perm, in[i]) : -1;
-}
 
 // Sources of a batch laid out by request (mfbc_bc_requests): group slot cg
 // holds sp.count[cg] consecutive sources from in[sp.first[cg]] on and
@@ -76,8 +72,8 @@ __global__ void k_zero_u32(uint32_t *p, size_t count) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) p[i] = 0u;
 }
 
-// T = (INF, 0) everywhere, both frontier bitmaps cleared, counters zeroed.
-__global__ void k_fwd_fill(int32_t *tdist, double *tsig, size_t total, uint32_t *ab0, uint32_t *ab1,
+// T = (INF, 0) everywhere, the frontier bitmaps cleared, counters zeroed.
+__global__ void k_fwd_fill(int32_t *tdist, size_t total, uint32_t *ab0, uint32_t *ab1, uint32_t *ab2,
                            size_t nab, unsigned long long *ctr, int nctr, int32_t *flags) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -85,62 +81,52 @@ __global__ void k_fwd_fill(int32_t *tdist, double *tsig, size_t total, uint32_t 
     // leaves and finishes in the backward, exports masked by tau), so only
     // tau is reset
     for (size_t i = t0; i < total; i += stride) tdist[i] = kInf;
-    (void)tsig;
     for (size_t i = t0; i < nab; i += stride) {
         ab0[i] = 0u;
         ab1[i] = 0u;
+        ab2[i] = 0u;
     }
     for (size_t i = t0; i < (size_t)nctr; i += stride) ctr[i] = 0ull;
     if (t0 == 0) flags[0] = 0;
 }
 
-// Rows of the sources in the first frontier start with every lane absent.
-__global__ void k_fwd_seed_rows(const int32_t *src, int nb, int n, uint32_t *ftup) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb || src[c] < 0) return;          // padding column
-    const size_t row = ((size_t)(c / kWave) * n + src[c]) * kWave;
-    for (int l = 0; l < kWave; l++) ftup[row + l] = kSent;
-}
-
-// The sources themselves: T(s, s) = (0, 1) and the first frontier {s}
-// carrying (0, 1).
-__global__ void k_fwd_seed(const int32_t *src, int nb, int n, int nwords, int32_t *tdist,
-                           double *tsig, uint32_t *ftup, uint32_t *abits) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb) return;
-    const int v = src[c];
-    if (v < 0) return;                           // padding column
-    const int cg = c / kWave, lane = c % kWave;
-    const size_t idx = ((size_t)cg * n + v) * kWave + lane;
-    tdist[idx] = 0;
-    tsig[idx] = 1.0;
-    ftup[idx] = 1u;                      // weight 0, multiplicity 1 inline
-    atomicOr(abits + (size_t)cg * nwords + (v >> 5), 1u << (v & 31));
-}
-
-// The same for the wide layout (groups Wq .. Wq+W-1 interleaved per lane,
-// one activity bitmap per wide group).
+// MFBF's seeds (launch_seed): the rows of the sources in the first frontier
+// start with every lane absent, then T(s, s) = (0, 1) and the frontier {s}
+// carries it.  W groups per row (the wide layout) and per activity bitmap.
 template <int W>
-__global__ void k_fwd_seed_rows_w(const int32_t *src, int nb, int n, uint32_t *ftup) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb || src[c] < 0) return;          // padding column
-    const size_t row = ((size_t)(c / (W * kWave)) * n + src[c]) * kWave * W;
-    for (int l = 0; l < kWave * W; l++) ftup[row + l] = kSent;
-}
+struct FwdSeed {
+    static constexpr int kGroups = W;
+    int n, nwords;
+    int32_t *tdist;
+    double *tsig;
+    uint32_t *ftup, *abits;
+    __device__ void row(int v, int q, int lane) const {
+        uint32_t *p = ftup + ((size_t)q * n + v) * kWave * W;
+#pragma unroll
+        for (int c = 0; c < W; c++) p[c * kWave + lane] = kSent;
+    }
+    __device__ void entry(int v, int c) const {
+        const int cg = c / kWave, lane = c % kWave, q = cg / W;
+        const size_t idx = ((size_t)cg * n + v) * kWave + lane;
+        tdist[idx] = 0;
+        tsig[idx] = 1.0;
+        ftup[(((size_t)q * n + v) * kWave + lane) * W + (cg % W)] = 1u;   // weight 0, multiplicity 1 inline
+        atomicOr(abits + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
+    }
+};
 
-template <int W>
-__global__ void k_fwd_seed_w(const int32_t *src, int nb, int n, int nwords, int32_t *tdist,
-                             double *tsig, uint32_t *ftup, uint32_t *abits) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb) return;
-    const int v = src[c];
-    if (v < 0) return;                           // padding column
-    const int cg = c / kWave, lane = c % kWave, q = cg / W;
-    const size_t idx = ((size_t)cg * n + v) * kWave + lane;
-    tdist[idx] = 0;
-    tsig[idx] = 1.0;
-    ftup[(((size_t)q * n + v) * kWave + lane) * W + (cg % W)] = 1u;
-    atomicOr(abits + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
+// Bitmaps, counters and one flag cleared before the backward products.
+__global__ void k_bwd_clear(uint32_t *ab0, uint32_t *ab1, uint32_t *ab2, size_t nab, unsigned long long *ctr,
+                            int nctr, int32_t *flag) {
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = t0; i < nab; i += stride) {
+        ab0[i] = 0u;
+        ab1[i] = 0u;
+        ab2[i] = 0u;
+    }
+    for (size_t i = t0; i < (size_t)nctr; i += stride) ctr[i] = 0ull;
+    if (t0 == 0) *flag = 0;
 }
 
 __global__ void k_zero_f64(double *p, size_t total) {
@@ -370,12 +356,12 @@ static FwdArgs fwd_args(mfbc_graph *g, const View &vw, int ncg, int j) {
     a.mb = g->mb;
     a.rp = vw.in.rp;
     a.arcs = arc_src(vw.in);
-    a.abits = ws.abits[b];
+    a.abits = ws.abits[(j - 1) % 3];
     a.ftup = (const uint32_t *)ws.fdist[b];
     a.fsig = ws.fsig[b];
     a.tdist = ws.tdist;
     a.tsig = ws.tsig;
-    a.abits_n = ws.abits[b ^ 1];
+    a.abits_n = ws.abits[j % 3];
     a.ftup_n = (uint32_t *)ws.fdist[b ^ 1];
     a.fsig_n = ws.fsig[b ^ 1];
     a.pd = ws.pd;
@@ -383,8 +369,12 @@ static FwdArgs fwd_args(mfbc_graph *g, const View &vw, int ncg, int j) {
     a.ctr = ws.counters + (size_t)(j % kCounterRing) * 4 * kCounterSlots;
     a.prev_ctr = j > 1 ? ws.counters + (size_t)((j - 1) % kCounterRing) * 4 * kCounterSlots : nullptr;
     a.flags = ws.flags;
-    a.clear_bits = ws.abits[b];
+    a.clear_bits = ws.abits[(j - 1) % 3];
     a.clear_ctr = ws.counters + (size_t)((j + 1) % kCounterRing) * 4 * kCounterSlots;
+    if (a.nhubs == 0) {
+        a.next_bits = ws.abits[(j + 1) % 3];
+        a.next_ctr = a.clear_ctr;
+    }
     a.nwide = fwd_wide_groups(ncg);
     a.nwide_all = a.nwide;
     return a;
@@ -399,64 +389,57 @@ void launch_check_sources(const int32_t *d_sources, int64_t count, int n, int32_
 }
 
 void launch_set_sources(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
-    const int total = ncg * kWave;
-    hipLaunchKernelGGL(k_set_sources, dim3(blocks_for(total, 256)), dim3(256), 0, s, g->ws.src,
-                       total, nb, d_sources, (const int32_t *)g->perm);
+    hipLaunchKernelGGL(k_seed_block<NoSeed>, dim3(1), dim3(1024), 0, s, NoSeed{}, g->ws.src, ncg * kWave, nb,
+                       d_sources, (const int32_t *)g->perm, g->n, g->ws.flags + 2);
 }
 
-void launch_fwd_init(mfbc_graph *g, int ncg, int nb, hipStream_t s) {
+template <int W>
+static void fwd_seed(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
+    Workspace &ws = g->ws;
+    const FwdSeed<W> seed{g->n, (g->n + 31) / 32, ws.tdist, ws.tsig, (uint32_t *)ws.fdist[0], ws.abits[0]};
+    launch_seed(g, seed, ncg, nb, d_sources, s);
+}
+
+void launch_fwd_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
     Workspace &ws = g->ws;
     const size_t total = (size_t)ncg * g->n * kWave;
     const int nwords = (g->n + 31) / 32;
-    hipLaunchKernelGGL(k_fwd_fill, dim3(blocks_for(total, 256, 65536)), dim3(256), 0, s, ws.tdist,
-                       ws.tsig, total, ws.abits[0], ws.abits[1], (size_t)ncg * nwords,
-                       ws.counters, kCounterRing * 4 * kCounterSlots, ws.flags);
-    if (fwd_wide_groups(ncg)) {
-        uint32_t *ft = (uint32_t *)ws.fdist[0];
-        hipLaunchKernelGGL(k_fwd_seed_rows_w<kWide>, dim3(blocks_for(nb, 256)), dim3(256), 0, s, ws.src,
-                           nb, g->n, ft);
-        hipLaunchKernelGGL(k_fwd_seed_w<kWide>, dim3(blocks_for(nb, 256)), dim3(256), 0, s, ws.src, nb,
-                           g->n, nwords, ws.tdist, ws.tsig, ft, ws.abits[0]);
-        return;
-    }
-    hipLaunchKernelGGL(k_fwd_seed_rows, dim3(blocks_for(nb, 256)), dim3(256), 0, s, ws.src, nb,
-                       g->n, (uint32_t *)ws.fdist[0]);
-    hipLaunchKernelGGL(k_fwd_seed, dim3(blocks_for(nb, 256)), dim3(256), 0, s, ws.src, nb, g->n,
-                       nwords, ws.tdist, ws.tsig, (uint32_t *)ws.fdist[0], ws.abits[0]);
+    hipLaunchKernelGGL(k_fwd_fill, dim3(blocks_for(total, 256, 65536)), dim3(256), 0, s, ws.tdist, total,
+                       ws.abits[0], ws.abits[1], ws.abits[2], (size_t)ncg * nwords, ws.counters,
+                       (int)kRingWords, ws.flags);
+    if (fwd_wide_groups(ncg)) fwd_seed<kWide>(g, ncg, nb, d_sources, s);
+    else fwd_seed<1>(g, ncg, nb, d_sources, s);
+}
+
+template <int AM>
+static void launch_fwd_pull(const FwdArgs &a, int grid, hipStream_t s) {
+    if (a.nwide && a.next_bits)
+        hipLaunchKernelGGL((k_fwd_pull_w<AM, kWide, false, true>), dim3(grid), dim3(kBlock), 0, s, a);
+    else if (a.nwide)
+        hipLaunchKernelGGL((k_fwd_pull_w<AM, kWide, false, false>), dim3(grid), dim3(kBlock), 0, s, a);
+    else if (a.next_bits)
+        hipLaunchKernelGGL((k_fwd_pull<AM, false, true>), dim3(grid), dim3(kBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_fwd_pull<AM, false, false>), dim3(grid), dim3(kBlock), 0, s, a);
 }
 
 void launch_fwd_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
-    FwdArgs a = fwd_args(g, vw, ncg, j);
-    if (a.nwide) {
-        if (ev) (void)hipEventRecord(ev[0], s);
-        const int grid = blocks_for((size_t)a.ntasks * a.nwide, kWavesPerBlock, 0x7fffffff);
-        switch (arc_mode(vw.in)) {
-            case 0: hipLaunchKernelGGL((k_fwd_pull_w<0, kWide, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-            case 1: hipLaunchKernelGGL((k_fwd_pull_w<1, kWide, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-            default: hipLaunchKernelGGL((k_fwd_pull_w<2, kWide, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        }
-        if (ev) (void)hipEventRecord(ev[1], s);
-        int mgrid = blocks_for((size_t)a.nhubs * a.nwide, kWavesPerBlock, 0x7fffffff);
-        const int cgrid = blocks_for((size_t)a.nwords, kBlock, 1024);
-        if (cgrid > mgrid) mgrid = cgrid;
-        hipLaunchKernelGGL((k_fwd_merge_w<kWide, false>), dim3(mgrid), dim3(kBlock), 0, s, a);
-        if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
-        return;
-    }
+    const FwdArgs a = fwd_args(g, vw, ncg, j);
+    const int groups = a.nwide ? a.nwide : ncg;
     if (ev) (void)hipEventRecord(ev[0], s);
-    const size_t waves = (size_t)a.ntasks * ncg;
-    const int grid = blocks_for(waves, kWavesPerBlock, 0x7fffffff);
+    const int grid = blocks_for((size_t)a.ntasks * groups, kWavesPerBlock, 0x7fffffff);
     switch (arc_mode(vw.in)) {
-        case 0: hipLaunchKernelGGL((k_fwd_pull<0, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        case 1: hipLaunchKernelGGL((k_fwd_pull<1, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_fwd_pull<2, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 0: launch_fwd_pull<0>(a, grid, s); break;
+        case 1: launch_fwd_pull<1>(a, grid, s); break;
+        default: launch_fwd_pull<2>(a, grid, s); break;
     }
     if (ev) (void)hipEventRecord(ev[1], s);
-    const size_t mw = (size_t)a.nhubs * ncg;
-    int mgrid = blocks_for(mw, kWavesPerBlock, 0x7fffffff);
-    const int cgrid = blocks_for((size_t)a.nwords, kBlock, 1024);
-    if (cgrid > mgrid) mgrid = cgrid;
-    hipLaunchKernelGGL(k_fwd_merge<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
+    if (a.nhubs) {
+        const int mgrid = std::max(blocks_for((size_t)a.nhubs * groups, kWavesPerBlock, 0x7fffffff),
+                                   blocks_for((size_t)a.nwords, kBlock, 1024));
+        if (a.nwide) hipLaunchKernelGGL((k_fwd_merge_w<kWide, false>), dim3(mgrid), dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL(k_fwd_merge<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
+    }
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
 
@@ -480,9 +463,9 @@ static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
     a.src = ws.src;
     a.tdist = ws.tdist;
     a.tsig = ws.tsig;
-    a.abits = ws.abits[b];
+    a.abits = ws.abits[(k + 2) % 3];       // of product k - 1
     a.fbits = ws.fbits[b];
-    a.abits_n = ws.abits[bn];
+    a.abits_n = ws.abits[k % 3];
     a.fbits_n = ws.fbits[bn];
     a.cnt = ws.fdist[0];
     a.zeta = ws.fsig[0];
@@ -498,8 +481,12 @@ static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
     a.tau2 = (const uint32_t *)ws.tau2;
     a.tau_full = ws.flags + 1;
     a.nwords = (g->n + 31) / 32;
-    a.clear_bits = ws.abits[b];
+    a.clear_bits = ws.abits[(k + 2) % 3];
     a.clear_ctr = ws.counters + (size_t)((k + 1) % kCounterRing) * 4 * kCounterSlots;
+    if (a.nhubs == 0) {
+        a.next_bits = ws.abits[(k + 1) % 3];
+        a.next_ctr = a.clear_ctr;
+    }
     // on weighted graphs the backward products run on pairs of groups like
     // the forward one (one pass over the arcs and one lane-mask gather serve
     // both).  Unweighted graphs tie often, their DAG masks are dense and the
@@ -513,16 +500,12 @@ static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
 
 hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t s, hipEvent_t *ev) {
     Workspace &ws = g->ws;
-    // the counting product writes B_0 into buffer 0: clear its bitmap and
-    // this product's counters first
+    // the counting product writes B_0 into buffer 0: clear the bitmaps, the
+    // counters and the flag of the compact tau first
     const int nwords = (g->n + 31) / 32;
     const size_t nab = (size_t)nwords * ncg;
-    hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for(nab, 256, 4096)), dim3(256), 0, s, ws.abits[0], nab);
-    hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for(nab, 256, 4096)), dim3(256), 0, s, ws.abits[1], nab);
-    const size_t nctr = (size_t)kCounterRing * 4 * kCounterSlots * 2;   // u64 counters as u32 words
-    hipLaunchKernelGGL(k_zero_u32, dim3(blocks_for(nctr, 256)), dim3(256), 0, s,
-                       (uint32_t *)ws.counters, nctr);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, (uint32_t *)ws.flags + 1, (size_t)1);
+    hipLaunchKernelGGL(k_bwd_clear, dim3(blocks_for(nab, 256, 4096)), dim3(256), 0, s, ws.abits[0], ws.abits[1],
+                       ws.abits[2], nab, ws.counters, (int)kRingWords, ws.flags + 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     BwdArgs a = bwd_args(g, vw, ncg, 0);
@@ -558,45 +541,45 @@ hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t 
         }
     }
     if (ev) (void)hipEventRecord(ev[1], s);
-    int mgrid = blocks_for((size_t)a.nhubs * ncg, kWavesPerBlock, 0x7fffffff);
-    const int cgrid = blocks_for((size_t)a.nwords, kBlock, 1024);
-    if (cgrid > mgrid) mgrid = cgrid;
-    hipLaunchKernelGGL(k_bwd_count_merge<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
+    if (a.nhubs) {
+        int mgrid = blocks_for((size_t)a.nhubs * ncg, kWavesPerBlock, 0x7fffffff);
+        const int cgrid = blocks_for((size_t)a.nwords, kBlock, 1024);
+        if (cgrid > mgrid) mgrid = cgrid;
+        hipLaunchKernelGGL(k_bwd_count_merge<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
+    }
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
     return hipGetLastError();
 }
 
+template <int AM>
+static void launch_bwd_pull(const BwdArgs &a, int grid, hipStream_t s) {
+    if (a.nwide && a.next_bits)
+        hipLaunchKernelGGL((k_bwd_pull_w<AM, false, true>), dim3(grid), dim3(kBlock), 0, s, a);
+    else if (a.nwide)
+        hipLaunchKernelGGL((k_bwd_pull_w<AM, false, false>), dim3(grid), dim3(kBlock), 0, s, a);
+    else if (a.next_bits)
+        hipLaunchKernelGGL((k_bwd_pull<AM, false, true>), dim3(grid), dim3(kBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_bwd_pull<AM, false, false>), dim3(grid), dim3(kBlock), 0, s, a);
+}
+
 void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, int k, hipStream_t s, hipEvent_t *ev) {
-    BwdArgs a = bwd_args(g, vw, ncg, k);
-    if (a.nwide) {
-        if (ev) (void)hipEventRecord(ev[0], s);
-        const int grid = blocks_for((size_t)a.ntasks * a.nwide, kWavesPerBlock, 0x7fffffff);
-        switch (arc_mode(vw.out)) {
-            case 0: hipLaunchKernelGGL((k_bwd_pull_w<0, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-            case 1: hipLaunchKernelGGL((k_bwd_pull_w<1, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-            default: hipLaunchKernelGGL((k_bwd_pull_w<2, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        }
-        if (ev) (void)hipEventRecord(ev[1], s);
-        int mgrid = blocks_for((size_t)a.nhubs * a.nwide, kWavesPerBlock, 0x7fffffff);
-        const int cgrid = blocks_for((size_t)a.nwords, kBlock, 1024);
-        if (cgrid > mgrid) mgrid = cgrid;
-        hipLaunchKernelGGL(k_bwd_merge_w<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
-        if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
-        return;
-    }
+    const BwdArgs a = bwd_args(g, vw, ncg, k);
+    const int groups = a.nwide ? a.nwide : ncg;
     if (ev) (void)hipEventRecord(ev[0], s);
-    const size_t waves = (size_t)a.ntasks * ncg;
-    const int grid = blocks_for(waves, kWavesPerBlock, 0x7fffffff);
+    const int grid = blocks_for((size_t)a.ntasks * groups, kWavesPerBlock, 0x7fffffff);
     switch (arc_mode(vw.out)) {
-        case 0: hipLaunchKernelGGL((k_bwd_pull<0, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        case 1: hipLaunchKernelGGL((k_bwd_pull<1, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_bwd_pull<2, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 0: launch_bwd_pull<0>(a, grid, s); break;
+        case 1: launch_bwd_pull<1>(a, grid, s); break;
+        default: launch_bwd_pull<2>(a, grid, s); break;
     }
     if (ev) (void)hipEventRecord(ev[1], s);
-    int mgrid = blocks_for((size_t)a.nhubs * ncg, kWavesPerBlock, 0x7fffffff);
-    const int cgrid = blocks_for((size_t)a.nwords, kBlock, 1024);
-    if (cgrid > mgrid) mgrid = cgrid;
-    hipLaunchKernelGGL(k_bwd_merge<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
+    if (a.nhubs) {
+        const int mgrid = std::max(blocks_for((size_t)a.nhubs * groups, kWavesPerBlock, 0x7fffffff),
+                                   blocks_for((size_t)a.nwords, kBlock, 1024));
+        if (a.nwide) hipLaunchKernelGGL(k_bwd_merge_w<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL(k_bwd_merge<false>, dim3(mgrid), dim3(kBlock), 0, s, a);
+    }
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
 
@@ -651,7 +634,7 @@ void launch_trace_fwd(mfbc_graph *g, int ncg, int nb, int j, uint64_t *d_rows, h
     const int words64 = (g->n + 63) / 64;
     const size_t waves = (size_t)nb * words64;
     hipLaunchKernelGGL(k_trace_fwd, dim3(blocks_for(waves, kWavesPerBlock, 0x7fffffff)), dim3(kBlock),
-                       0, s, (const uint32_t *)ws.abits[b], (const uint32_t *)ws.fdist[b], g->n,
+                       0, s, (const uint32_t *)ws.abits[j % 3], (const uint32_t *)ws.fdist[b], g->n,
                        (g->n + 31) / 32, nb, fwd_wide_groups(ncg) ? 1 : 0, (const int32_t *)g->perm,
                        (const int64_t *)g->full.out.rp, d_rows, words64, ws.trace_relax + j);
 }

@@ -6,9 +6,9 @@
 // empty frontier (Algorithm 1's loop condition, over all columns of the
 // batch); then the counting product and the backward products until the
 // backward frontier is empty (Algorithm 2); lambda parts are accumulated by
-// the kernels as entries complete.  The size of each new frontier is read
-// back after every product (a 256-byte copy and a stream synchronisation);
-// that is the only host round trip of the loop.
+// the kernels as entries complete.  Products are enqueued in windows, and one
+// copy per window brings back their frontier sizes and the error flags; that
+// is the only host round trip of the loop.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -110,12 +110,11 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool admit = 
         f(ws.fdist[b], tile);
         f(ws.fsig[b], tile);
         f(ws.fbits[b], n * ncg);
-        f(ws.abits[b], nwords * ncg);
     }
+    for (auto &b : ws.abits) f(b, nwords * ncg);
     f(ws.pd, slots);
     f(ws.pm, slots);
-    f(ws.counters, (size_t)kCounterRing * 4 * kCounterSlots);
-    f(ws.flags, (size_t)4);
+    f(ws.counters, kCounterWords);
     f(ws.lam, n * ncg);
     f(ws.dag, (size_t)std::max<int64_t>(g ? (admit ? g->arcs : g->core.arcs) : 0, 1) * ncg);
     f(ws.src, (size_t)ncg * kWave);
@@ -202,6 +201,7 @@ int ensure_workspace(mfbc_graph *g, int ncg) {
         return rc;
     }
     ws.ncg = ncg;
+    ws.flags = (int32_t *)(ws.counters + kRingWords);
     return MFBC_OK;
 }
 
@@ -209,15 +209,17 @@ struct Counts {
     int64_t produced = 0, outputs = 0, active_vertices = 0, active_arcs = 0;
 };
 
-// Wait for the stream and copy the whole counter ring to the host.
+// Wait for the stream and copy the counter ring and the flags to the host.
 int read_ring(mfbc_graph *g, hipStream_t s) {
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(g->h_ctr, g->ws.counters,
-                           sizeof(unsigned long long) * kCounterRing * 4 * kCounterSlots,
+    HIP_TRY(hipMemcpyAsync(g->h_ctr, g->ws.counters, sizeof(unsigned long long) * kCounterWords,
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     return MFBC_OK;
 }
+
+// Flag i of the workspace from the host copy.
+int32_t ring_flag(const mfbc_graph *g, int i) { return ((const int32_t *)(g->h_ctr + kRingWords))[i]; }
 
 // Counters of product `idx` from the host copy of the ring (see flush_counts).
 Counts ring_counts(const mfbc_graph *g, int idx) {
@@ -269,7 +271,15 @@ int check_sources(mfbc_graph *g, const int32_t *d_sources, int64_t count, hipStr
     return MFBC_OK;
 }
 
-// Algorithm 1 on the batch whose sources are already in ws.src.
+// A batch's sources are checked by the kernel that sets them; the flag comes
+// back with the first window's counters, before any output is written.  The
+// message names the source.
+int bad_source(mfbc_graph *g, const int32_t *d_sources, int64_t count, hipStream_t s) {
+    const int rc = check_sources(g, d_sources, count, s);
+    return rc ? rc : fail(MFBC_EINVAL, "a source is outside [0, n)");
+}
+
+// Algorithm 1 on a batch of sources (d_sources nullable: already in ws.src).
 //
 // Products are enqueued kWindow at a time and their counters read back
 // once per window: a product whose predecessor produced nothing skips
@@ -280,9 +290,9 @@ int check_sources(mfbc_graph *g, const int32_t *d_sources, int64_t count, hipStr
 // Trace (d_rows non-null or h_relax non-null): frontier membership of F_j
 // after every product j <= max_products, as vertex bitmaps per column
 // (d_rows + (j-1) * nb * words), and the relaxations of every product.
-int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, bool trace, uint64_t *d_rows, int64_t *h_nnz,
+int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d_sources, bool trace, uint64_t *d_rows, int64_t *h_nnz,
                 int64_t *h_relax, int max_products, int32_t *products, hipStream_t s) {
-    launch_fwd_init(g, ncg, nb, s);
+    launch_fwd_init(g, ncg, nb, d_sources, s);
     if (trace) launch_trace_fwd(g, ncg, nb, 0, nullptr, s);
     const double arc_bytes = g->weighted ? 8.0 : 4.0;
     const size_t words = ((size_t)g->n + 63) / 64;
@@ -302,6 +312,7 @@ int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, bool trace, uint
         }
         int rc = read_ring(g, s);
         if (rc) return rc;
+        if (j == 0 && d_sources && ring_flag(g, 2)) return bad_source(g, d_sources, nb, s);
         for (int i = 0; i < kWindow; i++) {
             const int jj = j + 1 + i;
             st.fwd_pull_launches++;
@@ -322,8 +333,6 @@ int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, bool trace, uint
     }
     g->stats.fwd_products += last;
     if (products) *products = last;
-    int32_t flag = 0;
-    HIP_TRY(hipMemcpyAsync(&flag, g->ws.flags, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     if (trace && h_relax) {
         const int k = std::min(last, max_products);
         std::vector<unsigned long long> r((size_t)k + 1, 0ull);
@@ -332,8 +341,7 @@ int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, bool trace, uint
         HIP_TRY(hipStreamSynchronize(s));
         for (int i = 0; i < k; i++) h_relax[i] = (int64_t)r[(size_t)i];
     }
-    HIP_TRY(hipStreamSynchronize(s));
-    if (flag) return fail(MFBC_EOVERFLOW, "a shortest-path count overflowed binary64");
+    if (ring_flag(g, 0)) return fail(MFBC_EOVERFLOW, "a shortest-path count overflowed binary64");
     return MFBC_OK;
 }
 
@@ -410,13 +418,15 @@ int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d
     if (nb < 1) return fail(MFBC_EINVAL, "nb must be >= 1");
     if (!d_dist || !d_sigma) return fail(MFBC_EINVAL, "output pointer is NULL");
     if (trace && max_products < 0) return fail(MFBC_EINVAL, "max_products must be >= 0");
+    if (!d_sources) return fail(MFBC_EINVAL, "sources pointer is NULL");
     DeviceGuard dg(g->device);
     hipStream_t s = (hipStream_t)stream;
-    int rc = check_sources(g, d_sources, nb, s);
-    if (rc) return rc;
+    int rc;
     const int ncg = (nb + kWave - 1) / kWave;
     if ((rc = ensure_workspace(g, ncg))) return rc;
     if (trace) {
+        // the trace's buffers are outputs: the sources are checked before they are cleared
+        if ((rc = check_sources(g, d_sources, nb, s))) return rc;
         // relaxations of products 1 .. n + 1 + kWindow (every product a loop can launch)
         const int need = g->n + 2 + kWindow;
         if (g->ws.trace_len < need) {
@@ -432,8 +442,7 @@ int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d
                                    s));
     }
     g->stats = mfbc_stats{};
-    launch_set_sources(g, ncg, nb, d_sources, s);
-    if ((rc = run_forward(g, g->full, ncg, nb, trace, d_rows, h_nnz, h_relax, max_products, h_products, s)))
+    if ((rc = run_forward(g, g->full, ncg, nb, d_sources, trace, d_rows, h_nnz, h_relax, max_products, h_products, s)))
         return rc;
     g->stats.batches = 1;
     launch_export_forward(g, ncg, nb, d_dist, d_sigma, s);
@@ -448,19 +457,22 @@ int backward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, const int
     if (!g) return fail(MFBC_EINVAL, "graph handle is NULL");
     if (nb < 1) return fail(MFBC_EINVAL, "nb must be >= 1");
     if (!d_dist || !d_sigma || !d_delta) return fail(MFBC_EINVAL, "array pointer is NULL");
+    if (!d_sources) return fail(MFBC_EINVAL, "sources pointer is NULL");
     DeviceGuard dg(g->device);
     hipStream_t s = (hipStream_t)stream;
-    int rc = check_sources(g, d_sources, nb, s);
-    if (rc) return rc;
+    int rc;
     const int ncg = (nb + kWave - 1) / kWave;
     if ((rc = ensure_workspace(g, ncg))) return rc;
     g->stats = mfbc_stats{};
     launch_set_sources(g, ncg, nb, d_sources, s);
     launch_import_forward(g, ncg, nb, d_dist, d_sigma, s);
     g->trace_step = d_step != nullptr;
-    rc = run_backward(g, g->core, ncg, nb, h_products, s);
+    int32_t products = 0;
+    rc = run_backward(g, g->core, ncg, nb, &products, s);
     g->trace_step = false;
     if (rc) return rc;
+    if (ring_flag(g, 2)) return bad_source(g, d_sources, nb, s);
+    if (h_products) *h_products = products;
     g->stats.batches = 1;
     launch_export_backward(g, ncg, nb, d_delta, d_step, s);
     HIP_TRY(hipGetLastError());
@@ -584,7 +596,7 @@ struct Scratch {
 // uniform graphs of degree 256 7.1% / 6.9%, of degree 40 33% / 31%; R-MAT
 // scale 16 8.7% / 8.7%).
 void landmark_bounds(mfbc_graph &t, int count, hipStream_t s) {
-    launch_mono_init(&t, MFBC_OP_SSSP, 1, count, s);
+    launch_mono_init(&t, MFBC_OP_SSSP, 1, count, nullptr, s);
     for (int j = 1; j <= 6; j++) launch_mono_product(&t, MFBC_OP_SSSP, 1, j, s, nullptr);
 }
 
@@ -650,10 +662,10 @@ int build_core(mfbc_graph *g, hipStream_t s) {
         if (g->directed) mem.take(&to, tile);
         for (int i = 0; i < 2; i++) {
             mem.take(&ws.fdist[i], tile);
-            mem.take(&ws.abits[i], words);
         }
+        for (auto &b : ws.abits) mem.take(&b, words);
         mem.take(&ws.pd, (size_t)max_slots(g) * kWave);
-        mem.take(&ws.counters, (size_t)kCounterRing * 4 * kCounterSlots);
+        mem.take(&ws.counters, kCounterWords);
         mem.take(&ws.src, (size_t)kWave);
         mem.take(&keep, (size_t)g->arcs);
         mem.take(&cnt, n);
@@ -741,8 +753,7 @@ int bc_batches(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32
     for (int64_t b0 = 0; b0 < n_sources; b0 += batch) {
         const int nb = (int)std::min<int64_t>(batch, n_sources - b0);
         const int bcg = (nb + kWave - 1) / kWave;
-        launch_set_sources(g, bcg, nb, d_sources + b0, s);
-        if ((rc = run_forward(g, g->core, bcg, nb, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
+        if ((rc = run_forward(g, g->core, bcg, nb, d_sources + b0, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
             return rc;
         if ((rc = run_backward(g, g->core, bcg, nb, nullptr, s))) return rc;
         g->stats.batches++;
@@ -753,15 +764,22 @@ int bc_batches(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32
     return MFBC_OK;
 }
 
-// Lanes of one mfbc_bc call: independent batches run at once on separate
-// streams (each batch's products depend only on its own state), which hides
-// the launch and read-back latency of small graphs' products and lets the
-// sparse products of one batch share the device with another batch's.
-int lanes_for(const mfbc_graph *g, int64_t n_batches, int ncg) {
-    int S = g->lanes;
-    // by default only where a product is too small to fill the device
-    if (S <= 0) S = (double)g->core.arcs * (double)ncg <= (double)(1 << 24) ? kMaxLanes : 1;
-    return (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)S, (int64_t)kMaxLanes, n_batches}));
+// How the batches of one mfbc_bc call run when no lane count is set (a
+// column depends on its own column of every product alone, Section 3), by the
+// arcs times column groups of one batch:
+//  * up to 2^21, where a product is mostly latency: as one wide batch of four,
+//    or of as many as keep the state within 256 MB, so a small graph's whole
+//    source list shares each launch and read-back (n = 1,024 of degree 8, all
+//    sources in batches of 64: 3.95 ms on four streams, 1.04 as one batch);
+//  * up to 2^24: on four streams, each product large enough to fill the device
+//    only partly (unweighted R-MAT scale 16, 2,048 sources in batches of 512:
+//    18.4 ms, 19.5 as one wide batch);
+//  * above: one after another.
+int64_t merged_batches(const mfbc_graph *g, int32_t batch, int ncg) {
+    if ((double)g->core.arcs * (double)ncg > (double)(1 << 21)) return 1;
+    const double column = 39.0 * g->n + (double)g->core.arcs * 8.0 / kWave;
+    const double fit = (double)(256 << 20) / column / (double)batch;
+    return std::max<int64_t>(kMaxLanes, (int64_t)fit);
 }
 
 // Lane i of g (i = 0: g itself), created on first use; a view is refreshed
@@ -777,7 +795,7 @@ int lane_graph(mfbc_graph *g, int i, mfbc_graph **out) {
         if (!sh) return fail(MFBC_ENOMEM, "host allocation failed");
         sh->is_shadow = true;
         if (hipHostMalloc((void **)&sh->h_ctr,
-                          sizeof(unsigned long long) * kCounterRing * 4 * kCounterSlots) != hipSuccess) {
+                          sizeof(unsigned long long) * kCounterWords) != hipSuccess) {
             sh->h_ctr = nullptr;
             delete sh;
             sh = nullptr;
@@ -848,8 +866,7 @@ int bc_lanes(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t
             const int64_t b0 = b * batch;
             const int nb = (int)std::min<int64_t>(batch, n_sources - b0);
             const int bcg = (nb + kWave - 1) / kWave;
-            launch_set_sources(x, bcg, nb, d_sources + b0, ls[i]);
-            if (!r) r = run_forward(x, x->core, bcg, nb, false, nullptr, nullptr, nullptr, 0, nullptr, ls[i]);
+            if (!r) r = run_forward(x, x->core, bcg, nb, d_sources + b0, false, nullptr, nullptr, nullptr, 0, nullptr, ls[i]);
             if (!r) r = run_backward(x, x->core, bcg, nb, nullptr, ls[i]);
             x->stats.batches++;
         }
@@ -904,6 +921,7 @@ void carve_workspace(const mfbc_graph *g, int ncg, char *base, Workspace &ws) {
         off = align256(off + std::max<size_t>(count, 1) * sizeof(*p));
     });
     ws.ncg = groups;
+    ws.flags = (int32_t *)(ws.counters + kRingWords);
     ws.external = true;
 }
 
@@ -995,8 +1013,7 @@ int mfbc_load_graph(int32_t n, int64_t n_arcs, const int64_t *h_row_ptr, const i
     g->h_rp_out.assign(rp_o, rp_o + (size_t)n + 1);
     g->h_rp_in = directed ? rpt : g->h_rp_out;
     if (!rc && hipHostMalloc((void **)&g->h_ctr,
-                             sizeof(unsigned long long) * kCounterRing * 4 * kCounterSlots) !=
-                   hipSuccess) {
+                             sizeof(unsigned long long) * kCounterWords) != hipSuccess) {
         g->h_ctr = nullptr;
         rc = fail(MFBC_ENOMEM, "pinned host allocation failed");
     }
@@ -1037,17 +1054,16 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
     if (!mono_op_known(op)) return fail(MFBC_EINVAL, "unknown operation");
     if (nb < 1) return fail(MFBC_EINVAL, "nb must be >= 1");
     if (!d_out) return fail(MFBC_EINVAL, "output pointer is NULL");
+    if (!d_sources) return fail(MFBC_EINVAL, "sources pointer is NULL");
     DeviceGuard dg(g->device);
     hipStream_t s = (hipStream_t)hip_stream;
-    int rc = check_sources(g, d_sources, nb, s);
-    if (rc) return rc;
+    int rc;
     const int ncg = (nb + kWave - 1) / kWave;
     if ((rc = ensure_workspace(g, ncg))) return rc;
     g->stats = mfbc_stats{};
-    launch_set_sources(g, ncg, nb, d_sources, s);
     const bool bits = bits_fit(g, op);
-    if (bits) launch_bits_init(g, ncg, nb, s);
-    else launch_mono_init(g, op, ncg, nb, s);
+    if (bits) launch_bits_init(g, ncg, nb, d_sources, s);
+    else launch_mono_init(g, op, ncg, nb, d_sources, s);
     int planes = 0;              // planes of the product number cleared so far
     const double arc_bytes = g->weighted && op != MFBC_OP_BFS ? 8.0 : 4.0;
     mfbc_stats &st = g->stats;
@@ -1066,6 +1082,7 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
             else launch_mono_product(g, op, ncg, j + 1 + i, s, window_events(g, i, true));
         }
         if ((rc = read_ring(g, s))) return rc;
+        if (j == 0 && ring_flag(g, 2)) return bad_source(g, d_sources, nb, s);
         for (int i = 0; i < kWindow; i++) {
             const int jj = j + 1 + i;
             st.fwd_pull_launches++;
@@ -1126,11 +1143,28 @@ int mfbc_bc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t 
     if (!d_bc) return fail(MFBC_EINVAL, "d_bc is NULL");
     DeviceGuard dg(g->device);
     hipStream_t s = (hipStream_t)hip_stream;
-    int rc = check_sources(g, d_sources, n_sources, s);
-    if (rc) return rc;
+    if (n_sources > 0 && !d_sources) return fail(MFBC_EINVAL, "sources pointer is NULL");
+    int rc;
     const int ncg = bc_groups(n_sources, batch);
-    const int S = lanes_for(g, (n_sources + batch - 1) / batch, ncg);
-    if (S > 1) return bc_lanes(g, d_sources, n_sources, batch, ncg, S, d_bc, s);
+    const int64_t nbat = (n_sources + batch - 1) / batch;
+    const double work = (double)g->core.arcs * (double)ncg;
+    const int lanes = g->lanes ? g->lanes : (work > (double)(1 << 21) && work <= (double)(1 << 24) ? kMaxLanes : 1);
+    if (lanes > 1 && nbat > 1) {
+        if ((rc = check_sources(g, d_sources, n_sources, s))) return rc;
+        return bc_lanes(g, d_sources, n_sources, batch, ncg, (int)std::min<int64_t>(lanes, nbat), d_bc, s);
+    }
+    const int64_t wide = g->lanes ? 1 : std::min(nbat, merged_batches(g, batch, ncg));
+    if (wide > 1) {
+        const int64_t cols = std::min<int64_t>(n_sources, wide * batch);
+        const int wcg = bc_groups(n_sources, (int32_t)cols);
+        rc = ensure_workspace(g, wcg);
+        if (!rc) {
+            rc = bc_batches(g, d_sources, n_sources, (int32_t)cols, wcg, d_bc, s);
+            g->stats.batches = nbat;
+            return rc;
+        }
+        if (rc != MFBC_ENOMEM) return rc;      // else as the caller sized it
+    }
     if ((rc = ensure_workspace(g, ncg))) return rc;
     return bc_batches(g, d_sources, n_sources, batch, ncg, d_bc, s);
 }
@@ -1180,7 +1214,7 @@ int mfbc_bc_requests(mfbc_graph *g, const int32_t *d_sources, const int64_t *h_f
         launch_set_sources_spans(g, bcg, d_sources, sp, s);
         launch_lambda_zero(g, bcg, s);
         // padding columns (source -1) seed nothing and reach nothing
-        if ((rc = run_forward(g, g->core, bcg, bcg * kWave, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
+        if ((rc = run_forward(g, g->core, bcg, bcg * kWave, nullptr, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
             return rc;
         if ((rc = run_backward(g, g->core, bcg, bcg * kWave, nullptr, s))) return rc;
         launch_lambda_add_groups(g, bcg, o, s);
@@ -1209,6 +1243,7 @@ int mfbc_bc_noalloc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, 
     DeviceGuard dg(g->device);
     hipStream_t s = (hipStream_t)hip_stream;
     int ncg = bc_groups(n_sources, batch);
+    const int64_t nbat = (n_sources + batch - 1) / batch;
     const size_t need = ws_bytes(g, ncg, true);
     if (need > kScratchBytes)
         return fail(MFBC_ENOMEM, "mfbc_bc_noalloc: this graph and batch need " + std::to_string(need) +
@@ -1218,6 +1253,11 @@ int mfbc_bc_noalloc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, 
     // parts (lambda is a sum over sources)
     while (ncg > 1 && ws_bytes(g, ncg, false) > kScratchSize) {
         ncg /= 2;
+        batch = ncg * kWave;
+    }
+    // several batches as one wide one while they fit, as in mfbc_bc
+    while (!g->lanes && ncg * (int64_t)kWave < n_sources && ws_bytes(g, 2 * ncg, false) <= kScratchSize) {
+        ncg = (int)std::min<int64_t>(2 * ncg, bc_groups(n_sources, INT32_MAX));
         batch = ncg * kWave;
     }
     if (ws_bytes(g, ncg, false) > kScratchSize)
@@ -1235,7 +1275,9 @@ int mfbc_bc_noalloc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, 
     HIP_TRY(hipMemcpyAsync(g->h_ctr, g->ws.flags + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (*(const int32_t *)g->h_ctr != 0) return fail(MFBC_EINVAL, "a source is outside [0, n)");
-    return bc_batches(g, d_sources, n_sources, batch, ncg, d_bc, s);
+    rc = bc_batches(g, d_sources, n_sources, batch, ncg, d_bc, s);
+    g->stats.batches = nbat;
+    return rc;
 }
 
 int mfbc_set_plan(mfbc_graph *g, int32_t run_arcs, int32_t run_verts, int32_t heavy,

@@ -26,6 +26,8 @@ constexpr int kBlock = kWave * kWavesPerBlock;
 constexpr int32_t kInf = MFBC_INF_DIST;
 constexpr int kCounterSlots = 32;        // spread of the frontier-size counters
 constexpr int kCounterRing = 16;         // products whose counters are live at once
+constexpr size_t kRingWords = (size_t)kCounterRing * 4 * kCounterSlots;
+constexpr size_t kCounterWords = kRingWords + 8;     // the ring and the flags
 constexpr int kWindow = 8;               // products enqueued per read-back of their counters
                                          // (at most kCounterRing - 1)
 constexpr int kWide = 2;                 // column groups per wave in the forward product
@@ -91,11 +93,13 @@ struct Workspace {
     int32_t *fdist[2] = {nullptr, nullptr};  // frontier weights (double-buffered)
     double *fsig[2] = {nullptr, nullptr};    // frontier multiplicities
     uint64_t *fbits[2] = {nullptr, nullptr}; // frontier lane masks [cg][n]
-    uint32_t *abits[2] = {nullptr, nullptr}; // activity bitmaps [cg][n/32] (backward: plane 0)
+    uint32_t *abits[3] = {};           // activity bitmaps [cg][n/32]: F_j in abits[j % 3]
     int32_t *pd = nullptr;             // partial weights / counters [cg][slots][64]
     double *pm = nullptr;              // partial multiplicities / sums
-    unsigned long long *counters = nullptr;  // [ring][4][slots]
-    int32_t *flags = nullptr;          // [0]: path count overflow, [1]: source out of range
+    unsigned long long *counters = nullptr;  // [ring][4][slots], then the flags
+    int32_t *flags = nullptr;          // [0] path count overflow, [1] tau beyond 16 bits,
+                                       // [2] source out of range (in `counters`' allocation,
+                                       // so that one copy reads both)
     double *lam = nullptr;             // per-column-group lambda parts [cg][n]
     int32_t *src = nullptr;            // column -> source vertex, -1 = padding
     uint64_t *dag = nullptr;           // shortest-path DAG: lane mask per out-arc [cg][arcs]
@@ -155,7 +159,8 @@ struct mfbc_graph {
 namespace mfbc {
 
 // ---- launchers (kernels.hip) ----
-void launch_fwd_init(mfbc_graph *g, int ncg, int nb, hipStream_t s);
+// d_sources (nullable): the batch's sources, caller ids; else ws.src is set already.
+void launch_fwd_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s);
 // `ev` (nullable): three events recorded before the product kernel, between
 // it and the merge kernel, and after the merge.  Product j (k) skips itself
 // on the device when product j-1 (k-1) produced no frontier entry.
@@ -192,6 +197,7 @@ void launch_import_forward(mfbc_graph *g, int ncg, int nb, const int32_t *d_dist
                            const double *d_sigma, hipStream_t s);
 void launch_export_backward(mfbc_graph *g, int ncg, int nb, double *d_delta, int32_t *d_step,
                             hipStream_t s);
+// ws.src from a source list; ws.flags[2] := whether one is outside [0, n).
 void launch_set_sources(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s);
 // *d_bad := 1 if a source is outside [0, n), else 0 (no host copy of the list).
 void launch_check_sources(const int32_t *d_sources, int64_t count, int n, int32_t *d_bad,
@@ -201,7 +207,7 @@ void launch_export_tiles_i32(mfbc_graph *g, int ncg, int nb, const int32_t *tile
 
 // ---- monoid fixpoints (monoid.hip) ----
 bool mono_op_known(int op);
-void launch_mono_init(mfbc_graph *g, int op, int ncg, int nb, hipStream_t s);
+void launch_mono_init(mfbc_graph *g, int op, int ncg, int nb, const int32_t *d_sources, hipStream_t s);
 void launch_mono_product(mfbc_graph *g, int op, int ncg, int j, hipStream_t s, hipEvent_t *ev);
 
 // ---- batched form (batched.hip) ----
@@ -216,7 +222,7 @@ ManyWorkspace &many_workspace(int device);
 // ---- fixpoints on bit masks (bits.hip) ----
 bool bits_fit(const mfbc_graph *g, int op);
 void launch_plan_owner(const Csr &c, const Plan &pl, hipStream_t s);
-void launch_bits_init(mfbc_graph *g, int ncg, int nb, hipStream_t s);
+void launch_bits_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s);
 void launch_bits_planes(mfbc_graph *g, int ncg, int from, int to, hipStream_t s);
 void launch_bits_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev);
 void launch_bits_export(mfbc_graph *g, int op, int ncg, int nb, int planes, void *out, hipStream_t s);

@@ -47,6 +47,8 @@ struct MonoArgs {
     const unsigned long long *prev_ctr;  // nullable: those of product j-1 (live_prev)
     uint32_t *clear_bits;      // merge: F_{j-1}'s bitmaps
     unsigned long long *clear_ctr;
+    uint32_t *next_bits;       // no split rows: F_{j+1}'s bitmaps and counters (close_product)
+    unsigned long long *next_ctr;
     int nwide;                 // pairs of groups (paired layout), 0: one group per wave
 };
 
@@ -210,9 +212,12 @@ struct MonoPull : PullDefaults {
 };
 
 // ------------------------------------------------------------------ kernels
-template <class Op, int AM, int W>
+template <class Op, int AM, int W, bool C>
 __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS void k_mono_pull(MonoArgs a) {
-    if (!live_prev(a.prev_ctr)) return;
+    if (!live_prev(a.prev_ctr)) {
+        if constexpr (C) close_skipped(a.next_ctr);
+        return;
+    }
     const int wid = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const int groups = W == 1 ? a.ncg : a.nwide;
     const int q = wid / a.ntasks;
@@ -221,7 +226,9 @@ __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS void k_mono_pull(MonoArgs a
         MonoPull<Op, AM, W> p(a, q, produced, outs);
         pull_task(p, a.tasks + (wid - q * a.ntasks), a.rp, a.arcs);
     }
-    flush_counts(produced, outs, 0, 0, a.ctr);
+    unsigned long long nv = 0, na = 0;
+    if constexpr (C) close_product(a.abits, a.next_bits, a.nwords, groups, a.rp, a.next_ctr, nv, na);
+    flush_counts(produced, outs, nv, na, a.ctr);
 }
 
 // Hub slices of F_{j-1}'s product; also clears F_{j-1}'s bitmaps (counting
@@ -247,42 +254,43 @@ __global__ __launch_bounds__(kBlock) void k_mono_merge(MonoArgs a) {
     flush_counts(produced, outs, nv, na, a.ctr);
 }
 
-// T = absent everywhere, both bitmaps and all counters cleared.
+// T = absent everywhere, the bitmaps and all counters cleared.
 template <class Op>
-__global__ void k_mono_fill(typename Op::V *tval, size_t total, uint32_t *ab0, uint32_t *ab1, size_t nab,
-                            unsigned long long *ctr, int nctr) {
+__global__ void k_mono_fill(typename Op::V *tval, size_t total, uint32_t *ab0, uint32_t *ab1, uint32_t *ab2,
+                            size_t nab, unsigned long long *ctr, int nctr) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (size_t i = t0; i < total; i += stride) tval[i] = Op::absent();
     for (size_t i = t0; i < nab; i += stride) {
         ab0[i] = 0u;
         ab1[i] = 0u;
+        ab2[i] = 0u;
     }
     for (size_t i = t0; i < (size_t)nctr; i += stride) ctr[i] = 0ull;
 }
 
-// The sources' rows of the first frontier start with every lane of their
-// plane absent (W groups per lane) ...
+// Seeds (launch_seed): the sources' rows of the first frontier start with
+// every lane of their plane absent (W groups per lane), then T(s, s) = the
+// seed and the first frontier is {s} carrying it.
 template <class Op, int W>
-__global__ void k_mono_seed_rows(const int32_t *src, int nb, int n, typename Op::V *fval) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb) return;
-    const size_t row = ((size_t)(c / (W * kWave)) * n + src[c]) * kWave * W;
-    for (int l = 0; l < kWave * W; l++) fval[row + l] = Op::absent();
-}
-
-// ... then T(s, s) = the seed and the first frontier is {s} carrying it.
-template <class Op, int W>
-__global__ void k_mono_seed(const int32_t *src, int nb, int n, int nwords, typename Op::V *tval,
-                            typename Op::V *fval, uint32_t *abits) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nb) return;
-    const int v = src[c];
-    const int cg = c / kWave, lane = c % kWave, q = cg / W;
-    tval[((size_t)cg * n + v) * kWave + lane] = Op::seed();
-    fval[(((size_t)q * n + v) * kWave + lane) * W + (cg % W)] = Op::seed();
-    atomicOr(abits + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
-}
+struct MonoSeed {
+    static constexpr int kGroups = W;
+    using V = typename Op::V;
+    int n, nwords;
+    V *tval, *fval;
+    uint32_t *abits;
+    __device__ void row(int v, int q, int lane) const {
+        V *p = fval + ((size_t)q * n + v) * kWave * W;
+#pragma unroll
+        for (int c = 0; c < W; c++) p[c * kWave + lane] = Op::absent();
+    }
+    __device__ void entry(int v, int c) const {
+        const int cg = c / kWave, lane = c % kWave, q = cg / W;
+        tval[((size_t)cg * n + v) * kWave + lane] = Op::seed();
+        fval[(((size_t)q * n + v) * kWave + lane) * W + (cg % W)] = Op::seed();
+        atomicOr(abits + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
+    }
+};
 
 inline int nblk(size_t work, int per, int cap = 0x7fffffff) {
     size_t b = (work + per - 1) / per;
@@ -301,12 +309,12 @@ ArcSrc mono_arcs(const Csr &c) {
 
 int mono_mode(const Csr &c) { return c.pk ? 1 : (c.w ? 2 : 0); }
 
-template <class Op, int W>
+template <class Op, int W, bool C>
 void launch_pull(int mode, int grid, hipStream_t s, const MonoArgs &a) {
     switch (mode) {
-        case 0: hipLaunchKernelGGL((k_mono_pull<Op, 0, W>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        case 1: hipLaunchKernelGGL((k_mono_pull<Op, 1, W>), dim3(grid), dim3(kBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_mono_pull<Op, 2, W>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 0: hipLaunchKernelGGL((k_mono_pull<Op, 0, W, C>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 1: hipLaunchKernelGGL((k_mono_pull<Op, 1, W, C>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        default: hipLaunchKernelGGL((k_mono_pull<Op, 2, W, C>), dim3(grid), dim3(kBlock), 0, s, a); break;
     }
 }
 
@@ -314,26 +322,25 @@ void launch_pull(int mode, int grid, hipStream_t s, const MonoArgs &a) {
 // number of groups).
 int mono_pairs(int ncg) { return ncg >= 2 ? (ncg + 1) / 2 : 0; }
 
+template <class Op, int W>
+void mono_seed(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
+    using V = typename Op::V;
+    Workspace &ws = g->ws;
+    const MonoSeed<Op, W> seed{g->n, (g->n + 31) / 32, (V *)ws.tdist, (V *)ws.fdist[0], ws.abits[0]};
+    launch_seed(g, seed, ncg, nb, d_sources, s);
+}
+
 template <class Op>
-void mono_init(mfbc_graph *g, int ncg, int nb, hipStream_t s) {
+void mono_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
     using V = typename Op::V;
     Workspace &ws = g->ws;
     const size_t total = (size_t)ncg * g->n * kWave;
     const int nwords = (g->n + 31) / 32;
-    hipLaunchKernelGGL(k_mono_fill<Op>, dim3(nblk(total, 256, 65536)), dim3(256), 0, s, (V *)ws.tdist,
-                       total, ws.abits[0], ws.abits[1], (size_t)ncg * nwords, ws.counters,
-                       kCounterRing * 4 * kCounterSlots);
-    if (mono_pairs(ncg)) {
-        hipLaunchKernelGGL((k_mono_seed_rows<Op, 2>), dim3(nblk(nb, 256)), dim3(256), 0, s, ws.src, nb,
-                           g->n, (V *)ws.fdist[0]);
-        hipLaunchKernelGGL((k_mono_seed<Op, 2>), dim3(nblk(nb, 256)), dim3(256), 0, s, ws.src, nb, g->n,
-                           nwords, (V *)ws.tdist, (V *)ws.fdist[0], ws.abits[0]);
-        return;
-    }
-    hipLaunchKernelGGL((k_mono_seed_rows<Op, 1>), dim3(nblk(nb, 256)), dim3(256), 0, s, ws.src, nb, g->n,
-                       (V *)ws.fdist[0]);
-    hipLaunchKernelGGL((k_mono_seed<Op, 1>), dim3(nblk(nb, 256)), dim3(256), 0, s, ws.src, nb, g->n,
-                       nwords, (V *)ws.tdist, (V *)ws.fdist[0], ws.abits[0]);
+    hipLaunchKernelGGL(k_mono_fill<Op>, dim3(nblk(total, 256, 65536)), dim3(256), 0, s, (V *)ws.tdist, total,
+                       ws.abits[0], ws.abits[1], ws.abits[2], (size_t)ncg * nwords, ws.counters,
+                       (int)kRingWords);
+    if (mono_pairs(ncg)) mono_seed<Op, 2>(g, ncg, nb, d_sources, s);
+    else mono_seed<Op, 1>(g, ncg, nb, d_sources, s);
 }
 
 template <class Op>
@@ -351,28 +358,38 @@ void mono_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev) 
     a.nwords = (g->n + 31) / 32;
     a.rp = g->full.in.rp;
     a.arcs = mono_arcs(g->full.in);
-    a.abits = ws.abits[b];
+    a.abits = ws.abits[(j - 1) % 3];
     a.fval = ws.fdist[b];
     a.tval = ws.tdist;
-    a.abits_n = ws.abits[b ^ 1];
+    a.abits_n = ws.abits[j % 3];
     a.fval_n = ws.fdist[b ^ 1];
     a.pd = ws.pd;
     a.ctr = ws.counters + (size_t)(j % kCounterRing) * 4 * kCounterSlots;
     a.prev_ctr = j > 1 ? ws.counters + (size_t)((j - 1) % kCounterRing) * 4 * kCounterSlots : nullptr;
-    a.clear_bits = ws.abits[b];
+    a.clear_bits = ws.abits[(j - 1) % 3];
     a.clear_ctr = ws.counters + (size_t)((j + 1) % kCounterRing) * 4 * kCounterSlots;
+    if (a.nhubs == 0) {
+        a.next_bits = ws.abits[(j + 1) % 3];
+        a.next_ctr = a.clear_ctr;
+    }
     a.nwide = mono_pairs(ncg);
     const int waves_per_task = a.nwide ? a.nwide : ncg;
     if (ev) (void)hipEventRecord(ev[0], s);
     const int grid = nblk((size_t)a.ntasks * waves_per_task, kWavesPerBlock);
-    if (a.nwide) launch_pull<Op, 2>(mono_mode(g->full.in), grid, s, a);
-    else launch_pull<Op, 1>(mono_mode(g->full.in), grid, s, a);
+    const int mode = mono_mode(g->full.in);
+    if (a.next_bits) {
+        if (a.nwide) launch_pull<Op, 2, true>(mode, grid, s, a);
+        else launch_pull<Op, 1, true>(mode, grid, s, a);
+    } else {
+        if (a.nwide) launch_pull<Op, 2, false>(mode, grid, s, a);
+        else launch_pull<Op, 1, false>(mode, grid, s, a);
+    }
     if (ev) (void)hipEventRecord(ev[1], s);
     const int mgrid = std::max(nblk((size_t)a.nhubs * waves_per_task, kWavesPerBlock),
                                nblk((size_t)a.nwords, kBlock, 1024));
-    if (a.nwide)
+    if (a.nhubs && a.nwide)
         hipLaunchKernelGGL((k_mono_merge<Op, 2>), dim3(mgrid), dim3(kBlock), 0, s, a);
-    else
+    else if (a.nhubs)
         hipLaunchKernelGGL((k_mono_merge<Op, 1>), dim3(mgrid), dim3(kBlock), 0, s, a);
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
@@ -383,12 +400,12 @@ bool mono_op_known(int op) {
     return op == MFBC_OP_SSSP || op == MFBC_OP_BFS || op == MFBC_OP_WIDEST || op == MFBC_OP_RESIST;
 }
 
-void launch_mono_init(mfbc_graph *g, int op, int ncg, int nb, hipStream_t s) {
+void launch_mono_init(mfbc_graph *g, int op, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
     switch (op) {
-        case MFBC_OP_SSSP: mono_init<OpSssp>(g, ncg, nb, s); break;
-        case MFBC_OP_BFS: mono_init<OpBfs>(g, ncg, nb, s); break;
-        case MFBC_OP_WIDEST: mono_init<OpWidest>(g, ncg, nb, s); break;
-        default: mono_init<OpResist>(g, ncg, nb, s); break;
+        case MFBC_OP_SSSP: mono_init<OpSssp>(g, ncg, nb, d_sources, s); break;
+        case MFBC_OP_BFS: mono_init<OpBfs>(g, ncg, nb, d_sources, s); break;
+        case MFBC_OP_WIDEST: mono_init<OpWidest>(g, ncg, nb, d_sources, s); break;
+        default: mono_init<OpResist>(g, ncg, nb, d_sources, s); break;
     }
 }
 

@@ -98,6 +98,116 @@ __device__ __forceinline__ void clear_and_count(uint32_t *bits, int words, int p
 }
 
 
+// A plan without split rows needs no merge kernel: the product kernel itself
+// (its C form; a flag instead cost the other form registers and up to 6%)
+// clears the bitmaps of the product after it (`next`, last read two products
+// ago) and the counters of that product, and counts the vertices of the
+// frontier it reads and their arcs.  One launch per product instead of two,
+// 4 us each: products of small graphs take 5 to 10.
+__device__ __forceinline__ void close_product(const uint32_t *bits, uint32_t *next, int words, int planes,
+                                              const int64_t *rp, unsigned long long *next_ctr,
+                                              unsigned long long &nv, unsigned long long &na) {
+    const int gtid = blockIdx.x * blockDim.x + threadIdx.x;
+    if (gtid < 4 * kCounterSlots) next_ctr[gtid] = 0ull;
+    for (int i = gtid; i < words; i += gridDim.x * blockDim.x) {
+        uint32_t w = 0u;
+        for (int p = 0; p < planes; p++) {
+            w |= bits[(size_t)p * words + i];
+            next[(size_t)p * words + i] = 0u;
+        }
+        const int64_t *r = rp + (size_t)i * 32;
+        nv += __popc(w);
+        while (w) {
+            const int b0 = __ffs(w) - 1;
+            const uint32_t from = w >> b0;
+            const int len = ~from ? __ffs(~from) - 1 : 32 - b0;
+            na += (unsigned long long)(r[b0 + len] - r[b0]);
+            w &= ~(uint32_t)(((1ull << len) - 1ull) << b0);
+        }
+    }
+}
+
+// The same for a product that is skipped (live_prev): only its successor's
+// counters, which must read as empty.
+__device__ __forceinline__ void close_skipped(unsigned long long *next_ctr) {
+    const int gtid = blockIdx.x * blockDim.x + threadIdx.x;
+    if (gtid < 4 * kCounterSlots) next_ctr[gtid] = 0ull;
+}
+
+// Sources of a batch and its first frontier in one workgroup: the source
+// list to device ids (d_in nullable: src is set already; -1 pads), whether one
+// is out of range, then every source's row filled by one wave, then the
+// entries of the sources themselves.  S::row(v, q, lane) fills this lane's
+// part of the row of vertex v in row group q, S::kGroups column groups to a
+// row; S::entry(v, c) writes column c's own entry.
+template <class S>
+__global__ __launch_bounds__(1024) void k_seed_block(S s, int32_t *src, int total, int nb,
+                                                     const int32_t *d_in, const int32_t *perm, int n,
+                                                     int32_t *bad) {
+    bool out = false;
+    if (d_in) {
+        for (int c = threadIdx.x; c < total; c += blockDim.x) {
+            int v = -1;
+            if (c < nb) {
+                v = d_in[c];
+                if (v < 0 || v >= n) {
+                    out = true;
+                    v = -1;
+                }
+            }
+            src[c] = v >= 0 && perm ? perm[v] : v;
+        }
+        const int any = __syncthreads_or(out);
+        if (threadIdx.x == 0 && bad) *bad = any;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int c = threadIdx.x >> 6; c < nb; c += (int)(blockDim.x >> 6)) {
+        const int v = src[c];
+        if (v >= 0) s.row(v, c / (S::kGroups * kWave), lane);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < nb; c += blockDim.x)
+        if (src[c] >= 0) s.entry(src[c], c);
+}
+
+// The same steps over a grid, for batches that one workgroup would take long for.
+template <class S>
+__global__ void k_seed_rows(S s, const int32_t *src, int nb) {
+    const int w = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (w < nb && src[w] >= 0) s.row(src[w], w / (S::kGroups * kWave), (int)(threadIdx.x & (kWave - 1)));
+}
+template <class S>
+__global__ void k_seed_entries(S s, const int32_t *src, int nb) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c < nb && src[c] >= 0) s.entry(src[c], c);
+}
+struct NoSeed {              // the source list alone
+    static constexpr int kGroups = 1;
+    __device__ void row(int, int, int) const {}
+    __device__ void entry(int, int) const {}
+};
+
+constexpr int kSeedBlockMax = 1024;      // columns seeded by one workgroup
+
+template <class S>
+void launch_seed(mfbc_graph *g, const S &seed, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
+    Workspace &ws = g->ws;
+    const int total = ncg * kWave;
+    const int32_t *perm = g->perm;
+    if (nb <= kSeedBlockMax) {
+        hipLaunchKernelGGL(k_seed_block<S>, dim3(1), dim3(1024), 0, s, seed, ws.src, total, nb, d_sources, perm,
+                           g->n, ws.flags ? ws.flags + 2 : nullptr);
+        return;
+    }
+    if (d_sources)
+        hipLaunchKernelGGL(k_seed_block<NoSeed>, dim3(1), dim3(1024), 0, s, NoSeed{}, ws.src, total, nb,
+                           d_sources, perm, g->n, ws.flags ? ws.flags + 2 : nullptr);
+    hipLaunchKernelGGL(k_seed_rows<S>, dim3((nb + 3) / 4), dim3(256), 0, s, seed, (const int32_t *)ws.src, nb);
+    hipLaunchKernelGGL(k_seed_entries<S>, dim3((nb + 255) / 256), dim3(256), 0, s, seed, (const int32_t *)ws.src,
+                       nb);
+}
+
 // Record the columns of group cg that produced frontier entries (one atomic
 // per wave, spread over 32 copies that the host ORs together).
 __device__ __forceinline__ void flush_colmask(unsigned long long *colmask, int ncg, int cg,
@@ -140,6 +250,8 @@ struct FwdArgs {
     int32_t *flags;
     uint32_t *clear_bits;      // merge: bitmaps to clear (F_{j-1}'s), ncg planes
     unsigned long long *clear_ctr;  // merge: counter slots of product j+1
+    uint32_t *next_bits;       // no split rows: bitmaps of F_{j+1} (close_product; else null)
+    unsigned long long *next_ctr;   //   and its counter slots
     unsigned long long *colmask;    // nullable: [32][ncg_all] columns that produced entries
     const int32_t *cglist;     // nullable: the ncg column groups of this launch (else 0..ncg-1)
     int ncg_all;               // column groups of the state (strides of colmask, bitmap planes)
@@ -512,6 +624,8 @@ struct BwdArgs {
     const unsigned long long *prev_ctr;  // nullable: counter slots of product k-1 (live_prev)
     uint32_t *clear_bits;      // ncg planes
     unsigned long long *clear_ctr;
+    uint32_t *next_bits;       // as in FwdArgs
+    unsigned long long *next_ctr;
     unsigned long long *colmask;    // nullable: [32][ncg_all] columns that produced entries
     const uint64_t *cmask;     // counting product: nullable per-group lane mask of the
                                // columns to count (others are left untouched)
@@ -1071,14 +1185,19 @@ __device__ __forceinline__ int pick_cg(const int32_t *cglist, int cg) {
     return cg;
 }
 
-template <int AM, bool L>
+template <int AM, bool L, bool C>
 __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS void k_fwd_pull(FwdArgs a) {
-    if (!live_prev(a.prev_ctr)) return;
+    if (!live_prev(a.prev_ctr)) {
+        if constexpr (C) close_skipped(a.next_ctr);
+        return;
+    }
     const int wid = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const int cg = wid / a.ntasks;                       // column-group major
     unsigned long long produced = 0, outs = 0;
     if (cg < a.ncg) fwd_task<AM>(a, pick_cg<L>(a.cglist, cg), wid - cg * a.ntasks, produced, outs);
-    flush_counts(produced, outs, 0, 0, a.ctr);
+    unsigned long long nv = 0, na = 0;
+    if constexpr (C) close_product(a.abits, a.next_bits, a.nwords, a.ncg_all, a.rp, a.next_ctr, nv, na);
+    flush_counts(produced, outs, nv, na, a.ctr);
 }
 
 // A merge whose product was skipped (see live_prev) only clears the next
@@ -1104,14 +1223,19 @@ __global__ __launch_bounds__(kBlock) void k_fwd_merge(FwdArgs a) {
 // Wide forward product: wave = (wide group, task), group-major.  With L the
 // launch covers the a.nwide wide groups listed in a.cglist (served form),
 // else groups 0 .. a.nwide-1; the merge clears a.nwide_all bitmap planes.
-template <int AM, int W, bool L>
+template <int AM, int W, bool L, bool C>
 __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS void k_fwd_pull_w(FwdArgs a) {
-    if (!live_prev(a.prev_ctr)) return;
+    if (!live_prev(a.prev_ctr)) {
+        if constexpr (C) close_skipped(a.next_ctr);
+        return;
+    }
     const int wid = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const int q = wid / a.ntasks;
     unsigned long long produced = 0, outs = 0;
     if (q < a.nwide) fwd_task_w<AM, W>(a, pick_cg<L>(a.cglist, q), wid - q * a.ntasks, produced, outs);
-    flush_counts(produced, outs, 0, 0, a.ctr);
+    unsigned long long nv = 0, na = 0;
+    if constexpr (C) close_product(a.abits, a.next_bits, a.nwords, a.nwide_all, a.rp, a.next_ctr, nv, na);
+    flush_counts(produced, outs, nv, na, a.ctr);
 }
 
 template <int W, bool L>
@@ -1167,26 +1291,36 @@ __global__ __launch_bounds__(kBlock) void k_bwd_count_merge(BwdArgs a) {
     flush_counts(produced, 0, 0, 0, a.ctr);
 }
 
-template <int AM, bool L>
+template <int AM, bool L, bool C>
 __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS __attribute__((amdgpu_waves_per_eu(8))) void k_bwd_pull(BwdArgs a) {
-    if (!live_prev(a.prev_ctr)) return;
+    if (!live_prev(a.prev_ctr)) {
+        if constexpr (C) close_skipped(a.next_ctr);
+        return;
+    }
     const int wid = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const int cg = wid / a.ntasks;                       // column-group major
     unsigned long long produced = 0, outs = 0;
     if (cg < a.ncg) bwd_task<AM>(a, pick_cg<L>(a.cglist, cg), wid - cg * a.ntasks, produced, outs);
-    flush_counts(produced, outs, 0, 0, a.ctr);
+    unsigned long long nv = 0, na = 0;
+    if constexpr (C) close_product(a.abits, a.next_bits, a.nwords, a.ncg_all, a.rp, a.next_ctr, nv, na);
+    flush_counts(produced, outs, nv, na, a.ctr);
 }
 
 // Paired backward product: wave = (pair, task), pair-major; with L over the
 // a.nwide pairs listed in a.cglist (served form).
-template <int AM, bool L>
+template <int AM, bool L, bool C>
 __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS void k_bwd_pull_w(BwdArgs a) {
-    if (!live_prev(a.prev_ctr)) return;
+    if (!live_prev(a.prev_ctr)) {
+        if constexpr (C) close_skipped(a.next_ctr);
+        return;
+    }
     const int wid = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const int q = wid / a.ntasks;
     unsigned long long produced = 0, outs = 0;
     if (q < a.nwide) bwd_task_w<AM, L>(a, pick_cg<L>(a.cglist, q), wid - q * a.ntasks, produced, outs);
-    flush_counts(produced, outs, 0, 0, a.ctr);
+    unsigned long long nv = 0, na = 0;
+    if constexpr (C) close_product(a.abits, a.next_bits, a.nwords, a.nwide_all, a.rp, a.next_ctr, nv, na);
+    flush_counts(produced, outs, nv, na, a.ctr);
 }
 
 template <bool L>

@@ -690,9 +690,9 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
             a.colmask = s->colmask + (size_t)r * cmw;
             const int grid = nblocks((size_t)a.ntasks * nf, kWavesPerBlock, 0x7fffffff);
             switch (srv_mode(g->core.in)) {
-                case 0: hipLaunchKernelGGL((k_fwd_pull_w<0, kWide, true>), dim3(grid), dim3(kBlock), 0, st, a); break;
-                case 1: hipLaunchKernelGGL((k_fwd_pull_w<1, kWide, true>), dim3(grid), dim3(kBlock), 0, st, a); break;
-                default: hipLaunchKernelGGL((k_fwd_pull_w<2, kWide, true>), dim3(grid), dim3(kBlock), 0, st, a); break;
+                case 0: hipLaunchKernelGGL((k_fwd_pull_w<0, kWide, true, false>), dim3(grid), dim3(kBlock), 0, st, a); break;
+                case 1: hipLaunchKernelGGL((k_fwd_pull_w<1, kWide, true, false>), dim3(grid), dim3(kBlock), 0, st, a); break;
+                default: hipLaunchKernelGGL((k_fwd_pull_w<2, kWide, true, false>), dim3(grid), dim3(kBlock), 0, st, a); break;
             }
             const int mgrid = std::max(nblocks((size_t)a.nhubs * nf, kWavesPerBlock, 0x7fffffff),
                                        nblocks((size_t)nw, kBlock, 1024));
@@ -717,9 +717,9 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
             c.cglist = s->cglists + ncg;
             const int grid = nblocks((size_t)c.ntasks * nbk, kWavesPerBlock, 0x7fffffff);
             switch (mode) {
-                case 0: hipLaunchKernelGGL((k_bwd_pull_w<0, true>), dim3(grid), dim3(kBlock), 0, st, c); break;
-                case 1: hipLaunchKernelGGL((k_bwd_pull_w<1, true>), dim3(grid), dim3(kBlock), 0, st, c); break;
-                default: hipLaunchKernelGGL((k_bwd_pull_w<2, true>), dim3(grid), dim3(kBlock), 0, st, c); break;
+                case 0: hipLaunchKernelGGL((k_bwd_pull_w<0, true, false>), dim3(grid), dim3(kBlock), 0, st, c); break;
+                case 1: hipLaunchKernelGGL((k_bwd_pull_w<1, true, false>), dim3(grid), dim3(kBlock), 0, st, c); break;
+                default: hipLaunchKernelGGL((k_bwd_pull_w<2, true, false>), dim3(grid), dim3(kBlock), 0, st, c); break;
             }
             const int mgrid = std::max(nblocks((size_t)c.nhubs * nbk, kWavesPerBlock, 0x7fffffff),
                                        nblocks((size_t)nw, kBlock, 1024));
