@@ -78,7 +78,8 @@ def make_sources(g, spec):
     return gg.pick_sources(g, spec["n_sources"], spec["source_seed"])
 
 
-KERNEL_SOURCES = ("pull.h", "products.h", "kernels.hip", "monoid.hip", "mfbc_internal.h")
+KERNEL_SOURCES = ("pull.h", "products.h", "kernels.hip", "monoid.hip", "bits.hip", "quad.hip",
+                  "core.hip", "mfbc_internal.h")
 
 
 def kernel_sha(csrc=None):
@@ -398,6 +399,8 @@ def run_fixpoint(args, spec):
           file=sys.stderr, flush=True)
     ms, alg, launches = tot["fwd_pull_ms"], tot["fwd_alg_bytes"], tot["fwd_pull_launches"]
     achieved = alg / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
+    # hop levels run on bit masks, distances in 16 bits, the rest in 32
+    kernel = {"bfs": "k_bits_pull", "sssp": "k_quad_pull"}.get(spec["op"], "k_mono_pull")
     line = {
         "metric": f"{spec['op'].upper()} TEPS (sources x edges / s) at 1 GPU",
         "value": src.size * g.m / (elapsed / args.steps), "unit": "TEPS", "n_gpus": 1,
@@ -407,9 +410,9 @@ def run_fixpoint(args, spec):
         "data": "synthetic",
         "config": {"workload": args.workload, "graph": g.name, "n": g.n, "m": g.m,
                    "n_sources": int(src.size), "batch": batch, "op": spec["op"]},
-        "roofline": {"bound": "hbm", "kernel": "k_mono_pull", "achieved": round(achieved, 2),
+        "roofline": {"bound": "hbm", "kernel": kernel, "achieved": round(achieved, 2),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": stored_traffic(args.workload, "k_mono_pull"),
+                     "traffic": stored_traffic(args.workload, kernel),
                      "launches": int(launches), "avg_launch_us": round(ms / max(launches, 1) * 1e3, 2),
                      "alg_bytes_per_launch": round(alg / max(launches, 1)),
                      "copy_gbs": copy_rate_gbs(torch)},

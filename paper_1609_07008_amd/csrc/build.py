@@ -17,7 +17,7 @@ PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmfbc.so")
-SOURCES = ["kernels.hip", "batched.hip", "server.hip", "monoid.hip", "bits.hip", "core.hip", "graph.cpp", "order.cpp",
+SOURCES = ["kernels.hip", "batched.hip", "server.hip", "monoid.hip", "bits.hip", "quad.hip", "core.hip", "graph.cpp", "order.cpp",
            "mfbc_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

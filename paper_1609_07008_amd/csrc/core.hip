@@ -80,6 +80,11 @@ __global__ void k_core_zero(int32_t *cnt, int n) {
     if (i < n) cnt[i] = 0;
 }
 
+__global__ void k_core_hub(const int32_t *bound, int n, int32_t *out) {
+    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v < n) out[v] = bound[(size_t)v * kWave];
+}
+
 // One wave per row: the kept arcs in their order, to the row's place in `out`.
 __global__ __launch_bounds__(kBlock) void k_core_compact(int n, Csr c, const uint8_t *keep, Csr out) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -160,6 +165,10 @@ void launch_core_mark(const Csr &c, const Plan &pl, const int32_t *near, const i
 
 void launch_core_zero(int32_t *cnt, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_core_zero, dim3((n + 255) / 256), dim3(256), 0, s, cnt, n);
+}
+
+void launch_core_hub(const int32_t *bound, int n, int32_t *out, hipStream_t s) {
+    hipLaunchKernelGGL(k_core_hub, dim3((n + 255) / 256), dim3(256), 0, s, bound, n, out);
 }
 
 void launch_core_compact(int32_t n, const Csr &c, const uint8_t *keep, const Csr &out, hipStream_t s) {

@@ -140,6 +140,7 @@ size_t ws_bytes(const mfbc_graph *g, int ncg, bool admit) {
 void free_workspace(Workspace &ws) {
     if (!ws.external) ws_arrays(nullptr, ws, 0, [](auto *&p, size_t) { dfree(p); });
     dfree(ws.trace_relax);
+    dfree(ws.quad_base);
     ws = Workspace{};
 }
 
@@ -202,6 +203,20 @@ int ensure_workspace(mfbc_graph *g, int ncg) {
     }
     ws.ncg = ncg;
     ws.flags = (int32_t *)(ws.counters + kRingWords);
+    return MFBC_OK;
+}
+
+// Grow the workspace's bounds for the 16-bit products of a batch.
+int ensure_quad(mfbc_graph *g, int ncg) {
+    Workspace &ws = g->ws;
+    if (ws.quad_ncg < ncg) {
+        dfree(ws.quad_base);
+        ws.quad_ncg = 0;
+        const int rc = dalloc(&ws.quad_base, quad_bound_bytes(g, ncg, nullptr, nullptr));
+        if (rc) return rc;
+        ws.quad_ncg = ncg;
+    }
+    (void)quad_bound_bytes(g, ncg, &ws.quad, ws.quad_base);
     return MFBC_OK;
 }
 
@@ -345,6 +360,54 @@ int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d
     return MFBC_OK;
 }
 
+// Algorithm 1, or the (min, a + w) fixpoint without multiplicities, in 16 bits
+// on every arc.  *fits becomes false, with nothing written, if the frontier
+// outlives the products whose entries fit.
+int run_quad(mfbc_graph *g, bool count, int ncg, int nb, const int32_t *d_sources, int32_t *products, bool *fits,
+             hipStream_t s) {
+    const int most = quad_products(g, count);
+    *fits = most > 0;
+    if (!*fits) return MFBC_OK;
+    int rc = ensure_quad(g, ncg);
+    if (rc) return rc;
+    launch_quad_init(g, count, ncg, nb, d_sources, s);
+    const double arc_bytes = g->weighted ? 8.0 : 4.0;
+    mfbc_stats &st = g->stats;
+    int64_t prev = nb;
+    int j = 0, last = 0;
+    while (!last) {
+        if (j + kWindow > most) {
+            *fits = false;
+            g->stats = mfbc_stats{};
+            return MFBC_OK;
+        }
+        for (int i = 0; i < kWindow; i++) launch_quad_product(g, count, ncg, j + 1 + i, s, window_events(g, i, true));
+        if ((rc = read_ring(g, s))) return rc;
+        if (j == 0 && ring_flag(g, 2)) return bad_source(g, d_sources, nb, s);
+        for (int i = 0; i < kWindow; i++) {
+            const int jj = j + 1 + i;
+            st.fwd_pull_launches++;
+            add_times(g, i, &st.fwd_pull_ms, &st.fwd_merge_ms, true);
+            if (last) continue;
+            const Counts c = ring_counts(g, jj);
+            st.fwd_entries += c.produced;
+            st.fwd_outputs += c.outputs;
+            st.fwd_active_vertices += c.active_vertices;
+            st.fwd_active_arcs += c.active_arcs;
+            st.fwd_alg_bytes += 8.0 * c.active_vertices + arc_bytes * c.active_arcs +
+                                (count ? 12.0 * (double)(prev + c.outputs + c.produced)
+                                       : 4.0 * (double)(prev + c.outputs) + 8.0 * (double)c.produced);
+            prev = c.produced;
+            if (c.produced == 0) last = jj;
+        }
+        j += kWindow;
+    }
+    if (count && ring_flag(g, 0)) return fail(MFBC_EOVERFLOW, "a shortest-path count overflowed binary64");
+    st.fwd_products = last;
+    if (products) *products = last;
+    return MFBC_OK;
+}
+
 // Algorithm 2 on the batch whose T is in the workspace: the counting
 // product (window position 0 of the first window), then backward products
 // in windows as in run_forward, until one produces no frontier entry.
@@ -442,6 +505,15 @@ int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d
                                    s));
     }
     g->stats = mfbc_stats{};
+    bool fits = false;
+    if (!trace && (rc = run_quad(g, true, ncg, nb, d_sources, h_products, &fits, s))) return rc;
+    if (fits) {
+        g->stats.batches = 1;
+        launch_quad_rows(g, true, ncg, nb, d_dist, d_sigma, s);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(s));
+        return MFBC_OK;
+    }
     if ((rc = run_forward(g, g->full, ncg, nb, d_sources, trace, d_rows, h_nnz, h_relax, max_products, h_products, s)))
         return rc;
     g->stats.batches = 1;
@@ -683,6 +755,8 @@ int build_core(mfbc_graph *g, hipStream_t s) {
     } else {
         to = from;
     }
+    // kept as the columns' offsets in the bounds of quad.hip, core or not
+    if (!dalloc(&g->hub_dist, n)) launch_core_hub(to, g->n, g->hub_dist, s);
     View c;
     rc = core_csr(g, g->full.out, g->full.plan_out, to, from, keep, cnt, c.out, g->h_core_rp_out, s);
     if (!rc && c.out.rp && g->directed)
@@ -733,6 +807,7 @@ void free_graph_memory(mfbc_graph *g) {
     g->has_core = false;
     free_view(g->full);
     dfree(g->perm);
+    dfree(g->hub_dist);
     g->h_perm.clear();
     if (g->h_ctr) (void)hipHostFree(g->h_ctr);
     g->h_ctr = nullptr;
@@ -1062,6 +1137,19 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
     if ((rc = ensure_workspace(g, ncg))) return rc;
     g->stats = mfbc_stats{};
     const bool bits = bits_fit(g, op);
+    if (op == MFBC_OP_SSSP && !bits) {
+        bool fits = false;
+        int32_t products = 0;
+        if ((rc = run_quad(g, false, ncg, nb, d_sources, &products, &fits, s))) return rc;
+        if (fits) {
+            g->stats.batches = 1;
+            if (h_products) *h_products = products;
+            launch_quad_rows(g, false, ncg, nb, (int32_t *)d_out, nullptr, s);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(hipStreamSynchronize(s));
+            return MFBC_OK;
+        }
+    }
     if (bits) launch_bits_init(g, ncg, nb, d_sources, s);
     else launch_mono_init(g, op, ncg, nb, d_sources, s);
     int planes = 0;              // planes of the product number cleared so far

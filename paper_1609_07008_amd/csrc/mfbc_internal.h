@@ -86,6 +86,15 @@ struct View {
     int64_t arcs = 0;
 };
 
+// Bounds of the 16-bit products (quad.hip), one row per vertex and wave of groups.
+struct QuadBounds {
+    uint16_t *lo[3] = {};              // of F_j in lo[j % 3]
+    size_t lo_words = 0;               // 32-bit words of each
+    int32_t *hi = nullptr;
+    int32_t *off = nullptr;            // offset of each column
+    unsigned long long *live = nullptr;  // columns with entries in F_j, [j % 3][ncg]
+};
+
 struct Workspace {
     int ncg = 0;                       // capacity in column groups
     int32_t *tdist = nullptr;          // T.w      [cg][n][64]
@@ -107,6 +116,9 @@ struct Workspace {
                                        // (read by the paired counting product)
     unsigned long long *trace_relax = nullptr;  // trace: relaxations per product
     int trace_len = 0;
+    char *quad_base = nullptr;         // memory behind `quad`, for batches of up to quad_ncg groups
+    int quad_ncg = 0;
+    QuadBounds quad;
     bool external = false;             // carved from caller-provided memory: never freed here
 };
 
@@ -125,6 +137,7 @@ struct mfbc_graph {
     // distances and path counts; the same arrays as `full` unless has_core.
     mfbc::View full, core;
     bool has_core = false;
+    int32_t *hub_dist = nullptr;  // upper bounds of the distances to the vertex of highest degree
     int64_t scratch_slots = 0;  // hub partial slots mfbc_bc_noalloc admits calls by
     int mb = 1;             // inline multiplicity bits of a packed frontier tuple
     mfbc::TaskParams params;
@@ -227,6 +240,16 @@ void launch_bits_planes(mfbc_graph *g, int ncg, int from, int to, hipStream_t s)
 void launch_bits_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev);
 void launch_bits_export(mfbc_graph *g, int op, int ncg, int nb, int planes, void *out, hipStream_t s);
 
+// ---- products in 16 bits (quad.hip) ----
+// Products a call may run before its entries could exceed 16 bits (0: the
+// graph's weights are too wide); count: with multiplicities.
+int quad_products(const mfbc_graph *g, bool count);
+// Bytes of the bounds of ncg groups; places them at `base` if given.
+size_t quad_bound_bytes(const mfbc_graph *g, int ncg, QuadBounds *qb, char *base);
+void launch_quad_init(mfbc_graph *g, bool count, int ncg, int nb, const int32_t *d_sources, hipStream_t s);
+void launch_quad_product(mfbc_graph *g, bool count, int ncg, int j, hipStream_t s, hipEvent_t *ev);
+void launch_quad_rows(mfbc_graph *g, bool count, int ncg, int nb, int32_t *dist, double *sigma, hipStream_t s);
+
 // ---- shortest-path core (core.hip) ----
 constexpr int kLandmarks = kWave;        // one per lane
 bool core_worth_trying(const mfbc_graph *g);
@@ -236,6 +259,8 @@ TaskParams core_params(int32_t n, int64_t arcs, int64_t full_arcs);   // default
 void launch_core_mark(const Csr &c, const Plan &pl, const int32_t *near, const int32_t *far, uint8_t *keep,
                       int32_t *cnt, hipStream_t s);
 void launch_core_zero(int32_t *cnt, int n, hipStream_t s);
+// out[v] = bound[v][0] (the landmark of highest degree)
+void launch_core_hub(const int32_t *bound, int n, int32_t *out, hipStream_t s);
 // The kept arcs of every row, in order, at rows rp2.
 void launch_core_compact(int32_t n, const Csr &c, const uint8_t *keep, const Csr &out, hipStream_t s);
 // Hub partial slots the workspace must hold for any plan of the graph.
