@@ -32,6 +32,7 @@ struct GraphDesc {
     ArcSrc arcs_in, arcs_out;
     const Task *tasks_in, *tasks_out;
     const Hub *hubs_in, *hubs_out;
+    const uint8_t *owner_out;  // row of each out-arc within its task
     const int32_t *perm;       // caller id -> device id (nullable)
 };
 
@@ -232,6 +233,7 @@ void k_bc_many(ManyArgs m) {
         c.nwords = nw;
         c.rp = gd.rp_out;
         c.arcs = gd.arcs_out;
+        c.owner = gd.owner_out;
         c.src = sl.src;
         c.tdist = sl.tdist;
         c.tsig = sl.tsig;
@@ -430,6 +432,7 @@ int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const in
         d.tasks_out = g->core.plan_out.tasks;
         d.hubs_in = g->core.plan_in.hubs;
         d.hubs_out = g->core.plan_out.hubs;
+        d.owner_out = g->core.plan_out.owner;
         d.perm = g->perm;
         n_max = std::max(n_max, g->n);
         slots_max = std::max(slots_max, max_slots(g));

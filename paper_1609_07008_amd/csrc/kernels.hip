@@ -460,6 +460,7 @@ static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
     a.k = k;
     a.rp = vw.out.rp;
     a.arcs = arc_src(vw.out);
+    a.owner = vw.plan_out.owner;
     a.src = ws.src;
     a.tdist = ws.tdist;
     a.tsig = ws.tsig;

@@ -16,6 +16,7 @@
 #include <string>
 #include <thread>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "mfbc_internal.h"
@@ -588,18 +589,17 @@ int upload_csr(int32_t n, int64_t arcs, const int64_t *rp, const int32_t *col, c
 }
 
 // The plans of one view (one for both orientations of an undirected graph).
-// owners: with the in-arcs' rows (Plan::owner).
 int plan_view(int32_t n, bool directed, const std::vector<int64_t> &rp_out, const std::vector<int64_t> &rp_in,
-              const TaskParams &p, View &v, bool owners) {
+              const TaskParams &p, View &v) {
     if (!directed) v.plan_in = Plan{};
     int rc = upload_plan(n, rp_out.data(), p, v.plan_out);
     if (!rc && directed) rc = upload_plan(n, rp_in.data(), p, v.plan_in);
-    Plan &pi = directed ? v.plan_in : v.plan_out;
-    if (!rc && owners && !(rc = dalloc(&pi.owner, (size_t)rp_in.back()))) {
-        launch_plan_owner(v.in, pi, nullptr);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipStreamSynchronize(nullptr));
+    for (auto [csr, plan] : {std::pair<const Csr *, Plan *>{&v.out, &v.plan_out}, {&v.in, &v.plan_in}}) {
+        if (rc || (plan == &v.plan_in && !directed)) break;
+        if (!(rc = dalloc(&plan->owner, (size_t)rp_out.back()))) launch_plan_owner(*csr, *plan, nullptr);
     }
+    if (!rc) HIP_TRY(hipGetLastError());
+    if (!rc) HIP_TRY(hipStreamSynchronize(nullptr));
     if (!directed) v.plan_in = v.plan_out;
     return rc;
 }
@@ -630,13 +630,13 @@ int plan_views(mfbc_graph *g, const TaskParams &knobs) {
         g->scratch_slots = std::max(g->scratch_slots, t);
         if (!g->directed) break;
     }
-    const int rc = plan_view(g->n, g->directed, g->h_rp_out, g->h_rp_in, g->params, g->full, true);
+    const int rc = plan_view(g->n, g->directed, g->h_rp_out, g->h_rp_in, g->params, g->full);
     if (!g->has_core) {
         g->core = g->full;       // also after a failure: no stale pointers
         return rc;
     }
     if (rc) return rc;
-    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, params(true), g->core, false);
+    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, params(true), g->core);
 }
 
 // One block of device memory, handed out in parts and freed at the end of
@@ -772,7 +772,7 @@ int build_core(mfbc_graph *g, hipStream_t s) {
     c.arcs = g->h_core_rp_out.back();
     g->core = c;
     g->has_core = true;
-    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs, g->full.arcs), g->core, false);
+    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs, g->full.arcs), g->core);
 }
 
 // Release a lane view: its workspace, counters and events (the device graph

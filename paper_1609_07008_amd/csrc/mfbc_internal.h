@@ -65,7 +65,7 @@ struct TaskParams {
 struct Plan {
     Task *tasks = nullptr;   // device
     Hub *hubs = nullptr;     // device
-    uint8_t *owner = nullptr;  // device: row of each arc within its task (in-arcs of the full view)
+    uint8_t *owner = nullptr;  // device: row of each arc within its task
     int32_t ntasks = 0, nhubs = 0, nslots = 0;
 };
 

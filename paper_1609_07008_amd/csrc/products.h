@@ -606,6 +606,7 @@ struct BwdArgs {
     int ntasks, nhubs, nslots, ncg, n, k, nwords;
     const int64_t *rp;         // out-arcs
     ArcSrc arcs;
+    const uint8_t *owner;      // row of each arc within its task
     const int32_t *src;        // column -> source vertex (-1 = padding)
     const int32_t *tdist;      // tau
     const double *tsig;        // sigma
@@ -955,8 +956,8 @@ __device__ __forceinline__ uint64_t bwd_finalize(const BwdArgs &a, size_t cgv, i
 // shortest path from s, the AND of two lane masks (the arc's tag) -- and
 // (+) sums the frontier values q(s, y) of the counted arcs with their number.
 // No distance is read, every counted arc belongs to a pending owner, and q is
-// gathered only for counted lanes.  Every row of a run is visited: rows that
-// count nothing clear their frontier lane masks.  W = 1: one column group;
+// gathered only for counted lanes.  A row that counts nothing keeps old lane
+// masks: they are read only behind its activity bit, which it does not set.  W = 1: one column group;
 // W = 2: a pair of groups (paired layout: lane masks [q][n][2], one activity
 // bitmap per pair, one pass over the arcs and one 16-byte mask gather for
 // both); a padding group (odd group count) has no state and counts nothing.
@@ -966,7 +967,6 @@ struct BwdPull : PullDefaults {
     static constexpr int AM = AM_;
     static constexpr int U = U_;
     static constexpr int H = 4;
-    static constexpr bool kEveryRow = true;
     struct Tag {
         uint64_t live[W];      // lanes for which the arc counts, per group
     };
@@ -1087,13 +1087,6 @@ struct BwdPull : PullDefaults {
         }
         return bb;
     }
-    __device__ __forceinline__ void idle(int v) const {
-        if constexpr (W == 1) {
-            if (lane == 0) a.fbits_n[cgv(0) + (size_t)v] = 0ull;
-        } else {
-            if (lane < 2) a.fbits_n[((size_t)q * n + (size_t)v) * 2 + lane] = 0ull;
-        }
-    }
     __device__ __forceinline__ size_t slot(int c, int part) const {
         return ((size_t)(cg0 + c) * a.nslots + part) * kWave + lane;
     }
@@ -1139,7 +1132,7 @@ template <int AM>
 __device__ __forceinline__ void bwd_task(const BwdArgs &a, int cg, int t, unsigned long long &produced,
                                          unsigned long long &outs) {
     BwdPull<AM, 1> p(a, cg, produced, outs);
-    pull_task_owner(p, a.tasks + t, a.rp, a.arcs);
+    pull_task_owner(p, a.tasks + t, a.arcs, a.owner);
     p.flush();
 }
 
@@ -1155,7 +1148,7 @@ template <int AM, bool CM>
 __device__ __forceinline__ void bwd_task_w(const BwdArgs &a, int q, int t, unsigned long long &produced,
                                            unsigned long long &outs) {
     BwdPull<AM, 2, CM> p(a, q, produced, outs);
-    pull_task_owner(p, a.tasks + t, a.rp, a.arcs);
+    pull_task_owner(p, a.tasks + t, a.arcs, a.owner);
     p.flush();
 }
 

@@ -33,12 +33,8 @@
 //                         lanes in the next frontier (any group)
 //   p.store(part, acc), p.load(slot), p.merge(acc, part), p.finish_hub(v, acc)
 //                         partials of a split (hub) row and their combination
-//   P::kEveryRow, p.idle(v)  when set, every row of a run without a
-//                         candidate is visited too (MFBr clears its frontier
-//                         lane masks there)
 //
-// PullDefaults supplies the optional members (no tag, nothing masked, no
-// batch hook, only rows with candidates visited).
+// PullDefaults supplies the optional members (no tag, nothing masked).
 //
 // The task's arcs are read 64 at a time (the next 64 in flight while the
 // current ones are processed); the arcs whose source is active are taken U
@@ -130,10 +126,8 @@ __device__ __forceinline__ void decode_arc(const ArcSrc &s, uint32_t r0, uint32_
 
 struct PullDefaults {
     struct Tag {};
-    static constexpr bool kEveryRow = false;
     __device__ __forceinline__ Tag tag(int, int64_t) const { return Tag{}; }
     __device__ __forceinline__ bool live(const Tag &) const { return true; }
-    __device__ __forceinline__ void idle(int) const {}
 };
 
 template <class P>
@@ -213,9 +207,6 @@ __device__ __forceinline__ void pull_task(P &p, const Task *tp, const int64_t *r
                 if (ow[k] >= 0) {
                     if (ow[k] != cur) {
                         if (cur >= 0 && hub < 0 && p.finish(v0 + cur, acc, own)) run_act |= 1ull << cur;
-                        if constexpr (P::kEveryRow)
-                            if (hub < 0)
-                                for (int o = cur + 1; o < ow[k]; o++) p.idle(v0 + o);
                         cur = ow[k];
                         p.reset(acc);
                         own = on[k];
@@ -228,56 +219,41 @@ __device__ __forceinline__ void pull_task(P &p, const Task *tp, const int64_t *r
     }
     if (hub < 0) {
         if (cur >= 0 && p.finish(v0 + cur, acc, own)) run_act |= 1ull << cur;
-        if constexpr (P::kEveryRow)
-            for (int o = cur + 1; o < v1 - v0; o++) p.idle(v0 + o);
         if (lane == 0 && run_act) or_run_bits(p.bits_n, v0, run_act);
     } else {
         p.store(part, acc);
     }
 }
 
-// The same product in owner order: the task's rows are taken one after
-// another and the batch of U active arcs is drawn from the current row only,
-// the owner's T entries loaded with the batch's gathers.  Fewer registers
-// than batches across owners (the batch needs no owner index per arc), for
-// products whose rows are finished often without a candidate (P::kEveryRow)
-// and whose per-arc masks already skip the arcs that feed no lane.
-__device__ __forceinline__ uint64_t owner_mask(int64_t e, int64_t vend) {
-    const int64_t lim = vend - e;
-    return lim >= kWave ? ~0ull : (lim <= 0 ? 0ull : ((1ull << lim) - 1ull));
-}
-
+// The same product in owner order: a batch of U active arcs is drawn from one
+// row only, the owner's T entries loaded with the first batch's gathers.
+// Fewer registers than batches across owners (the batch needs no owner index
+// per arc), for products whose per-arc masks already skip the arcs that feed
+// no lane.  The row of an arc comes from the plan's byte per arc (`owner`), so
+// rows without an active arc cost nothing; walking the row pointers instead,
+// one dependent scalar load per row, took 80 us a product on the core of R-MAT
+// scale 20 when almost nothing was active (27 here).
 template <class P>
-__device__ __forceinline__ void pull_task_owner(P &p, const Task *tp, const int64_t *rp, const ArcSrc &arcs) {
+__device__ __forceinline__ void pull_task_owner(P &p, const Task *tp, const ArcSrc &arcs, const uint8_t *owner) {
     constexpr int U = P::U;
     constexpr int AM = P::AM;
     const int lane = threadIdx.x & (kWave - 1);
-    const int v0 = uni(tp->v0), v1 = uni(tp->v1), hub = uni(tp->hub), part = uni(tp->part);
+    const int v0 = uni(tp->v0), hub = uni(tp->hub), part = uni(tp->part);
     const int64_t e0 = uni64(tp->e0), e1 = uni64(tp->e1);
     const uint32_t *Ab = p.bits;
-    int x = v0;
-    int64_t vend = hub >= 0 ? e1 : rp[v0 + 1];
-    bool loaded = false;
+    int cur = -1;            // row (offset from v0) of the open reduction
     typename P::Acc acc;
     typename P::Own own = p.none();
     p.reset(acc);
     uint64_t run_act = 0;
-    auto close = [&]() {
-        if (loaded) {
-            if (p.finish(x, acc, own)) run_act |= 1ull << (x - v0);
-        } else if constexpr (P::kEveryRow) {
-            p.idle(x);
-        }
-        loaded = false;
-        p.reset(acc);
-    };
     for (int64_t e = e0; e < e1; e += kWave) {
         const int64_t my = e + lane;
-        int y = 0, wt = 1;
+        int y = 0, wt = 1, o = -1;
         typename P::Tag tg{};
         bool act = false;
         if (my < e1) {
             load_arc<AM>(arcs, my, y, wt);
+            o = owner[my];
             if ((Ab[y >> 5] >> (y & 31)) & 1u) {
                 tg = p.tag(y, my);
                 act = p.live(tg);
@@ -285,45 +261,39 @@ __device__ __forceinline__ void pull_task_owner(P &p, const Task *tp, const int6
         }
         uint64_t am = ballot(act);
         while (am) {
-            const int j0 = __ffsll((unsigned long long)am) - 1;
-            if (hub < 0) {
-                while (e + j0 >= vend) {
-                    close();
-                    ++x;
-                    vend = rp[x + 1];
-                }
+            const int x = rdlane(o, __builtin_ctzll(am));
+            uint64_t cand = am & ballot(o == x);
+            am &= ~cand;
+            if (x != cur) {
+                if (cur >= 0 && hub < 0 && p.finish(v0 + cur, acc, own)) run_act |= 1ull << cur;
+                cur = x;
+                p.reset(acc);
+                own = p.own(v0, x);
             }
-            uint64_t cand = am & owner_mask(e, vend);
-            int wk[U], uk[U];
-            typename P::Row rk[U];
+            while (cand) {
+                int wk[U], uk[U];
+                typename P::Row rk[U];
 #pragma unroll
-            for (int k = 0; k < U; k++) {
-                rk[k] = p.absent();
-                uk[k] = 0;
-                wk[k] = 0;
-                if (cand) {
-                    const int j = __ffsll((unsigned long long)cand) - 1;
-                    cand &= cand - 1;
-                    am &= ~(1ull << j);
-                    uk[k] = rdlane(y, j);
-                    wk[k] = AM ? rdlane(wt, j) : 1;
-                    rk[k] = p.gather(uk[k], tg, j);
+                for (int k = 0; k < U; k++) {
+                    rk[k] = p.absent();
+                    uk[k] = 0;
+                    wk[k] = 0;
+                    if (cand) {
+                        const int j = __builtin_ctzll(cand);
+                        cand &= cand - 1;
+                        uk[k] = rdlane(y, j);
+                        wk[k] = AM ? rdlane(wt, j) : 1;
+                        rk[k] = p.gather(uk[k], tg, j);
+                    }
                 }
-            }
-            if (!loaded) {
-                own = p.own(v0, x - v0);
-                loaded = true;
-            }
-            p.batch(rk, uk);
+                p.batch(rk, uk);
 #pragma unroll
-            for (int k = 0; k < U; k++) p.fold(acc, rk[k], wk[k], uk[k]);
+                for (int k = 0; k < U; k++) p.fold(acc, rk[k], wk[k], uk[k]);
+            }
         }
     }
     if (hub < 0) {
-        while (x < v1) {
-            close();
-            ++x;
-        }
+        if (cur >= 0 && p.finish(v0 + cur, acc, own)) run_act |= 1ull << cur;
         if (lane == 0 && run_act) or_run_bits(p.bits_n, v0, run_act);
     } else {
         p.store(part, acc);

@@ -586,6 +586,7 @@ int mfbc_server_step_launch(mfbc_server *s, void *hip_stream) {
     c.nwords = nw;
     c.rp = g->core.out.rp;
     c.arcs = srv_arc_src(g->core.out);
+    c.owner = g->core.plan_out.owner;
     c.src = s->src;
     c.tdist = s->tdist;
     c.tsig = s->tsig;
