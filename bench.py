@@ -97,6 +97,16 @@ def kernel_sha(csrc=None):
     return h.hexdigest()[:16]
 
 
+def forward_kernel(g):
+    """The kernel of a centrality call's forward products: 16-bit entries where
+    the products that fit (weight and two bits of multiplicity) are 40 or more
+    and, on a graph of short rows, cover its longest possible path."""
+    fits = ((1 << 14) - 2) // g.max_weight - 1
+    fits -= fits % 8
+    short_rows = float((g.degree.astype(float) ** 2).sum()) < 16.0 * g.arcs
+    return "k_fwd_pull" if fits < 40 or (short_rows and g.n > fits) else "k_quad_pull"
+
+
 def stored_traffic(workload, kernel):
     """HBM bytes per launch from committed rocprofv3 counter runs, if still valid."""
     path = os.path.join(ROOT, "profiles", f"traffic_{kernel}_{workload}.json")
@@ -548,8 +558,9 @@ def main():
     if census:
         print(f"[bench] relaxations per step: {census}", file=sys.stderr, flush=True)
 
+    fwd = forward_kernel(g)
     kernels = {
-        "k_fwd_pull": (tot["fwd_pull_ms"], tot["fwd_alg_bytes"], tot["fwd_pull_launches"]),
+        fwd: (tot["fwd_pull_ms"], tot["fwd_alg_bytes"], tot["fwd_pull_launches"]),
         "k_bwd_pull": (tot["bwd_pull_ms"], tot["bwd_alg_bytes"], tot["bwd_pull_launches"]),
         "k_bwd_count": (tot["count_ms"], tot["count_alg_bytes"], tot["count_launches"]),
     }
@@ -557,7 +568,7 @@ def main():
     ms, alg, launches = kernels[dom]
     achieved = alg / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
     traffic = stored_traffic(args.workload, dom)
-    # batches of two or more column groups run the forward product two groups per wave
+    # batches of two or more column groups run the 32-bit forward product two groups per wave
     label = "k_fwd_pull_w" if dom == "k_fwd_pull" and min(batch, src.size) > 64 else dom
     avg_us = ms / max(launches, 1) * 1e3
     roofline = {"bound": "hbm", "kernel": label, "achieved": round(achieved, 2),

@@ -117,13 +117,16 @@ __global__ __launch_bounds__(kBlock) void k_core_compact(int n, Csr c, const uin
 // on weights 1..100 / 1..255: uniform graphs of degree 12 (mean 13) 85%, 20
 // 56%, 40 31%; R-MAT graphs of edge factor 2 (mean 70) 34%, 4 22%, 16 8%.
 bool core_worth_trying(const mfbc_graph *g) {
-    if (!g->weighted || g->maxw <= 1 || g->arcs < 2048) return false;
+    return g->weighted && g->maxw > 1 && g->arcs >= 2048 && !g->sparse;
+}
+
+bool sparse_rows(const mfbc_graph *g) {
     double sq = 0.0;
     for (int32_t v = 0; v < g->n; v++) {
         const double d = (double)(g->h_rp_out[(size_t)v + 1] - g->h_rp_out[(size_t)v]);
         sq += d * d;
     }
-    return sq >= 16.0 * (double)g->arcs;
+    return sq < 16.0 * (double)g->arcs;
 }
 
 // A core's rows are short (2.5 arcs on average at R-MAT scale 20), so a run

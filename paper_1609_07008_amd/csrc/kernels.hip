@@ -499,7 +499,7 @@ static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
     return a;
 }
 
-hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t s, hipEvent_t *ev) {
+hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, bool tau16, hipStream_t s, hipEvent_t *ev) {
     Workspace &ws = g->ws;
     // the counting product writes B_0 into buffer 0: clear the bitmaps, the
     // counters and the flag of the compact tau first
@@ -511,7 +511,15 @@ hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t 
     if (e != hipSuccess) return e;
     BwdArgs a = bwd_args(g, vw, ncg, 0);
     if (ev) (void)hipEventRecord(ev[0], s);
-    if (ncg >= 2) {
+    if (tau16) {
+        a.tau2 = (const uint32_t *)ws.tdist;
+        const int grid = blocks_for((size_t)a.ntasks * ((ncg + 1) / 2), kWavesPerBlock, 0x7fffffff);
+        switch (arc_mode(vw.out)) {
+            case 0: hipLaunchKernelGGL((k_bwd_count_w<0, false, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
+            case 1: hipLaunchKernelGGL((k_bwd_count_w<1, false, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
+            default: hipLaunchKernelGGL((k_bwd_count_w<2, false, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        }
+    } else if (ncg >= 2) {
         // pairs of groups: tau interleaved per pair, then one wave per (pair, task)
         const int npairs = (ncg + 1) / 2;
         const size_t plane = (size_t)g->n * kWave;
@@ -533,6 +541,7 @@ hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t 
                 break;
         }
     } else {
+        a.tau_full = nullptr;        // one group: tau from tdist
         const size_t waves = (size_t)a.ntasks * ncg;
         const int grid = blocks_for(waves, kWavesPerBlock, 0x7fffffff);
         switch (arc_mode(vw.out)) {

@@ -207,17 +207,21 @@ int ensure_workspace(mfbc_graph *g, int ncg) {
     return MFBC_OK;
 }
 
-// Grow the workspace's bounds for the 16-bit products of a batch.
-int ensure_quad(mfbc_graph *g, int ncg) {
+// Set up the workspace for 16-bit products with `words` 32-bit words per lane;
+// with bounds (on every arc) the memory behind them is grown to the batch.
+int ensure_quad(mfbc_graph *g, int ncg, int words, bool bounds) {
     Workspace &ws = g->ws;
+    ws.quad = QuadBounds{};
+    ws.quad.words = words;
+    if (!bounds) return MFBC_OK;
     if (ws.quad_ncg < ncg) {
         dfree(ws.quad_base);
         ws.quad_ncg = 0;
-        const int rc = dalloc(&ws.quad_base, quad_bound_bytes(g, ncg, nullptr, nullptr));
+        const int rc = dalloc(&ws.quad_base, quad_bound_bytes(g, ncg, 1, nullptr, nullptr));
         if (rc) return rc;
         ws.quad_ncg = ncg;
     }
-    (void)quad_bound_bytes(g, ncg, &ws.quad, ws.quad_base);
+    (void)quad_bound_bytes(g, ncg, words, &ws.quad, ws.quad_base);
     return MFBC_OK;
 }
 
@@ -361,30 +365,41 @@ int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d
     return MFBC_OK;
 }
 
+// Below this many arcs mfbc_forward and the fixpoint stay in 32 bits: a task's
+// fixed cost (bounds, live columns) shows there.  Distances and path counts of
+// 256 sources, ms in 32 / 16 bits: uniform n = 10,000 of degree 10 1.13 / 1.51,
+// weighted R-MAT scale 12 0.77 / 0.93, 14 1.50 / 1.47, 16 3.69 / 2.12, 18 (200
+// sources) 10.5 / 5.3.
+constexpr int64_t kQuadArcs = 1 << 18;
+
 // Algorithm 1, or the (min, a + w) fixpoint without multiplicities, in 16 bits
-// on every arc.  *fits becomes false, with nothing written, if the frontier
+// (d_sources nullable: already in ws.src): on every arc with bounds, on the
+// core without.  *fits becomes false, with nothing written, if the frontier
 // outlives the products whose entries fit.
-int run_quad(mfbc_graph *g, bool count, int ncg, int nb, const int32_t *d_sources, int32_t *products, bool *fits,
-             hipStream_t s) {
-    const int most = quad_products(g, count);
+int run_quad(mfbc_graph *g, bool core, bool count, int ncg, int nb, const int32_t *d_sources, int32_t *products,
+             bool *fits, hipStream_t s) {
+    const View &vw = core ? g->core : g->full;
+    const int words = core || ncg <= 2 ? 1 : 2;
+    const int most = core || g->arcs >= kQuadArcs ? quad_products(g, count) : 0;
     *fits = most > 0;
     if (!*fits) return MFBC_OK;
-    int rc = ensure_quad(g, ncg);
+    int rc = ensure_quad(g, ncg, words, !core);
     if (rc) return rc;
-    launch_quad_init(g, count, ncg, nb, d_sources, s);
+    launch_quad_init(g, vw, count, ncg, nb, d_sources, s);
     const double arc_bytes = g->weighted ? 8.0 : 4.0;
     mfbc_stats &st = g->stats;
+    const mfbc_stats before = st;
     int64_t prev = nb;
     int j = 0, last = 0;
     while (!last) {
         if (j + kWindow > most) {
             *fits = false;
-            g->stats = mfbc_stats{};
+            g->stats = before;
             return MFBC_OK;
         }
-        for (int i = 0; i < kWindow; i++) launch_quad_product(g, count, ncg, j + 1 + i, s, window_events(g, i, true));
+        for (int i = 0; i < kWindow; i++) launch_quad_product(g, vw, count, ncg, j + 1 + i, s, window_events(g, i, true));
         if ((rc = read_ring(g, s))) return rc;
-        if (j == 0 && ring_flag(g, 2)) return bad_source(g, d_sources, nb, s);
+        if (j == 0 && d_sources && ring_flag(g, 2)) return bad_source(g, d_sources, nb, s);
         for (int i = 0; i < kWindow; i++) {
             const int jj = j + 1 + i;
             st.fwd_pull_launches++;
@@ -404,7 +419,7 @@ int run_quad(mfbc_graph *g, bool count, int ncg, int nb, const int32_t *d_source
         j += kWindow;
     }
     if (count && ring_flag(g, 0)) return fail(MFBC_EOVERFLOW, "a shortest-path count overflowed binary64");
-    st.fwd_products = last;
+    st.fwd_products += last;
     if (products) *products = last;
     return MFBC_OK;
 }
@@ -412,7 +427,7 @@ int run_quad(mfbc_graph *g, bool count, int ncg, int nb, const int32_t *d_source
 // Algorithm 2 on the batch whose T is in the workspace: the counting
 // product (window position 0 of the first window), then backward products
 // in windows as in run_forward, until one produces no frontier entry.
-int run_backward(mfbc_graph *g, const View &vw, int ncg, int nb, int32_t *products, hipStream_t s) {
+int run_backward(mfbc_graph *g, const View &vw, int ncg, int nb, bool tau16, int32_t *products, hipStream_t s) {
     const double arc_bytes = g->weighted ? 8.0 : 4.0;
     mfbc_stats &st = g->stats;
     int64_t prev = 0;
@@ -422,7 +437,7 @@ int run_backward(mfbc_graph *g, const View &vw, int ncg, int nb, int32_t *produc
         for (int i = 0; i < kWindow; i++) {
             const int kk = k + i;
             if (kk == 0) {
-                const hipError_t e = launch_bwd_count(g, vw, ncg, s, window_events(g, i, false));
+                const hipError_t e = launch_bwd_count(g, vw, ncg, tau16, s, window_events(g, i, false));
                 if (e != hipSuccess)
                     return fail(MFBC_EDEVICE, std::string("counting product: ") + hipGetErrorString(e));
             } else {
@@ -475,6 +490,17 @@ int run_backward(mfbc_graph *g, const View &vw, int ncg, int nb, int32_t *produc
     return MFBC_OK;
 }
 
+// One batch of Algorithm 3: the forward products in 16 bits where they fit (two
+// groups to a word, the layout that the counting product reads), else in 32.
+int run_batch(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
+    int rc;
+    bool tau16 = false;
+    if ((rc = run_quad(g, true, true, ncg, nb, d_sources, nullptr, &tau16, s))) return rc;
+    if (!tau16 && (rc = run_forward(g, g->core, ncg, nb, d_sources, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
+        return rc;
+    return run_backward(g, g->core, ncg, nb, tau16, nullptr, s);
+}
+
 int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d_dist,
                  double *d_sigma, bool trace, uint64_t *d_rows, int64_t *h_nnz, int64_t *h_relax,
                  int32_t max_products, int32_t *h_products, void *stream) {
@@ -507,7 +533,7 @@ int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d
     }
     g->stats = mfbc_stats{};
     bool fits = false;
-    if (!trace && (rc = run_quad(g, true, ncg, nb, d_sources, h_products, &fits, s))) return rc;
+    if (!trace && (rc = run_quad(g, false, true, ncg, nb, d_sources, h_products, &fits, s))) return rc;
     if (fits) {
         g->stats.batches = 1;
         launch_quad_rows(g, true, ncg, nb, d_dist, d_sigma, s);
@@ -541,7 +567,7 @@ int backward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, const int
     launch_import_forward(g, ncg, nb, d_dist, d_sigma, s);
     g->trace_step = d_step != nullptr;
     int32_t products = 0;
-    rc = run_backward(g, g->core, ncg, nb, &products, s);
+    rc = run_backward(g, g->core, ncg, nb, false, &products, s);
     g->trace_step = false;
     if (rc) return rc;
     if (ring_flag(g, 2)) return bad_source(g, d_sources, nb, s);
@@ -828,9 +854,7 @@ int bc_batches(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32
     for (int64_t b0 = 0; b0 < n_sources; b0 += batch) {
         const int nb = (int)std::min<int64_t>(batch, n_sources - b0);
         const int bcg = (nb + kWave - 1) / kWave;
-        if ((rc = run_forward(g, g->core, bcg, nb, d_sources + b0, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
-            return rc;
-        if ((rc = run_backward(g, g->core, bcg, nb, nullptr, s))) return rc;
+        if ((rc = run_batch(g, bcg, nb, d_sources + b0, s))) return rc;
         g->stats.batches++;
     }
     launch_lambda_reduce(g, ncg, d_bc, s);
@@ -884,6 +908,7 @@ int lane_graph(mfbc_graph *g, int i, mfbc_graph **out) {
     sh->maxw = g->maxw;
     sh->weighted = g->weighted;
     sh->directed = g->directed;
+    sh->sparse = g->sparse;
     sh->full = g->full;
     sh->core = g->core;
     sh->has_core = g->has_core;
@@ -941,8 +966,7 @@ int bc_lanes(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t
             const int64_t b0 = b * batch;
             const int nb = (int)std::min<int64_t>(batch, n_sources - b0);
             const int bcg = (nb + kWave - 1) / kWave;
-            if (!r) r = run_forward(x, x->core, bcg, nb, d_sources + b0, false, nullptr, nullptr, nullptr, 0, nullptr, ls[i]);
-            if (!r) r = run_backward(x, x->core, bcg, nb, nullptr, ls[i]);
+            if (!r) r = run_batch(x, bcg, nb, d_sources + b0, ls[i]);
             x->stats.batches++;
         }
         if (!r && hipStreamSynchronize(ls[i]) != hipSuccess) r = fail(MFBC_EDEVICE, "lane stream failed");
@@ -1094,6 +1118,7 @@ int mfbc_load_graph(int32_t n, int64_t n_arcs, const int64_t *h_row_ptr, const i
     }
     g->full.arcs = n_arcs;
     if (!rc) rc = plan_views(g, TaskParams{0, 0, 0, 0});
+    if (!rc) g->sparse = sparse_rows(g);
     if (!rc && core_worth_trying(g)) rc = build_core(g, (hipStream_t)hip_stream);
     if (rc) {
         free_graph_memory(g);
@@ -1140,7 +1165,7 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
     if (op == MFBC_OP_SSSP && !bits) {
         bool fits = false;
         int32_t products = 0;
-        if ((rc = run_quad(g, false, ncg, nb, d_sources, &products, &fits, s))) return rc;
+        if ((rc = run_quad(g, false, false, ncg, nb, d_sources, &products, &fits, s))) return rc;
         if (fits) {
             g->stats.batches = 1;
             if (h_products) *h_products = products;
@@ -1302,9 +1327,7 @@ int mfbc_bc_requests(mfbc_graph *g, const int32_t *d_sources, const int64_t *h_f
         launch_set_sources_spans(g, bcg, d_sources, sp, s);
         launch_lambda_zero(g, bcg, s);
         // padding columns (source -1) seed nothing and reach nothing
-        if ((rc = run_forward(g, g->core, bcg, bcg * kWave, nullptr, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
-            return rc;
-        if ((rc = run_backward(g, g->core, bcg, bcg * kWave, nullptr, s))) return rc;
+        if ((rc = run_batch(g, bcg, bcg * kWave, nullptr, s))) return rc;
         launch_lambda_add_groups(g, bcg, o, s);
         g->stats.batches++;
     }

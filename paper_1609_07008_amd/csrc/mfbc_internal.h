@@ -90,6 +90,7 @@ struct View {
 struct QuadBounds {
     uint16_t *lo[3] = {};              // of F_j in lo[j % 3]
     size_t lo_words = 0;               // 32-bit words of each
+    int words = 1;                     // 32-bit words per lane: 2 column groups each
     int32_t *hi = nullptr;
     int32_t *off = nullptr;            // offset of each column
     unsigned long long *live = nullptr;  // columns with entries in F_j, [j % 3][ncg]
@@ -131,6 +132,7 @@ struct mfbc_graph {
     int32_t maxw = 1;
     bool weighted = false;
     bool directed = false;
+    bool sparse = false;     // an arc's row has fewer than 16 arcs on average
     // full: every arc (calls whose results depend on the frontiers themselves:
     // mfbc_forward, the traces, the fixpoints).  core: the arcs that can lie on
     // a shortest path (core.hip), for every call whose result is a function of
@@ -178,7 +180,8 @@ void launch_fwd_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, h
 // it and the merge kernel, and after the merge.  Product j (k) skips itself
 // on the device when product j-1 (k-1) produced no frontier entry.
 void launch_fwd_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s, hipEvent_t *ev);
-hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, hipStream_t s, hipEvent_t *ev);
+// tau16: T is in 16 bits already, two groups to a word (quad.hip).
+hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, bool tau16, hipStream_t s, hipEvent_t *ev);
 void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, int k, hipStream_t s, hipEvent_t *ev);
 // Trace: membership of forward frontier F_j (j = 0: the sources) as
 // per-column vertex bitmaps in caller order (d_rows: nb rows of (n+63)/64
@@ -245,14 +248,17 @@ void launch_bits_export(mfbc_graph *g, int op, int ncg, int nb, int planes, void
 // graph's weights are too wide); count: with multiplicities.
 int quad_products(const mfbc_graph *g, bool count);
 // Bytes of the bounds of ncg groups; places them at `base` if given.
-size_t quad_bound_bytes(const mfbc_graph *g, int ncg, QuadBounds *qb, char *base);
-void launch_quad_init(mfbc_graph *g, bool count, int ncg, int nb, const int32_t *d_sources, hipStream_t s);
-void launch_quad_product(mfbc_graph *g, bool count, int ncg, int j, hipStream_t s, hipEvent_t *ev);
+size_t quad_bound_bytes(const mfbc_graph *g, int ncg, int words, QuadBounds *qb, char *base);
+void launch_quad_init(mfbc_graph *g, const View &vw, bool count, int ncg, int nb, const int32_t *d_sources,
+                      hipStream_t s);
+void launch_quad_product(mfbc_graph *g, const View &vw, bool count, int ncg, int j, hipStream_t s,
+                         hipEvent_t *ev);
 void launch_quad_rows(mfbc_graph *g, bool count, int ncg, int nb, int32_t *dist, double *sigma, hipStream_t s);
 
 // ---- shortest-path core (core.hip) ----
 constexpr int kLandmarks = kWave;        // one per lane
 bool core_worth_trying(const mfbc_graph *g);
+bool sparse_rows(const mfbc_graph *g);
 TaskParams core_params(int32_t n, int64_t arcs, int64_t full_arcs);   // default decomposition of a core
 // Flags of the arcs of one orientation that pass the landmark test (byte per
 // arc) and their number per row.  `near`[v][64], `far`[v][64]: see core.hip.

@@ -746,23 +746,6 @@ __device__ __forceinline__ void count_task(const BwdArgs &a, int cg, int t, unsi
     flush_colmask(a.colmask, a.ncg_all, cg, colany);
 }
 
-__device__ __forceinline__ void count_hub(const BwdArgs &a, int cg, int h, unsigned long long &produced) {
-    const int lane = threadIdx.x & (kWave - 1);
-    uint64_t colany = 0;
-    const Hub *hp = a.hubs + h;
-    const int x = uni(hp->v), first = uni(hp->first), np = uni(hp->nparts);
-    const size_t cgv = (size_t)cg * (size_t)a.n;
-    int c = 0;
-    for (int p = first; p < first + np; p++) c += a.pd[((size_t)cg * a.nslots + p) * kWave + lane];
-    const int dx = a.tdist[(cgv + (size_t)x) * kWave + lane];
-    const uint64_t b = count_finalize(a, cgv, cg, x, dx, c, lane);
-    produced += __popcll(b);
-    colany |= b;
-    if (b && lane == 0)
-        atomicOr(a.abits_n + (size_t)ab_plane(a, cg) * a.nwords + (x >> 5), 1u << (x & 31));
-    flush_colmask(a.colmask, a.ncg_all, cg, colany);
-}
-
 // tau of a pair of column groups for the paired counting product, 16 bits
 // per group in one 32-bit entry per (vertex, lane): group 2q in the low half,
 // 2q+1 in the high half, kTau16Inf for an unreachable vertex.  It holds only
@@ -777,11 +760,31 @@ __device__ __forceinline__ uint32_t tau16(int t) { return t == kInf ? kTau16Inf 
 __device__ __forceinline__ uint32_t pack_tau16(int t0, int t1) { return tau16(t0) | (tau16(t1) << 16); }
 __device__ __forceinline__ int unpack_tau16(uint32_t h) { return h == kTau16Inf ? kInf : (int)h; }
 
+__device__ __forceinline__ void count_hub(const BwdArgs &a, int cg, int h, unsigned long long &produced) {
+    const int lane = threadIdx.x & (kWave - 1);
+    uint64_t colany = 0;
+    const Hub *hp = a.hubs + h;
+    const int x = uni(hp->v), first = uni(hp->first), np = uni(hp->nparts);
+    const size_t cgv = (size_t)cg * (size_t)a.n;
+    int c = 0;
+    for (int p = first; p < first + np; p++) c += a.pd[((size_t)cg * a.nslots + p) * kWave + lane];
+    // the compact copy where there is one: T itself may exist in 16 bits only
+    const int dx = a.tau_full && uni(*a.tau_full) == 0
+                       ? unpack_tau16((a.tau2[((size_t)(cg >> 1) * a.n + (size_t)x) * kWave + lane] >> (16 * (cg & 1))) & 0xffffu)
+                       : a.tdist[(cgv + (size_t)x) * kWave + lane];
+    const uint64_t b = count_finalize(a, cgv, cg, x, dx, c, lane);
+    produced += __popcll(b);
+    colany |= b;
+    if (b && lane == 0)
+        atomicOr(a.abits_n + (size_t)ab_plane(a, cg) * a.nwords + (x >> 5), 1u << (x & 31));
+    flush_colmask(a.colmask, a.ncg_all, cg, colany);
+}
+
 // One task of the counting product for the pair of column groups q (batches
 // of two or more groups): tau of both groups is read from its interleaved
 // 16-bit copy (tau2), so one 4-byte gather per arc and lane serves the tests
 // of both groups, where one group per wave issues a 256-B gather per arc for
-// each group; the owner's tau is read in full from tdist.  Each group keeps its own counters,
+// each group.  Each group keeps its own counters,
 // leaves and DAG masks, written in the layouts the backward products of the
 // batch read (fb_index, ab_plane).  A padding group (odd group count) counts
 // nothing and writes nothing.
@@ -809,8 +812,13 @@ __device__ __forceinline__ void count_task_w(const BwdArgs &a, int q, int t, uns
     const int xa = v0, xb = hub >= 0 ? v0 + 1 : v1;
     for (int x = xa; x < xb; x++) {
         int2 dx;
-        dx.x = Td0[(size_t)x * kWave + lane];
-        dx.y = has1 ? Td1[(size_t)x * kWave + lane] : kInf;
+        if constexpr (!FULL) {
+            const uint32_t h = T16[(size_t)x * kWave + lane];
+            dx = make_int2(unpack_tau16(h & 0xffffu), unpack_tau16(h >> 16));
+        } else {
+            dx.x = Td0[(size_t)x * kWave + lane];
+            dx.y = has1 ? Td1[(size_t)x * kWave + lane] : kInf;
+        }
         const bool r0 = in0 && dx.x != kInf, r1 = in1 && dx.y != kInf;
         const int64_t ea = hub >= 0 ? e0 : a.rp[x];
         const int64_t eb = hub >= 0 ? e1 : a.rp[x + 1];

@@ -1,7 +1,8 @@
 // Distances and path counts (MFBF, Algorithm 1) and shortest distances (the
 // min, a + w fixpoint) of a batch in 16 bits an entry, on every arc of the
-// graph.  Same products, frontiers and results as the 32-bit forms in
-// products.h and monoid.hip; three things make them cheaper.
+// graph, and for centrality on its shortest-path core.  Same products,
+// frontiers and results as the 32-bit forms in products.h and monoid.hip; three
+// things make them cheaper (the first alone on a core).
 //
 // 1. A frontier entry of product j has j arcs, so its weight is at most j times
 //    the largest weight: while that leaves room, weight and multiplicity share
@@ -12,7 +13,8 @@
 //    more": the value is in the binary64 array, and sums that reach it are
 //    taken again in binary64, over the row's arcs in order.  The encoding is
 //    exact.  A call whose frontier outlives the products that fit starts over
-//    in 32 bits (quad_products).
+//    in 32 bits (quad_products).  T in this layout is what the paired counting
+//    product of a centrality call reads, so no copy of it is made.
 //
 // 2. An arc u -> v can change v only if F(u) + w <= T(v) in some column (< for
 //    distances alone).  Columns differ mostly by how far their source is from
@@ -23,7 +25,10 @@
 //    with the left minimum kept per frontier row (16 bits, `lo`) and the right
 //    maximum per vertex (`hi`, columns whose frontier has died out left out).
 //    Any offsets are sound; these leave 29% of the gathers on weighted R-MAT
-//    graphs and 23% on uniform ones of degree 256.
+//    graphs and 23% on uniform ones of degree 256.  On a core nearly every arc
+//    passes and rows are short, so no bounds are kept (centrality of all sources
+//    of a uniform graph of 1,024 vertices, degree 8: 1.32 ms with, 1.03 without;
+//    uniform, degree 60, n = 10,000, 900 sources: 3.5 / 2.6).
 //
 // 3. `lo` is also the activity test, so that a chunk of arcs makes one gather
 //    of 16-bit words where the 32-bit forms gather bitmap words.
@@ -131,7 +136,9 @@ __device__ __forceinline__ void store_lane(uint32_t *p, size_t row, int lane, co
 }
 
 // One wave's product: COUNT carries multiplicities (MFBF), else distances only.
-template <int AM, int Q, bool COUNT>
+// B: arcs are tested against the bounds; without (on a core) the activity bitmap
+// is the test and no bound, offset or live-column mask is kept.
+template <int AM, int Q, bool COUNT, bool B>
 struct QuadPull {
     static constexpr int G = 2 * Q;              // column groups per lane
     static constexpr int U = Q == 1 ? 8 : 4;     // active arcs per batch
@@ -149,6 +156,8 @@ struct QuadPull {
         for (int g = 0; g < G; g++) {
             any[g] = 0;
             const int cg = q * G + g;
+            off[g] = 0;
+            if constexpr (!B) continue;
             off[g] = cg < a.ncg ? a.off[cg * kWave + lane] : 0;
             if (cg < a.ncg) live |= (uint32_t)((or_copies(a.live[cg * kLiveCopies + (lane & (kLiveCopies - 1))]) >> lane) & 1ull) << g;
         }
@@ -214,7 +223,8 @@ struct QuadPull {
             bool act = false;
             if (my < eb) {
                 load_arc<AM>(a.arcs, my, u, wt);
-                act = a.lo[row0 + (size_t)(uint32_t)u] != kLoOff;
+                if constexpr (B) act = a.lo[row0 + (size_t)(uint32_t)u] != kLoOff;
+                else act = (a.bits[(size_t)q * a.nwords + (u >> 5)] >> (u & 31)) & 1u;
             }
             uint64_t am = ballot(act);
             while (am) {
@@ -274,20 +284,21 @@ struct QuadPull {
                 nt.w[g >> 1] = (nt.w[g >> 1] & ~(0xffffu << sh)) | (d[g] << sh);
                 nf.w[g >> 1] = (nf.w[g >> 1] & ~(0xffffu << sh)) | (x << sh);
                 const int r = (int)d[g] - off[g];
-                if (r < least) least = r;
+                if (B && r < least) least = r;
             }
-            if ((live >> g) & 1u) {
+            if (B && ((live >> g) & 1u)) {
                 const int r = tn == kNone16 ? INT32_MAX : (int)tn - off[g];
                 if (r > most) most = r;
             }
             const uint64_t b = ballot(keep);
             produced += __popcll(b);
             kept |= b;
-            any[g] |= b;
+            if constexpr (B) any[g] |= b;
         }
         if (!kept) return false;
         store_lane<Q>(a.t, row0 + (size_t)v, lane, nt);
         store_lane<Q>(a.f_n, row0 + (size_t)v, lane, nf);
+        if constexpr (!B) return true;
         least = wave_extreme<false>(least);
         most = wave_extreme<true>(most);
         if (lane == 0) {
@@ -302,8 +313,9 @@ struct QuadPull {
         const Task *tp = a.tasks + t;
         const int v0 = uni(tp->v0), v1 = uni(tp->v1), hub = uni(tp->hub), part = uni(tp->part);
         const int64_t e0 = uni64(tp->e0), e1 = uni64(tp->e1);
-        const uint16_t *lo = a.lo + row0;
-        const int thr_l = v0 + lane < v1 ? a.hi[row0 + (size_t)(v0 + lane)] : INT32_MIN;
+        const uint16_t *lo = B ? a.lo + row0 : nullptr;
+        const uint32_t *bits = a.bits + (size_t)q * a.nwords;
+        const int thr_l = B && v0 + lane < v1 ? a.hi[row0 + (size_t)(v0 + lane)] : INT32_MIN;
         int cur = -1;            // row (offset from v0) of the open reduction
         Lane<Q> acc, own;
 #pragma unroll
@@ -330,13 +342,18 @@ struct QuadPull {
             int u, wt;
             decode_arc<AM>(a.arcs, rn0, rn1, u, wt);
             const int o = on0;
-            const uint32_t x = my < e1 ? lo[(uint32_t)u] : kLoOff;
+            uint32_t x = kLoOff;
+            bool act = false;
+            if (my < e1) {
+                if constexpr (B) x = lo[(uint32_t)u];
+                else act = (bits[u >> 5] >> (u & 31)) & 1u;
+            }
             if (my + kWave < e1) {
                 load_arc_raw<AM>(a.arcs, my + kWave, rn0, rn1);
                 on0 = a.owner[my + kWave];
             }
-            const int thr = __shfl(thr_l, o, kWave);
-            uint64_t am = ballot(pass(x, wt, thr));
+            if constexpr (B) act = pass(x, wt, __shfl(thr_l, o, kWave));
+            uint64_t am = ballot(act);
             int na = __popcll(am);
             while (na > 0) {
                 int ow[U], wk[U];
@@ -460,17 +477,19 @@ struct QuadPull {
 // What a product leaves ready for the next: the bitmaps, bounds, live columns
 // and counters of F_{j+1}, last read two products ago, cleared; the vertices
 // of the frontier just read and their arcs counted.
+template <bool B>
 __device__ __forceinline__ void quad_close(const QuadArgs &a, unsigned long long &nv, unsigned long long &na) {
     const int gtid = blockIdx.x * blockDim.x + threadIdx.x;
     const int total = gridDim.x * blockDim.x;
     close_product(a.bits, a.next_bits, a.nwords, a.nq, a.rp, a.next_ctr, nv, na);
+    if constexpr (!B) return;
     const size_t count = (size_t)a.nq * a.n;
     uint32_t *p = (uint32_t *)a.lo_clear;        // the allocation is whole words
     for (size_t i = gtid; i < (count + 1) / 2; i += total) p[i] = kNone32;
     for (int i = gtid; i < a.ncg * kLiveCopies; i += total) a.live_clear[i] = 0ull;
 }
 
-template <int AM, int Q, bool COUNT, bool C>
+template <int AM, int Q, bool COUNT, bool B, bool C>
 __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS void k_quad_pull(QuadArgs a) {
     if (!live_prev(a.prev_ctr)) {
         if constexpr (C) close_skipped(a.next_ctr);
@@ -480,30 +499,30 @@ __global__ __launch_bounds__(kBlock) MFBC_PULL_SGPRS void k_quad_pull(QuadArgs a
     const int q = wid / a.ntasks;
     unsigned long long produced = 0, outs = 0, nv = 0, na = 0;
     if (q < a.nq) {
-        QuadPull<AM, Q, COUNT> p(a, q);
+        QuadPull<AM, Q, COUNT, B> p(a, q);
         p.task(wid - q * a.ntasks);
-        p.flush();
+        if constexpr (B) p.flush();
         produced = p.produced;
         outs = p.outs;
     }
-    if constexpr (C) quad_close(a, nv, na);
+    if constexpr (C) quad_close<B>(a, nv, na);
     flush_counts(produced, outs, nv, na, a.ctr);
 }
 
-template <int Q, bool COUNT>
+template <int Q, bool COUNT, bool B>
 __global__ __launch_bounds__(kBlock) void k_quad_merge(QuadArgs a) {
     if (!live_prev(a.prev_ctr)) {
         close_skipped(a.next_ctr);
         return;
     }
     unsigned long long nv = 0, na = 0, produced = 0, outs = 0;
-    quad_close(a, nv, na);
+    quad_close<B>(a, nv, na);
     const int wid = blockIdx.x * kWavesPerBlock + uni((int)(threadIdx.x >> 6));
     const int q = wid / a.nhubs;
     if (q < a.nq) {
-        QuadPull<0, Q, COUNT> p(a, q);
+        QuadPull<0, Q, COUNT, B> p(a, q);
         p.merge(wid - q * a.nhubs);
-        p.flush();
+        if constexpr (B) p.flush();
         produced = p.produced;
         outs = p.outs;
     }
@@ -552,13 +571,17 @@ struct QuadSeed {
         ((uint16_t *)t)[i] = 0;
         ((uint16_t *)f)[i] = COUNT ? 1 : 0;      // weight 0, multiplicity 1 inline
         if (COUNT) tsig[((size_t)cg * n + v) * kWave + lane] = 1.0;
+        if (!lo) return mark(abits, q, v);
         int h = hub ? hub[v] : 0;
         if (h == kInf) h = 0;
         off[c] = h;
         const int code = kLoBias - h;
         lo[row] = (uint16_t)(code < 0 ? 0 : code);
-        atomicOr(abits + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
+        mark(abits, q, v);
         atomicOr(live + cg * kLiveCopies, 1ull << lane);
+    }
+    __device__ void mark(uint32_t *bm, int q, int v) const {
+        atomicOr(bm + (size_t)q * nwords + (v >> 5), 1u << (v & 31));
     }
 };
 
@@ -637,19 +660,19 @@ int bits_of(int64_t x) {
     return b;
 }
 
-int quad_words(int ncg) { return ncg <= 2 ? 1 : 2; }
 
 // Multiplicity bits of the frontier that product j reads: its candidates
 // weigh at most j * maxw, and no entry may equal the all-ones one.
 int quad_mb(const mfbc_graph *g, int j) { return 16 - bits_of((int64_t)j * g->maxw + 1); }
 
-size_t quad_rows(const mfbc_graph *g, int ncg) { return (size_t)((ncg + 2 * quad_words(ncg) - 1) / (2 * quad_words(ncg))) * g->n; }
+size_t quad_rows(const mfbc_graph *g, int ncg, int words) {
+    return (size_t)((ncg + 2 * words - 1) / (2 * words)) * g->n;
+}
 
-QuadArgs quad_args(mfbc_graph *g, int ncg, int j) {
+QuadArgs quad_args(mfbc_graph *g, const View &vw, int ncg, int j) {
     Workspace &ws = g->ws;
-    const View &vw = g->full;
     QuadArgs a{};
-    const int Q = quad_words(ncg), b = (j - 1) & 1;
+    const int Q = ws.quad.words, b = (j - 1) & 1;
     a.tasks = vw.plan_in.tasks;
     a.hubs = vw.plan_in.hubs;
     a.ntasks = vw.plan_in.ntasks;
@@ -696,40 +719,40 @@ QuadArgs quad_args(mfbc_graph *g, int ncg, int j) {
     return a;
 }
 
-template <int Q, bool COUNT>
-void quad_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
-    const QuadArgs a = quad_args(g, ncg, 1);
+template <int Q, bool COUNT, bool B>
+void quad_init(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
+    const QuadArgs a = quad_args(g, vw, ncg, 1);
     Workspace &ws = g->ws;
     const size_t rows = (size_t)a.nq * g->n, words = rows * kWave * Q;
-    hipLaunchKernelGGL(k_quad_init, dim3(grid_for(words, 1024, 16384)), dim3(256), 0, s, a.t, words, a.hi, rows,
-                       (uint32_t *)ws.quad.lo[0], 3 * ws.quad.lo_words, ws.abits[0], ws.abits[1], ws.abits[2],
-                       (size_t)a.nq * a.nwords, ws.quad.live, (size_t)3 * ncg * kLiveCopies, ws.counters, (int)kRingWords,
-                       ws.flags);
+    hipLaunchKernelGGL(k_quad_init, dim3(grid_for(words, 1024, 16384)), dim3(256), 0, s, a.t, words, a.hi,
+                       B ? rows : 0, (uint32_t *)ws.quad.lo[0], B ? 3 * ws.quad.lo_words : 0, ws.abits[0], ws.abits[1],
+                       ws.abits[2], (size_t)a.nq * a.nwords, ws.quad.live, B ? (size_t)3 * ncg * kLiveCopies : 0,
+                       ws.counters, (int)kRingWords, ws.flags);
     const QuadSeed<Q, COUNT> seed{g->n,    a.nwords,  (uint32_t *)ws.fdist[0], a.t, ws.abits[0], ws.quad.lo[0],
                                   ws.quad.off, g->hub_dist, ws.quad.live, ws.tsig};
     launch_seed(g, seed, ncg, nb, d_sources, s);
 }
 
-template <int AM, int Q, bool COUNT>
+template <int AM, int Q, bool COUNT, bool B>
 void quad_pull(const QuadArgs &a, int grid, hipStream_t s) {
-    if (a.nhubs) hipLaunchKernelGGL((k_quad_pull<AM, Q, COUNT, false>), dim3(grid), dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((k_quad_pull<AM, Q, COUNT, true>), dim3(grid), dim3(kBlock), 0, s, a);
+    if (a.nhubs) hipLaunchKernelGGL((k_quad_pull<AM, Q, COUNT, B, false>), dim3(grid), dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_quad_pull<AM, Q, COUNT, B, true>), dim3(grid), dim3(kBlock), 0, s, a);
 }
 
-template <int Q, bool COUNT>
-void quad_product(mfbc_graph *g, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
-    const QuadArgs a = quad_args(g, ncg, j);
+template <int Q, bool COUNT, bool B>
+void quad_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
+    const QuadArgs a = quad_args(g, vw, ncg, j);
     if (ev) (void)hipEventRecord(ev[0], s);
     const int grid = grid_for((size_t)a.ntasks * a.nq, kWavesPerBlock);
-    const Csr &c = g->full.in;
-    if (c.pk) quad_pull<1, Q, COUNT>(a, grid, s);
-    else if (c.w) quad_pull<2, Q, COUNT>(a, grid, s);
-    else quad_pull<0, Q, COUNT>(a, grid, s);
+    const Csr &c = vw.in;
+    if (c.pk) quad_pull<1, Q, COUNT, B>(a, grid, s);
+    else if (c.w) quad_pull<2, Q, COUNT, B>(a, grid, s);
+    else quad_pull<0, Q, COUNT, B>(a, grid, s);
     if (ev) (void)hipEventRecord(ev[1], s);
     if (a.nhubs) {
         const int mgrid = std::max(grid_for((size_t)a.nhubs * a.nq, kWavesPerBlock),
                                    grid_for((size_t)a.nwords, kBlock, 1024));
-        hipLaunchKernelGGL((k_quad_merge<Q, COUNT>), dim3(mgrid), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL((k_quad_merge<Q, COUNT, B>), dim3(mgrid), dim3(kBlock), 0, s, a);
     }
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
@@ -751,21 +774,21 @@ void quad_rows_out(mfbc_graph *g, int ncg, int nb, int32_t *dist, double *sigma,
 // that a call would often start over in 32 bits.  Distances need j * maxw <
 // 65535, multiplicities two bits besides: weights up to 255 fit 56 products
 // with multiplicities (most graphs take 10 to 25), 256 without.
-// Below 2^18 arcs the 32-bit forms stay: a task's fixed cost (bounds, live
-// columns) shows there.  Distances and path counts of 256 sources, ms in 32 /
-// 16 bits: uniform n = 10,000 of degree 10 1.13 / 1.51, weighted R-MAT scale
-// 12 0.77 / 0.93, 14 1.50 / 1.47, 16 3.69 / 2.12, 18 (200 sources) 10.5 / 5.3.
+// A graph of short rows (grids, paths) may take any number of products and
+// gains little (uniform n = 10,000 of degree 10, 900 sources: 5.3 ms of
+// centrality in 32 bits, 5.0 in 16; a grid of 30 by 30 with weights to 255, 62
+// products: 2.1 in 32 bits, 2.6 with the 56 that fit taken twice), so it has
+// to fit whole: no shortest path has more arcs than vertices.
 int quad_products(const mfbc_graph *g, bool count) {
     constexpr int kLeast = 40;
-    if (g->arcs < (1 << 18)) return 0;
     const int64_t most = count ? ((int64_t)1 << 14) - 1 : 65535;
     const int64_t j = (most - 1) / g->maxw - (count ? 1 : 0);     // product j writes for product j + 1
     const int64_t fit = j / kWindow * kWindow;
-    return fit < kLeast ? 0 : (int)std::min<int64_t>(fit, 1 << 20);
+    return fit < kLeast || (g->sparse && g->n > fit) ? 0 : (int)std::min<int64_t>(fit, 1 << 20);
 }
 
-size_t quad_bound_bytes(const mfbc_graph *g, int ncg, QuadBounds *qb, char *base) {
-    const size_t rows = quad_rows(g, ncg);
+size_t quad_bound_bytes(const mfbc_graph *g, int ncg, int words, QuadBounds *qb, char *base) {
+    const size_t rows = quad_rows(g, ncg, words);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char *p = base ? base + off : nullptr;
@@ -773,6 +796,7 @@ size_t quad_bound_bytes(const mfbc_graph *g, int ncg, QuadBounds *qb, char *base
         return p;
     };
     QuadBounds b;
+    b.words = words;
     b.lo_words = (rows + 1) / 2;
     uint16_t *lo = (uint16_t *)take(3 * b.lo_words * 4);
     for (int i = 0; i < 3; i++) b.lo[i] = lo ? lo + (size_t)i * 2 * b.lo_words : nullptr;
@@ -783,25 +807,30 @@ size_t quad_bound_bytes(const mfbc_graph *g, int ncg, QuadBounds *qb, char *base
     return off;
 }
 
+// The forms in use: with bounds, one or two words a lane, with multiplicities
+// or without; and one word with multiplicities without bounds (a core).
 #define MFBC_QUAD(fn, ...)                                              \
     do {                                                                \
-        if (quad_words(ncg) == 1) {                                     \
-            if (count) fn<1, true>(__VA_ARGS__);                        \
-            else fn<1, false>(__VA_ARGS__);                             \
-        } else {                                                        \
-            if (count) fn<2, true>(__VA_ARGS__);                        \
-            else fn<2, false>(__VA_ARGS__);                             \
-        }                                                               \
+        if (!g->ws.quad.hi) fn<1, true, false>(__VA_ARGS__);            \
+        else if (g->ws.quad.words == 1 && count) fn<1, true, true>(__VA_ARGS__); \
+        else if (g->ws.quad.words == 1) fn<1, false, true>(__VA_ARGS__);         \
+        else if (count) fn<2, true, true>(__VA_ARGS__);                 \
+        else fn<2, false, true>(__VA_ARGS__);                           \
     } while (0)
 
-void launch_quad_init(mfbc_graph *g, bool count, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
-    MFBC_QUAD(quad_init, g, ncg, nb, d_sources, s);
+void launch_quad_init(mfbc_graph *g, const View &vw, bool count, int ncg, int nb, const int32_t *d_sources,
+                      hipStream_t s) {
+    MFBC_QUAD(quad_init, g, vw, ncg, nb, d_sources, s);
 }
-void launch_quad_product(mfbc_graph *g, bool count, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
-    MFBC_QUAD(quad_product, g, ncg, j, s, ev);
+void launch_quad_product(mfbc_graph *g, const View &vw, bool count, int ncg, int j, hipStream_t s,
+                         hipEvent_t *ev) {
+    MFBC_QUAD(quad_product, g, vw, ncg, j, s, ev);
 }
 void launch_quad_rows(mfbc_graph *g, bool count, int ncg, int nb, int32_t *dist, double *sigma, hipStream_t s) {
-    MFBC_QUAD(quad_rows_out, g, ncg, nb, dist, sigma, s);
+    if (g->ws.quad.words == 1 && count) quad_rows_out<1, true>(g, ncg, nb, dist, sigma, s);
+    else if (g->ws.quad.words == 1) quad_rows_out<1, false>(g, ncg, nb, dist, sigma, s);
+    else if (count) quad_rows_out<2, true>(g, ncg, nb, dist, sigma, s);
+    else quad_rows_out<2, false>(g, ncg, nb, dist, sigma, s);
 }
 
 }  // namespace mfbc
