@@ -567,4 +567,19 @@ int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const in
 
 namespace mfbc {
 size_t ws_scratch_bytes_impl(const ManyWorkspace &ws) { return ws.scratch_bytes; }
+
+// The workspace's scratch, grown to `bytes` (null if they do not fit).
+char *many_scratch(ManyWorkspace &ws, size_t bytes) {
+    if (ws.scratch_bytes >= bytes) return ws.scratch;
+    if (ws.scratch) (void)hipFree(ws.scratch);
+    ws.scratch = nullptr;
+    ws.scratch_bytes = 0;
+    if (hipMalloc((void **)&ws.scratch, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        ws.scratch = nullptr;
+        return nullptr;
+    }
+    ws.scratch_bytes = bytes;
+    return ws.scratch;
+}
 }  // namespace mfbc

@@ -10,10 +10,12 @@
 // copy per window brings back their frontier sizes and the error flags; that
 // is the only host round trip of the loop.
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <type_traits>
 #include <utility>
@@ -832,6 +834,9 @@ void free_graph_memory(mfbc_graph *g) {
     g->core = View{};
     g->has_core = false;
     free_view(g->full);
+    if (g->own_in.tasks != g->own_out.tasks) free_plan(g->own_in);
+    free_plan(g->own_out);
+    g->own_in = Plan{};
     dfree(g->perm);
     dfree(g->hub_dist);
     g->h_perm.clear();
@@ -988,27 +993,6 @@ int bc_lanes(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t
     return MFBC_OK;
 }
 
-// Address of the static scratch on `device` (which must be current): taken
-// once per device with hipGetSymbolAddress and kept.  Host code never uses
-// the array's own name as an address.
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-char *g_scratch_base[kMaxDevices] = {};
-
-int scratch_base(int device, char **out) {
-    if (device < 0 || device >= kMaxDevices) return fail(MFBC_EDEVICE, "device index out of range");
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_base[device]) {
-        void *p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p)
-            return fail(MFBC_EDEVICE, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
-        g_scratch_base[device] = (char *)p;
-    }
-    *out = g_scratch_base[device];
-    return MFBC_OK;
-}
-
 // The workspace of `ncg` groups carved from `base` (same arrays and sizes as
 // ensure_workspace allocates, each 256-byte aligned).
 void carve_workspace(const mfbc_graph *g, int ncg, char *base, Workspace &ws) {
@@ -1031,6 +1015,170 @@ struct WorkspaceSwap {
     explicit WorkspaceSwap(mfbc_graph *gr) : g(gr), saved(gr->ws) { g->ws = Workspace{}; }
     ~WorkspaceSwap() { g->ws = saved; }
 };
+
+// The library's own decomposition of a graph's core in place of one set with
+// mfbc_set_plan, for the duration of a scope: run sizes tuned for the batched
+// form's workgroups are too coarse for products that spread over the device
+// (32 graphs of 200..6,000 vertices: 50 ms under them, 29 under its own).
+struct OwnPlan {
+    mfbc_graph *g;
+    Plan out, in;
+    explicit OwnPlan(mfbc_graph *gr) : g(gr), out(gr->core.plan_out), in(gr->core.plan_in) {
+        if (!g->own_out.tasks) return;
+        g->core.plan_out = g->own_out;
+        g->core.plan_in = g->own_in;
+    }
+    ~OwnPlan() {
+        g->core.plan_out = out;
+        g->core.plan_in = in;
+    }
+};
+
+// Whether the batched form's graphs run one after another on streams.  With T
+// the sum over its two-group jobs of the graph's arcs and vertices and M the
+// largest of them, the streams take about 230 us a graph and 2.2 ns an arc; the
+// persistent launch the time of its largest job (eight waves: 1.5 us an
+// of M) or, with every workgroup busy, 2.8 ns an arc.  Measured, streams /
+// persistent, in ms:
+//   3 graphs of 300                     0.9 / 1.9    32 of 200..6,000       29 / 94
+//   8 of 200..1,000                     2.1 / 9.2    24 of 200..20,000     209 / 410
+//   16 of 1,000..1,200, degree 40..64   5.2 / 19     64 of 200..20,000     344 / 496
+//   40 of 200..2,000                     11 / 28     96 of 4,000..6,000    364 / 471
+//   100 of 200..3,000                    38 / 57     200 of 200..1,000      46 / 22
+//   64 of 1,000..1,200, degree 4..8     24.5 / 24.2
+bool many_underfilled(const std::vector<mfbc_graph *> &gs, const std::vector<int64_t> &ns) {
+    double total = 0, most = 0;
+    for (size_t i = 0; i < gs.size(); i++) {
+        const double job = (double)gs[i]->core.arcs + gs[i]->n;
+        total += job * (double)((ns[i] + 2 * kWave - 1) / (2 * kWave));
+        if (ns[i]) most = std::max(most, job);
+    }
+    return 230e3 * (double)gs.size() + 2.2 * total < std::max(1500.0 * most, 2.8 * total);
+}
+
+// The batched form on streams: the graphs one after another on up to four,
+// largest first, each with its sources in wide batches, so that a product
+// spreads over the whole device instead of the eight waves of a job.  The
+// state of the streams is carved from the batched form's scratch.
+constexpr size_t kManyLaneBytes = (size_t)512 << 20;
+
+int many_on_streams(const std::vector<mfbc_graph *> &gs, const std::vector<const int32_t *> &src,
+                    const std::vector<int64_t> &ns, const std::vector<double *> &out, size_t budget,
+                    ManyWorkspace &mw, hipStream_t s, bool *done, unsigned long long *products) {
+    *done = false;
+    struct Item {
+        mfbc_graph *g;
+        std::vector<size_t> at;      // positions in the call (a graph may be listed twice)
+        int ncg;                     // column groups of a batch
+        double cost;
+    };
+    std::vector<Item> items;
+    for (size_t i = 0; i < gs.size(); i++) {
+        Item *it = nullptr;
+        for (auto &x : items)
+            if (x.g == gs[i]) it = &x;
+        if (!it) {
+            items.push_back({gs[i], {}, 1, 0.0});
+            it = &items.back();
+        }
+        it->at.push_back(i);
+        it->cost += (double)ns[i] * (double)(gs[i]->core.arcs + gs[i]->n);
+    }
+    size_t lane_bytes = 0;
+    for (auto &x : items) {
+        const OwnPlan own(x.g);
+        int64_t most = 0;
+        for (size_t i : x.at) most = std::max(most, ns[i]);
+        const int all = bc_groups(most, INT32_MAX);
+        int batches = 1;
+        x.ncg = all;
+        while (x.ncg > 1 && ws_bytes(x.g, x.ncg, false) > kManyLaneBytes) {
+            batches++;
+            x.ncg = (all + batches - 1) / batches;
+        }
+        lane_bytes = std::max(lane_bytes, ws_bytes(x.g, x.ncg, false));
+    }
+    lane_bytes = align256(lane_bytes);
+    const int lanes = (int)std::min<size_t>({(size_t)kMaxLanes, items.size(), budget / std::max<size_t>(lane_bytes, 1)});
+    if (lanes < 1) return MFBC_OK;
+    char *base = many_scratch(mw, lane_bytes * (size_t)lanes);
+    if (!base) return MFBC_OK;
+    std::stable_sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.cost > b.cost; });
+    mfbc_graph *g0 = gs[0];
+    hipStream_t ls[kMaxLanes] = {s};
+    if (!g0->lane_start) HIP_TRY(hipEventCreateWithFlags(&g0->lane_start, hipEventDisableTiming));
+    HIP_TRY(hipEventRecord(g0->lane_start, s));
+    for (int i = 1; i < lanes; i++) {
+        if (!g0->lane_stream[i]) HIP_TRY(hipStreamCreateWithFlags(&g0->lane_stream[i], hipStreamNonBlocking));
+        ls[i] = g0->lane_stream[i];
+        HIP_TRY(hipStreamWaitEvent(ls[i], g0->lane_start, 0));
+    }
+    std::atomic<size_t> next{0};
+    std::atomic<bool> stop{false};
+    int rcs[kMaxLanes] = {};
+    std::string msgs[kMaxLanes];
+    std::atomic<unsigned long long> fwd{0}, bwd{0};
+    auto lane = [&](int i) {
+        int rc = hipSetDevice(g0->device) == hipSuccess ? MFBC_OK : fail(MFBC_EDEVICE, "hipSetDevice failed");
+        while (!rc && !stop) {
+            const size_t k = next++;
+            if (k >= items.size()) break;
+            Item &x = items[k];
+            const OwnPlan own(x.g);
+            WorkspaceSwap sw(x.g);
+            carve_workspace(x.g, x.ncg, base + (size_t)i * lane_bytes, x.g->ws);
+            for (size_t at : x.at) {
+                if (rc) break;
+                const mfbc_stats before = x.g->stats;
+                rc = bc_batches(x.g, src[at], ns[at], x.ncg * kWave, bc_groups(ns[at], x.ncg * kWave), out[at], ls[i]);
+                fwd += (unsigned long long)x.g->stats.fwd_products;
+                bwd += (unsigned long long)x.g->stats.bwd_products;
+                x.g->stats = before;
+            }
+        }
+        if (rc) {
+            stop = true;
+            msgs[i] = mfbc_last_error();
+            (void)hipStreamSynchronize(ls[i]);
+        }
+        rcs[i] = rc;
+    };
+    std::vector<std::thread> th;
+    try {
+        for (int i = 1; i < lanes; i++) th.emplace_back(lane, i);
+    } catch (const std::system_error &) {
+        // fewer threads: the lanes that run take every graph
+    }
+    lane(0);
+    for (auto &t : th) t.join();
+    for (int i = 0; i < lanes; i++)
+        if (rcs[i]) return fail(rcs[i], msgs[i]);
+    products[0] += fwd;
+    products[1] += bwd;
+    *done = true;
+    return MFBC_OK;
+}
+
+// Address of the static scratch on `device` (which must be current): taken
+// once per device with hipGetSymbolAddress and kept.  Host code never uses
+// the array's own name as an address.
+constexpr int kMaxDevices = 64;
+std::mutex g_scratch_mu;
+char *g_scratch_base[kMaxDevices] = {};
+
+int scratch_base(int device, char **out) {
+    if (device < 0 || device >= kMaxDevices) return fail(MFBC_EDEVICE, "device index out of range");
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    if (!g_scratch_base[device]) {
+        void *p = nullptr;
+        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        if (e != hipSuccess || !p)
+            return fail(MFBC_EDEVICE, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
+        g_scratch_base[device] = (char *)p;
+    }
+    *out = g_scratch_base[device];
+    return MFBC_OK;
+}
 
 }  // namespace
 
@@ -1405,6 +1553,12 @@ int mfbc_set_plan(mfbc_graph *g, int32_t run_arcs, int32_t run_verts, int32_t he
     DeviceGuard dg(g->device);
     HIP_TRY(hipDeviceSynchronize());
     const int32_t old_slots = max_slots(g);
+    if (!g->own_out.tasks) {         // the library's own decomposition is kept
+        g->own_out = g->core.plan_out;
+        g->own_in = g->core.plan_in;
+        g->core.plan_out = g->core.plan_in = Plan{};
+        if (!g->has_core) g->full.plan_out = g->full.plan_in = Plan{};
+    }
     const int rc = plan_views(g, TaskParams{run_arcs, run_verts, heavy, slice});
     if (rc) return rc;
     // the partial buffers are sized by the slot count: regrow on next use
@@ -1484,9 +1638,11 @@ int mfbc_bc_many(int32_t n_graphs, mfbc_graph *const *graphs, const int32_t *con
     const size_t budget = (free_b + ws_scratch_bytes(ws)) / 2;
     const int cap = (int)std::max<size_t>(1, budget / std::max<size_t>(slot, 1));
     blocks = std::min(blocks, cap);
-    // one persistent launch per arc encoding (unweighted, packed, separate)
     unsigned long long tot[2] = {0, 0};
-    for (int mode = 0; mode < 3; mode++) {
+    bool done = false;
+    if (many_underfilled(gs, ns) && (rc = many_on_streams(gs, src, ns, out, budget, ws, s, &done, tot))) return rc;
+    // one persistent launch per arc encoding (unweighted, packed, separate)
+    for (int mode = 0; mode < 3 && !done; mode++) {
         std::vector<mfbc_graph *> g2;
         std::vector<const int32_t *> s2;
         std::vector<int64_t> n2;

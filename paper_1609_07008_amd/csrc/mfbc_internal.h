@@ -139,6 +139,7 @@ struct mfbc_graph {
     // distances and path counts; the same arrays as `full` unless has_core.
     mfbc::View full, core;
     bool has_core = false;
+    mfbc::Plan own_out, own_in;   // the core's default decomposition, once mfbc_set_plan replaced it
     int32_t *hub_dist = nullptr;  // upper bounds of the distances to the vertex of highest degree
     int64_t scratch_slots = 0;  // hub partial slots mfbc_bc_noalloc admits calls by
     int mb = 1;             // inline multiplicity bits of a packed frontier tuple
@@ -234,6 +235,7 @@ int launch_bc_many(std::vector<mfbc_graph *> &graphs, const std::vector<const in
                    int block_threads, int blocks, int w, hipStream_t s, ManyWorkspace &ws,
                    unsigned long long *h_stats, int32_t *h_flags, std::string &err);
 ManyWorkspace &many_workspace(int device);
+char *many_scratch(ManyWorkspace &ws, size_t bytes);
 
 // ---- fixpoints on bit masks (bits.hip) ----
 bool bits_fit(const mfbc_graph *g, int op);
