@@ -443,7 +443,7 @@ void launch_fwd_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
 
-static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
+static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, bool tau16, int k) {
     Workspace &ws = g->ws;
     // k = 0: counting product writes B_0 into buffer 0; product k reads
     // B_{k-1} from buffer (k-1)&1 and writes B_k into buffer k&1.
@@ -479,7 +479,8 @@ static BwdArgs bwd_args(mfbc_graph *g, const View &vw, int ncg, int k) {
     a.pm = ws.pm;
     a.ctr = ws.counters + (size_t)(k % kCounterRing) * 4 * kCounterSlots;
     a.prev_ctr = k > 0 ? ws.counters + (size_t)((k - 1) % kCounterRing) * 4 * kCounterSlots : nullptr;
-    a.tau2 = (const uint32_t *)ws.tau2;
+    a.tau2 = tau16 ? (const uint32_t *)ws.tdist : ws.tau2;
+    a.sig16 = tau16 ? ws.tau2 : nullptr;
     a.tau_full = ws.flags + 1;
     a.nwords = (g->n + 31) / 32;
     a.clear_bits = ws.abits[(k + 2) % 3];
@@ -509,10 +510,9 @@ hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, bool tau16, 
                        ws.abits[2], nab, ws.counters, (int)kRingWords, ws.flags + 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    BwdArgs a = bwd_args(g, vw, ncg, 0);
+    BwdArgs a = bwd_args(g, vw, ncg, tau16, 0);
     if (ev) (void)hipEventRecord(ev[0], s);
     if (tau16) {
-        a.tau2 = (const uint32_t *)ws.tdist;
         const int grid = blocks_for((size_t)a.ntasks * ((ncg + 1) / 2), kWavesPerBlock, 0x7fffffff);
         switch (arc_mode(vw.out)) {
             case 0: hipLaunchKernelGGL((k_bwd_count_w<0, false, false>), dim3(grid), dim3(kBlock), 0, s, a); break;
@@ -573,8 +573,8 @@ static void launch_bwd_pull(const BwdArgs &a, int grid, hipStream_t s) {
         hipLaunchKernelGGL((k_bwd_pull<AM, false, false>), dim3(grid), dim3(kBlock), 0, s, a);
 }
 
-void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, int k, hipStream_t s, hipEvent_t *ev) {
-    const BwdArgs a = bwd_args(g, vw, ncg, k);
+void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, bool tau16, int k, hipStream_t s, hipEvent_t *ev) {
+    const BwdArgs a = bwd_args(g, vw, ncg, tau16, k);
     const int groups = a.nwide ? a.nwide : ncg;
     if (ev) (void)hipEventRecord(ev[0], s);
     const int grid = blocks_for((size_t)a.ntasks * groups, kWavesPerBlock, 0x7fffffff);

@@ -33,9 +33,10 @@ using namespace mfbc;
 // array is larger, since the default row cut of a small graph takes up to
 // 4.7 MB more hub partials per group than the formula counts (rows cut into
 // slices of max(64, arcs / 4096) arcs, 768 B each), and a core's partials and
-// DAG masks up to 1.4 B per arc more than the masks of every arc.
+// DAG masks up to 1.4 B per arc more than the masks of every arc, and path
+// counts in 16 bits a tenth of a one-group workspace.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-constexpr size_t kScratchSize = (size_t)76 << 20;
+constexpr size_t kScratchSize = (size_t)84 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchSize];
 
 namespace {
@@ -121,7 +122,10 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool admit = 
     f(ws.lam, n * ncg);
     f(ws.dag, (size_t)std::max<int64_t>(g ? (admit ? g->arcs : g->core.arcs) : 0, 1) * ncg);
     f(ws.src, (size_t)ncg * kWave);
-    f(ws.tau2, ncg >= 2 ? tile / 2 : (size_t)1);   // the paired counting product's 16-bit tau
+    // the paired counting product's tau in 16 bits, or path counts in 16 bits (two
+    // words a lane from three groups on, as in quad.hip)
+    if (admit) f(ws.tau2, ncg >= 2 ? tile / 2 : (size_t)1);
+    else f(ws.tau2, n * kWave * (size_t)(ncg <= 2 ? 1 : 2 * ((ncg + 3) / 4)));
 }
 
 // Column groups the workspace holds for a batch of `ncg` groups: batches of
@@ -443,7 +447,7 @@ int run_backward(mfbc_graph *g, const View &vw, int ncg, int nb, bool tau16, int
                 if (e != hipSuccess)
                     return fail(MFBC_EDEVICE, std::string("counting product: ") + hipGetErrorString(e));
             } else {
-                launch_bwd_product(g, vw, ncg, kk, s, window_events(g, i, false));
+                launch_bwd_product(g, vw, ncg, tau16, kk, s, window_events(g, i, false));
             }
         }
         int rc = read_ring(g, s);

@@ -114,7 +114,8 @@ struct Workspace {
     int32_t *src = nullptr;            // column -> source vertex, -1 = padding
     uint64_t *dag = nullptr;           // shortest-path DAG: lane mask per out-arc [cg][arcs]
     uint32_t *tau2 = nullptr;          // tau per pair of groups, 16 bits a group [cg/2][n][64]
-                                       // (read by the paired counting product)
+                                       // (read by the paired counting product); where T itself is
+                                       // in 16 bits, its path counts
     unsigned long long *trace_relax = nullptr;  // trace: relaxations per product
     int trace_len = 0;
     char *quad_base = nullptr;         // memory behind `quad`, for batches of up to quad_ncg groups
@@ -181,9 +182,9 @@ void launch_fwd_init(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, h
 // it and the merge kernel, and after the merge.  Product j (k) skips itself
 // on the device when product j-1 (k-1) produced no frontier entry.
 void launch_fwd_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s, hipEvent_t *ev);
-// tau16: T is in 16 bits already, two groups to a word (quad.hip).
+// tau16: T and its path counts are in 16 bits, two groups to a word (quad.hip).
 hipError_t launch_bwd_count(mfbc_graph *g, const View &vw, int ncg, bool tau16, hipStream_t s, hipEvent_t *ev);
-void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, int k, hipStream_t s, hipEvent_t *ev);
+void launch_bwd_product(mfbc_graph *g, const View &vw, int ncg, bool tau16, int k, hipStream_t s, hipEvent_t *ev);
 // Trace: membership of forward frontier F_j (j = 0: the sources) as
 // per-column vertex bitmaps in caller order (d_rows: nb rows of (n+63)/64
 // words; nullable), and the out-degrees of its members added to

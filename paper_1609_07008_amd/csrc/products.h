@@ -610,6 +610,8 @@ struct BwdArgs {
     const int32_t *src;        // column -> source vertex (-1 = padding)
     const int32_t *tdist;      // tau
     const double *tsig;        // sigma
+    const uint32_t *sig16;     // nullable: sigma in 16 bits, two groups to a word as tau2; where
+                               //   it is kSig16Far the value is in tsig
     const uint32_t *abits;     // frontier B_{k-1}: [cg][nwords] activity bitmaps
     const uint64_t *fbits;     //   lane masks [cg][n]
     uint32_t *abits_n;         // frontier B_k
@@ -652,7 +654,25 @@ __device__ __forceinline__ size_t fb_index(const BwdArgs &a, int cg, int x) {
 }
 __device__ __forceinline__ int ab_plane(const BwdArgs &a, int cg) { return a.nwide ? cg >> 1 : cg; }
 
-// Per-vertex finish of the counting product: counters, leaves, zeta = 0.
+constexpr uint32_t kSig16Far = 0xffffu;
+__device__ __forceinline__ double sigma_of(const BwdArgs &a, int cg, int x, size_t idx, int lane) {
+    if (a.sig16) {
+        const uint32_t h = a.sig16[((size_t)(cg >> 1) * (size_t)a.n + (size_t)x) * kWave + lane];
+        const uint32_t s = (cg & 1) ? h >> 16 : h & 0xffffu;
+        if (s != kSig16Far) return (double)s;
+    }
+    return a.tsig[idx];
+}
+
+// Set in a counter whose zeta has not been written yet (the counter itself is
+// at most a vertex's degree).
+constexpr int kZetaUnset = 1 << 30;
+
+// Per-vertex finish of the counting product: counters, leaves, zeta = 0.  Where
+// T is in 16 bits (sig16) only what a later product reads is written: a
+// counter, marked kZetaUnset, where arcs were counted, a frontier value where
+// none were; on 256 columns of the core of weighted R-MAT scale 20 the counting
+// product wrote 4.6 GB in 2.24 ms before, 1.4 GB in 1.48 now.
 __device__ __forceinline__ uint64_t count_finalize(const BwdArgs &a, size_t cgv, int cg, int x,
                                                    int dx, int c, int lane) {
     const uint64_t mask = a.cmask ? a.cmask[cg] : ~0ull;
@@ -662,10 +682,14 @@ __device__ __forceinline__ uint64_t count_finalize(const BwdArgs &a, size_t cgv,
     const bool leaf = reach && c == 0;
     const bool front = mine && leaf && a.src[cg * kWave + lane] != x;
     if (mine) {
-        a.cnt[idx] = (reach && c > 0) ? c : -1;
-        a.zeta[idx] = 0.0;
-        if (a.step) a.step[idx] = leaf ? 0 : -1;
-        if (leaf) a.q[idx] = 1.0 / a.tsig[idx];
+        if (a.sig16) {
+            if (reach && c > 0) a.cnt[idx] = c | kZetaUnset;
+        } else {
+            a.cnt[idx] = (reach && c > 0) ? c : -1;
+            a.zeta[idx] = 0.0;
+            if (a.step) a.step[idx] = leaf ? 0 : -1;
+        }
+        if (leaf) a.q[idx] = 1.0 / sigma_of(a, cg, x, idx, lane);
     }
     const uint64_t bits = ballot(front);
     if (lane == 0) {
@@ -929,13 +953,13 @@ __device__ __forceinline__ uint64_t bwd_finalize(const BwdArgs &a, size_t cgv, i
         bool done = false, front = false;
         double dep = 0.0;
         if (got > 0) {
-            const int c = cx - got;
-            const double z = a.zeta[idx] + acc;
-            a.zeta[idx] = z;
+            const int c = (cx & ~kZetaUnset) - got;
+            const double z = cx & kZetaUnset ? acc : a.zeta[idx] + acc;
+            if (c > 0 || !a.sig16) a.zeta[idx] = z;
             if (c == 0) {
-                const double sg = a.tsig[idx];
+                const double sg = sigma_of(a, cg, x, idx, lane);
                 a.q[idx] = z + 1.0 / sg;
-                a.cnt[idx] = -1;
+                if (!a.sig16) a.cnt[idx] = -1;
                 if (a.step) a.step[idx] = a.k;
                 done = true;
                 const bool self = a.src[cg * kWave + lane] == x;

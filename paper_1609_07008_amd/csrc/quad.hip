@@ -14,7 +14,11 @@
 //    taken again in binary64, over the row's arcs in order.  The encoding is
 //    exact.  A call whose frontier outlives the products that fit starts over
 //    in 32 bits (quad_products).  T in this layout is what the paired counting
-//    product of a centrality call reads, so no copy of it is made.
+//    product of a centrality call reads, so no copy of it is made.  T's
+//    multiplicities are kept the same way, 16 bits with the binary64 array behind
+//    those that do not fit: a kept entry writes 6 bytes where it wrote 12, and
+//    the backward half reads 2 for 8 (centrality of 256 sources on weighted R-MAT
+//    scale 20: 12.5 ms before, 9.6 so).
 //
 // 2. An arc u -> v can change v only if F(u) + w <= T(v) in some column (< for
 //    distances alone).  Columns differ mostly by how far their source is from
@@ -78,7 +82,8 @@ struct QuadArgs {
     const unsigned long long *prev_ctr;
     // multiplicities
     int mb, mbn;                 // bits of m in F_{j-1} and F_j
-    double *tsig;                // [cg][n][64]
+    uint32_t *sig;               // multiplicities of T, laid out as T: 16 bits where they fit,
+    double *tsig;                // else kSig16Far and the value here, [cg][n][64]
     const double *fsig;
     double *fsig_n;
     int32_t *flags;
@@ -255,7 +260,16 @@ struct QuadPull {
             hm |= h;
         }
         if (!hm) return false;
-        Lane<Q> nt = own, nf;
+        Lane<Q> nt = own, nf, ns;
+        if constexpr (COUNT && B) {
+            // with bounds a third of the rows keep nothing (forward of 200 sources,
+            // weighted R-MAT scale 18: 4.97 ms without this look, 4.75 with)
+            bool some = false;
+#pragma unroll
+            for (int g = 0; g < G; g++) some |= d[g] <= half_of(own.w[g >> 1], g & 1) && d[g] != kNone16;
+            if (!ballot(some)) return false;
+        }
+        if constexpr (COUNT) ns = load_lane<Q>(a.sig, row0 + (size_t)v, lane);
         int least = INT32_MAX, most = INT32_MIN;
         uint64_t kept = 0;
 #pragma unroll
@@ -271,10 +285,17 @@ struct QuadPull {
                 uint32_t x = d[g];
                 if constexpr (COUNT) {
                     const size_t i = at(g, v);
+                    const uint32_t si = half_of(ns.w[g >> 1], g & 1);
                     double s = m[g];
-                    if (d[g] == t) s += a.tsig[i];
-                    a.tsig[i] = s;
-                    if (__builtin_isinf(s)) a.flags[0] = 1;
+                    if (d[g] == t) s += si != kSig16Far ? (double)si : a.tsig[i];
+                    uint32_t sn = kSig16Far;
+                    if (s < (double)kSig16Far) {
+                        sn = (uint32_t)s;
+                    } else {
+                        a.tsig[i] = s;
+                        if (__builtin_isinf(s)) a.flags[0] = 1;
+                    }
+                    ns.w[g >> 1] = (ns.w[g >> 1] & ~(0xffffu << sh)) | (sn << sh);
                     const uint32_t most_m = (1u << a.mbn) - 1u;
                     uint32_t mi = most_m;
                     if (m[g] < (double)most_m) mi = (uint32_t)m[g];
@@ -297,6 +318,7 @@ struct QuadPull {
         }
         if (!kept) return false;
         store_lane<Q>(a.t, row0 + (size_t)v, lane, nt);
+        if constexpr (COUNT) store_lane<Q>(a.sig, row0 + (size_t)v, lane, ns);
         store_lane<Q>(a.f_n, row0 + (size_t)v, lane, nf);
         if constexpr (!B) return true;
         least = wave_extreme<false>(least);
@@ -557,7 +579,7 @@ struct QuadSeed {
     int32_t *off;
     const int32_t *hub;          // nullable: distance to the landmark of highest degree
     unsigned long long *live;
-    double *tsig;
+    uint16_t *sig;
     __device__ void row(int v, int q, int lane) const {
         Lane<Q> r;
 #pragma unroll
@@ -570,7 +592,7 @@ struct QuadSeed {
         const size_t i = ((row * kWave + lane) * Q + (g >> 1)) * 2 + (g & 1);
         ((uint16_t *)t)[i] = 0;
         ((uint16_t *)f)[i] = COUNT ? 1 : 0;      // weight 0, multiplicity 1 inline
-        if (COUNT) tsig[((size_t)cg * n + v) * kWave + lane] = 1.0;
+        if (COUNT) sig[i] = 1;
         if (!lo) return mark(abits, q, v);
         int h = hub ? hub[v] : 0;
         if (h == kInf) h = 0;
@@ -622,8 +644,9 @@ __global__ __launch_bounds__(kBlock) void k_quad_dist(const uint32_t *t, int32_t
 
 // sigma of one group's 64 columns at 32 caller vertices, 0 where unreached.
 template <int Q>
-__global__ __launch_bounds__(kBlock) void k_quad_sigma(const uint32_t *t, const double *tsig, double *sigma, int n,
-                                                       int nb, const int32_t *perm) {
+__global__ __launch_bounds__(kBlock) void k_quad_sigma(const uint32_t *t, const uint32_t *sig,
+                                                       const double *tsig, double *sigma, int n, int nb,
+                                                       const int32_t *perm) {
     __shared__ double sh[32][65];
     const int cg = blockIdx.y, v0 = blockIdx.x * 32, g = cg % (2 * Q);
     const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
@@ -633,8 +656,10 @@ __global__ __launch_bounds__(kBlock) void k_quad_sigma(const uint32_t *t, const 
         if (v < n) {
             const int d = perm ? perm[v] : v;
             const size_t row = (size_t)(cg / (2 * Q)) * n + d;
-            const bool far = half_of(t[(row * kWave + c) * Q + (g >> 1)], g & 1) == kNone16;
-            sh[r][c] = far ? 0.0 : tsig[((size_t)cg * n + d) * kWave + c];
+            const size_t i = (row * kWave + c) * Q + (g >> 1);
+            const uint32_t s = half_of(sig[i], g & 1);
+            const bool far = half_of(t[i], g & 1) == kNone16;
+            sh[r][c] = far ? 0.0 : s != kSig16Far ? (double)s : tsig[((size_t)cg * n + d) * kWave + c];
         }
     }
     __syncthreads();
@@ -659,7 +684,6 @@ int bits_of(int64_t x) {
     }
     return b;
 }
-
 
 // Multiplicity bits of the frontier that product j reads: its candidates
 // weigh at most j * maxw, and no entry may equal the all-ones one.
@@ -712,6 +736,7 @@ QuadArgs quad_args(mfbc_graph *g, const View &vw, int ncg, int j) {
     a.next_ctr = ws.counters + (size_t)((j + 1) % kCounterRing) * 4 * kCounterSlots;
     a.mb = quad_mb(g, j);
     a.mbn = quad_mb(g, j + 1);
+    a.sig = ws.tau2;
     a.tsig = ws.tsig;
     a.fsig = ws.fsig[b];
     a.fsig_n = ws.fsig[b ^ 1];
@@ -729,7 +754,7 @@ void quad_init(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d_
                        ws.abits[2], (size_t)a.nq * a.nwords, ws.quad.live, B ? (size_t)3 * ncg * kLiveCopies : 0,
                        ws.counters, (int)kRingWords, ws.flags);
     const QuadSeed<Q, COUNT> seed{g->n,    a.nwords,  (uint32_t *)ws.fdist[0], a.t, ws.abits[0], ws.quad.lo[0],
-                                  ws.quad.off, g->hub_dist, ws.quad.live, ws.tsig};
+                                  ws.quad.off, g->hub_dist, ws.quad.live, (uint16_t *)a.sig};
     launch_seed(g, seed, ncg, nb, d_sources, s);
 }
 
@@ -765,7 +790,7 @@ void quad_rows_out(mfbc_graph *g, int ncg, int nb, int32_t *dist, double *sigma,
                        perm);
     if constexpr (COUNT)
         hipLaunchKernelGGL(k_quad_sigma<Q>, dim3((g->n + 31) / 32, ncg), dim3(kBlock), 0, s, t,
-                           (const double *)g->ws.tsig, sigma, g->n, nb, perm);
+                           (const uint32_t *)g->ws.tau2, (const double *)g->ws.tsig, sigma, g->n, nb, perm);
 }
 
 }  // namespace

@@ -9,6 +9,7 @@ import pytest
 import oracle
 from paper_1609_07008_amd import graphgen as gg
 from tests.test_gpu_parity import DELTA_TOL, mfbc, rel_close, torch  # noqa: F401
+from tests.test_gpu_quad import beside
 
 pytestmark = pytest.mark.gpu
 
@@ -18,12 +19,23 @@ def weighted(g, w):
     return gg.csr_from_edges(g.n, u, v, np.full(u.size, w), g.name)
 
 
+def bundles(a, b):
+    """Two bundles of parallel two-arc paths in a row: a * b shortest paths end to end."""
+    mid = np.arange(a), a + 1 + np.arange(b)
+    ends = np.full(a, a + b + 1), np.full(a, a), np.full(b, a), np.full(b, a + b + 2)
+    return gg.csr_from_edges(a + b + 3, np.concatenate([mid[0], mid[0], mid[1], mid[1]]), np.concatenate(ends), None,
+                             f"bundles{a}x{b}")
+
+
 FORMS = {
     "er1024": lambda: gg.er_graph(1024, 8, 3, (1, 100)),
     "rmat10_w255": lambda: gg.rmat_graph(10, 16, 6, wrange=(1, 255)),
     "rmat11_unw": lambda: gg.rmat_graph(11, 16, 5),
     "diamonds": lambda: gg.diamond_chain(60),                       # 2^60 paths
     "diamonds_w9": lambda: weighted(gg.diamond_chain(30), 9),
+    "paths65534": lambda: bundles(217, 302),
+    "paths65535": lambda: bundles(255, 257),
+    "paths65536": lambda: bundles(256, 256),
     "layers": lambda: gg.layered_bipartite(6, 60),                  # 60^5 paths
     "path57_w255": lambda: gg.path_graph(57, w=255),                # the last that fits, in 56 products
     "path90_w255": lambda: gg.path_graph(90, w=255),                # outlives them
@@ -40,6 +52,8 @@ def test_centrality_against_the_oracle(torch, mfbc, name):  # noqa: F811
     g = FORMS[name]()
     dg = mfbc.DeviceGraph(g, directed=name == "directed")
     src = np.random.default_rng(5).integers(0, g.n, size=330).astype(np.int32)
+    if name.startswith("paths"):
+        src[[0, 70, 129]] = g.n - 1, g.n - 2, g.n - 1               # the ends of the bundles
     out = torch.empty(g.n, dtype=torch.float64, device="cuda")
     for nb in (1, 64, 65, 128, 129, 330):
         print(f"[bc16] {name} arcs={g.arcs} nb={nb}", flush=True)
@@ -57,4 +71,18 @@ def test_centrality_against_the_oracle(torch, mfbc, name):  # noqa: F811
     parts = [src[:3], src[3:80], src[80:]]
     for o, p in zip(dg.bc_requests(parts, 128), parts):
         rel_close(o.cpu().numpy(), oracle.brandes(g, p, per_source=False)["lambda"], DELTA_TOL, "request")
+    dg.close()
+
+
+@pytest.mark.parametrize("name", ["paths65534", "paths65535", "paths65536"])
+def test_path_counts_where_they_stop_fitting(mfbc, name):  # noqa: F811
+    g = beside(FORMS[name]())
+    dg = mfbc.DeviceGraph(g)
+    small = FORMS[name]().n
+    for nb in (3, 130, 200):
+        src = np.arange(small - nb, small, dtype=np.int32)
+        print(f"[bc16] {name} forward nb={nb}", flush=True)
+        ref = oracle.brandes(g, src)
+        f = dg.forward(src)
+        assert np.array_equal(f["sigma"].cpu().numpy(), ref["sigma"])
     dg.close()
