@@ -30,7 +30,9 @@ def bundles(a, b):
 FORMS = {
     "er1024": lambda: gg.er_graph(1024, 8, 3, (1, 100)),
     "rmat10_w255": lambda: gg.rmat_graph(10, 16, 6, wrange=(1, 255)),
-    "rmat11_unw": lambda: gg.rmat_graph(11, 16, 5),
+    "rmat11_unw": lambda: gg.rmat_graph(11, 16, 5),                 # rows that every column has reached
+    "hubs_unw": lambda: gg.rmat_graph(12, 48, 9, (0.7, 0.1, 0.1, 0.1)),
+    "directed_unw": lambda: gg.directed_rmat_graph(10, 24, 12),
     "diamonds": lambda: gg.diamond_chain(60),                       # 2^60 paths
     "diamonds_w9": lambda: weighted(gg.diamond_chain(30), 9),
     "paths65534": lambda: bundles(217, 302),
@@ -50,7 +52,7 @@ FORMS = {
 @pytest.mark.parametrize("name", list(FORMS))
 def test_centrality_against_the_oracle(torch, mfbc, name):  # noqa: F811
     g = FORMS[name]()
-    dg = mfbc.DeviceGraph(g, directed=name == "directed")
+    dg = mfbc.DeviceGraph(g, directed=name.startswith("directed"))
     src = np.random.default_rng(5).integers(0, g.n, size=330).astype(np.int32)
     if name.startswith("paths"):
         src[[0, 70, 129]] = g.n - 1, g.n - 2, g.n - 1               # the ends of the bundles
