@@ -175,7 +175,11 @@ __global__ void k_lambda_reduce_lanes(LanePtrs p, int nlanes, int ncg, int n, do
 
 // Tile transposes between [cg][v][64] tiles (device numbering) and
 // source-major rows [s][v] (caller numbering), 64 x 64 per block through LDS
-// (padded against bank conflicts).  A block covers 64 consecutive caller
+// (padded against bank conflicts).  A thread's loads are issued together, past
+// the last vertex or column at the last one's address: behind a test each they
+// waited for one another (64-column binary64 rows to tiles at n = 262,144: 202 us
+// for three groups before, 148 so; tiles of a graph of 300 vertices to rows: 11
+// and 7.6).  A block covers 64 consecutive caller
 // vertices: the row side stays coalesced, the tile side moves whole 256-B
 // tile rows.
 template <typename T>
@@ -184,12 +188,15 @@ __global__ __launch_bounds__(kBlock) void k_tiles_to_rows(const T *tiles, T *row
     __shared__ T sh[64][65];
     const int cg = blockIdx.y, v0 = blockIdx.x * 64;
     const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
-    for (int r = r0; r < 64; r += 4) {
-        const int v = v0 + r;
-        if (v < n) sh[r][c] = tiles[((size_t)cg * n + dev_id(perm, v)) * 64 + c];
-    }
+    T x[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) x[i] = tiles[((size_t)cg * n + dev_id(perm, min(v0 + r0 + 4 * i, n - 1))) * 64 + c];
+#pragma unroll
+    for (int i = 0; i < 16; i++) sh[r0 + 4 * i][c] = x[i];
     __syncthreads();
-    for (int r = r0; r < 64; r += 4) {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int r = r0 + 4 * i;
         const int s = cg * 64 + r, v = v0 + c;
         if (s < nb && v < n) rows[(size_t)s * n + v] = sh[c][r];
     }
@@ -202,15 +209,20 @@ __global__ __launch_bounds__(kBlock) void k_sigma_rows(const double *tsig, const
     __shared__ double sh[64][65];
     const int cg = blockIdx.y, v0 = blockIdx.x * 64;
     const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
-    for (int r = r0; r < 64; r += 4) {
-        const int v = v0 + r;
-        if (v < n) {
-            const size_t idx = ((size_t)cg * n + dev_id(perm, v)) * 64 + c;
-            sh[r][c] = tdist[idx] != kInf ? tsig[idx] : 0.0;
-        }
+    double x[16];
+    int t[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const size_t idx = ((size_t)cg * n + dev_id(perm, min(v0 + r0 + 4 * i, n - 1))) * 64 + c;
+        x[i] = tsig[idx];
+        t[i] = tdist[idx];
     }
+#pragma unroll
+    for (int i = 0; i < 16; i++) sh[r0 + 4 * i][c] = t[i] != kInf ? x[i] : 0.0;
     __syncthreads();
-    for (int r = r0; r < 64; r += 4) {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int r = r0 + 4 * i;
         const int s = cg * 64 + r, v = v0 + c;
         if (s < nb && v < n) rows[(size_t)s * n + v] = sh[c][r];
     }
@@ -222,12 +234,15 @@ __global__ __launch_bounds__(kBlock) void k_rows_to_tiles(const T *rows, T *tile
     __shared__ T sh[64][65];
     const int cg = blockIdx.y, v0 = blockIdx.x * 64;
     const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
-    for (int r = r0; r < 64; r += 4) {
-        const int s = cg * 64 + r, v = v0 + c;
-        sh[c][r] = (s < nb && v < n) ? rows[(size_t)s * n + v] : pad;
-    }
+    T x[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) x[i] = rows[(size_t)min(cg * 64 + r0 + 4 * i, nb - 1) * n + min(v0 + c, n - 1)];
+#pragma unroll
+    for (int i = 0; i < 16; i++) sh[c][r0 + 4 * i] = cg * 64 + r0 + 4 * i < nb ? x[i] : pad;
     __syncthreads();
-    for (int r = r0; r < 64; r += 4) {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int r = r0 + 4 * i;
         const int v = v0 + r;
         if (v < n) tiles[((size_t)cg * n + dev_id(perm, v)) * 64 + c] = sh[r][c];
     }
@@ -238,22 +253,29 @@ __global__ __launch_bounds__(kBlock) void k_delta_rows(const double *zeta, const
                                                        const int32_t *tdist, const int32_t *src,
                                                        double *rows, int n, int nb,
                                                        const int32_t *perm) {
-    __shared__ double sh[64][65];
-    const int cg = blockIdx.y, v0 = blockIdx.x * 64;
+    __shared__ double sh[32][65];
+    const int cg = blockIdx.y, v0 = blockIdx.x * 32;
     const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
-    for (int r = r0; r < 64; r += 4) {
-        const int v = v0 + r;
-        if (v < n) {
-            const int d = dev_id(perm, v);
-            const size_t idx = ((size_t)cg * n + d) * 64 + c;
-            const bool ok = tdist[idx] != kInf && src[cg * 64 + c] != d;
-            sh[r][c] = ok ? zeta[idx] * tsig[idx] : 0.0;
-        }
+    const int me = src[cg * 64 + c];
+    double z[8], x[8];
+    int t[8];
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        const int d = dev_id(perm, min(v0 + r0 + 4 * i, n - 1));
+        const size_t idx = ((size_t)cg * n + d) * 64 + c;
+        z[i] = zeta[idx];
+        x[i] = tsig[idx];
+        t[i] = me != d ? tdist[idx] : kInf;
     }
+#pragma unroll
+    for (int i = 0; i < 8; i++) sh[r0 + 4 * i][c] = t[i] != kInf ? z[i] * x[i] : 0.0;
     __syncthreads();
-    for (int r = r0; r < 64; r += 4) {
-        const int s = cg * 64 + r, v = v0 + c;
-        if (s < nb && v < n) rows[(size_t)s * n + v] = sh[c][r];
+    const int vl = threadIdx.x & 31, v = v0 + vl;
+    if (v >= n) return;
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        const int l = (int)(threadIdx.x >> 5) + 8 * i, s = cg * 64 + l;
+        if (s < nb) rows[(size_t)s * n + v] = sh[vl][l];
     }
 }
 
@@ -669,7 +691,7 @@ void launch_import_forward(mfbc_graph *g, int ncg, int nb, const int32_t *d_dist
 void launch_export_backward(mfbc_graph *g, int ncg, int nb, double *d_delta, int32_t *d_step,
                             hipStream_t s) {
     dim3 grid((g->n + 63) / 64, ncg);
-    hipLaunchKernelGGL(k_delta_rows, grid, dim3(kBlock), 0, s, (const double *)g->ws.fsig[0],
+    hipLaunchKernelGGL(k_delta_rows, dim3((g->n + 31) / 32, ncg), dim3(kBlock), 0, s, (const double *)g->ws.fsig[0],
                        (const double *)g->ws.tsig, (const int32_t *)g->ws.tdist,
                        (const int32_t *)g->ws.src, d_delta, g->n, nb, (const int32_t *)g->perm);
     if (d_step)

@@ -653,57 +653,65 @@ __global__ __launch_bounds__(kBlock) void k_quad_dist(const uint32_t *t, int32_t
     __shared__ uint32_t sh[64][65];              // [vertex][lane]: the word
     const int wd = blockIdx.y, v0 = blockIdx.x * 64;
     const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+    uint32_t x[16];
 #pragma unroll
     for (int i = 0; i < 16; i++) {
-        const int r = r0 + 4 * i, v = v0 + r;
-        if (v < n) {
-            const size_t row = (size_t)(wd / Q) * n + (perm ? perm[v] : v);
-            sh[r][c] = t[(row * kWave + c) * Q + wd % Q];
-        }
+        const int u = min(v0 + r0 + 4 * i, n - 1);
+        x[i] = t[(((size_t)(wd / Q) * n + (perm ? perm[u] : u)) * kWave + c) * Q + wd % Q];
     }
+#pragma unroll
+    for (int i = 0; i < 16; i++) sh[r0 + 4 * i][c] = x[i];
     __syncthreads();
     const int v = v0 + c;
     if (v >= n) return;
 #pragma unroll
     for (int i = 0; i < 16; i++) {
         const int l = r0 + 4 * i;
-        const uint32_t x = sh[c][l];
+        const uint32_t word = sh[c][l];
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             const int s = (2 * wd + h) * kWave + l;
-            const uint32_t d = half_of(x, h);
+            const uint32_t d = half_of(word, h);
             if (s < nb) dist[(size_t)s * n + v] = d == kNone16 ? kInf : (int32_t)d;
         }
     }
 }
 
-// sigma of one group's 64 columns at 32 caller vertices, 0 where unreached.
+// sigma of one word's 128 columns at 64 caller vertices, 0 where unreached: the
+// tile holds the 16-bit counts, those past them are read where they are written.
 template <int Q>
-__global__ __launch_bounds__(kBlock) void k_quad_sigma(const uint32_t *t, const uint32_t *sig,
-                                                       const double *tsig, double *sigma, int n, int nb,
-                                                       const int32_t *perm) {
-    __shared__ double sh[32][65];
-    const int cg = blockIdx.y, v0 = blockIdx.x * 32, g = cg % (2 * Q);
+__global__ __launch_bounds__(kBlock) void k_quad_sigma(const uint32_t *t, const uint32_t *sig, const double *tsig,
+                                                       double *sigma, int n, int nb, const int32_t *perm) {
+    __shared__ uint32_t sh[64][65];              // [vertex][lane]: the word
+    const int wd = blockIdx.y, v0 = blockIdx.x * 64;
     const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+    uint32_t d[16], m[16];
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const int r = r0 + 4 * i, v = v0 + r;
-        if (v < n) {
-            const int d = perm ? perm[v] : v;
-            const size_t row = (size_t)(cg / (2 * Q)) * n + d;
-            const size_t i = (row * kWave + c) * Q + (g >> 1);
-            const uint32_t s = half_of(sig[i], g & 1);
-            const bool far = half_of(t[i], g & 1) == kNone16;
-            sh[r][c] = far ? 0.0 : s != kSig16Far ? (double)s : tsig[((size_t)cg * n + d) * kWave + c];
-        }
+    for (int i = 0; i < 16; i++) {
+        const int u = min(v0 + r0 + 4 * i, n - 1);
+        const size_t at = (((size_t)(wd / Q) * n + (perm ? perm[u] : u)) * kWave + c) * Q + wd % Q;
+        d[i] = t[at];
+        m[i] = sig[at];
     }
-    __syncthreads();
-    const int vl = threadIdx.x & 31, v = v0 + vl;
-    if (v >= n) return;
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const int l = (int)(threadIdx.x >> 5) + 8 * i, s = cg * kWave + l;
-        if (s < nb) sigma[(size_t)s * n + v] = sh[vl][l];
+    for (int i = 0; i < 16; i++)
+        sh[r0 + 4 * i][c] = ((d[i] & 0xffffu) == kNone16 ? 0u : m[i] & 0xffffu) |
+                            ((d[i] >> 16) == kNone16 ? 0u : m[i] & 0xffff0000u);
+    __syncthreads();
+    const int v = v0 + c;
+    if (v >= n) return;
+    const size_t dv = perm ? perm[v] : v;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int l = r0 + 4 * i;
+        const uint32_t word = sh[c][l];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int cg = 2 * wd + h, s = cg * kWave + l;
+            const uint32_t x = half_of(word, h);
+            if (s < nb)
+                sigma[(size_t)s * n + v] = x != kSig16Far ? (double)x : tsig[((size_t)cg * n + dv) * kWave + l];
+        }
     }
 }
 
@@ -827,7 +835,7 @@ void quad_rows_out(mfbc_graph *g, int ncg, int nb, int32_t *dist, double *sigma,
     hipLaunchKernelGGL(k_quad_dist<Q>, dim3((g->n + 63) / 64, (ncg + 1) / 2), dim3(kBlock), 0, s, t, dist, g->n, nb,
                        perm);
     if constexpr (COUNT)
-        hipLaunchKernelGGL(k_quad_sigma<Q>, dim3((g->n + 31) / 32, ncg), dim3(kBlock), 0, s, t,
+        hipLaunchKernelGGL(k_quad_sigma<Q>, dim3((g->n + 63) / 64, (ncg + 1) / 2), dim3(kBlock), 0, s, t,
                            (const uint32_t *)g->ws.tau2, (const double *)g->ws.tsig, sigma, g->n, nb, perm);
 }
 
