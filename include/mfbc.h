@@ -309,7 +309,11 @@ typedef struct mfbc_stats {
     int64_t fwd_entries;    /* frontier entries produced, forward          */
     int64_t bwd_entries;    /* frontier entries produced, backward         */
     int64_t batches;
-    int64_t fwd_outputs;
+    int64_t fwd_outputs;    /* entries that received a candidate; like the
+                             * counts below, over the arcs that the products
+                             * read (centrality: those that can lie on a
+                             * shortest path; batches that run as one wide
+                             * batch share their products)                 */
     int64_t bwd_outputs;
     int64_t fwd_active_vertices;
     int64_t fwd_active_arcs;
@@ -354,13 +358,17 @@ int mfbc_graph_info(const mfbc_graph *g, int32_t *n, int64_t *n_arcs,
                     int32_t *max_weight);
 
 /*
- * mfbc_bc_many -- batched form: MFBC over many independent graphs in one
- * persistent launch.  Each workgroup takes (graph, job_width-source) jobs
- * from a device queue and runs Algorithms 1-3 for its job with no host
- * round trip per product; jobs are issued largest first.  Per graph the
- * result equals mfbc_bc(graphs[i], d_sources[i], h_n_sources[i], job_width,
- * d_bc[i]) up to rounding (the per-job parts are summed in job order, so
- * repeated calls with one configuration are bitwise identical).
+ * mfbc_bc_many -- batched form: MFBC over many independent graphs.  Many
+ * small graphs run in one persistent launch: each workgroup takes (graph,
+ * job_width-source) jobs from a device queue and runs Algorithms 1-3 for its
+ * job with no host round trip per product; jobs are issued largest first.
+ * Few or large graphs, which would leave most workgroups idle, run one after
+ * another on up to four streams of the library in wide batches, under the
+ * library's own work decomposition (config and mfbc_set_plan shape the
+ * persistent launch alone).  Per graph the result equals mfbc_bc(graphs[i],
+ * d_sources[i], h_n_sources[i], job_width, d_bc[i]) up to rounding (parts are
+ * summed in a fixed order, so repeated calls with one configuration are
+ * bitwise identical).
  *   graphs[n_graphs]      host array of loaded graphs (same device).
  *   d_sources[n_graphs]   host array of device pointers to each graph's
  *                         source list; h_n_sources[n_graphs] their lengths.
@@ -377,7 +385,8 @@ int mfbc_graph_info(const mfbc_graph *g, int32_t *n, int64_t *n_arcs,
  *                         128 runs the paired products (one gather per arc
  *                         for both column groups) at twice the state per
  *                         workgroup.
- *   h_stats (nullable)    out: products over all jobs.
+ *   h_stats (nullable)    out: products over all jobs (over all batches
+ *                         where the graphs run on streams).
  * The library keeps a grow-only workspace per device for this call, shared
  * by every call on that device: calls on one device must not overlap (one
  * host thread at a time), and the graphs of a call follow the one-thread rule

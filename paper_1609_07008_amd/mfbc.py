@@ -300,7 +300,7 @@ class DeviceGraph:
 
 def bc_many(graphs, sources, block_threads: int = 0, blocks: int = 0, job_width: int = 0,
             outs=None, stream=None):
-    """Batched form: lambda of every graph over its source list, one persistent launch.
+    """Batched form: lambda of every graph over its source list, in one call.
 
     ``graphs``: DeviceGraph list; ``sources``: one int32 source list (numpy
     or CUDA tensor) per graph; ``job_width``: sources per job, 64 or 128
