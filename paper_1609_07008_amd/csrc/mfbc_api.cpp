@@ -802,9 +802,14 @@ int build_core(mfbc_graph *g, hipStream_t s) {
         g->h_core_rp_in = g->h_core_rp_out;
     }
     c.arcs = g->h_core_rp_out.back();
+    rc = plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs, g->full.arcs), c);
+    if (rc) {
+        free_view(c);
+        return rc == MFBC_ENOMEM ? MFBC_OK : rc;
+    }
     g->core = c;
     g->has_core = true;
-    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs, g->full.arcs), g->core);
+    return MFBC_OK;
 }
 
 // Release a lane view: its workspace, counters and events (the device graph
