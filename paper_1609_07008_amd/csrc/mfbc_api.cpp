@@ -166,21 +166,27 @@ void free_csr(Csr &c) {
     c = Csr{};
 }
 
-// (an undirected view holds one orientation and one plan, twice)
+// The plans of both orientations (of an undirected graph one plan, twice).
+void free_plans(Plan &out, Plan &in) {
+    if (in.tasks != out.tasks) free_plan(in);
+    free_plan(out);
+    in = Plan{};
+}
+
+// (an undirected view holds one orientation, twice)
 void free_view(View &v) {
-    if (v.plan_in.tasks != v.plan_out.tasks) free_plan(v.plan_in);
-    free_plan(v.plan_out);
+    free_plans(v.plan_out, v.plan_in);
     if (v.in.rp != v.out.rp) free_csr(v.in);
     free_csr(v.out);
     v = View{};
 }
 
+// Fills an empty plan; what it holds after a failure is the caller's to free.
 int upload_plan(int32_t n, const int64_t *h_rp, const TaskParams &prm, Plan &plan) {
     std::vector<Task> tasks;
     std::vector<Hub> hubs;
     int32_t nslots = 0;
     build_plan(n, h_rp, prm, tasks, hubs, nslots);
-    free_plan(plan);
     int rc;
     if ((rc = dalloc(&plan.tasks, tasks.size()))) return rc;
     if (!hubs.empty() && (rc = dalloc(&plan.hubs, hubs.size()))) return rc;
@@ -620,24 +626,27 @@ int upload_csr(int32_t n, int64_t arcs, const int64_t *rp, const int32_t *col, c
     return MFBC_OK;
 }
 
-// The plans of one view (one for both orientations of an undirected graph).
-int plan_view(int32_t n, bool directed, const std::vector<int64_t> &rp_out, const std::vector<int64_t> &rp_in,
-              const TaskParams &p, View &v) {
-    if (!directed) v.plan_in = Plan{};
-    int rc = upload_plan(n, rp_out.data(), p, v.plan_out);
-    if (!rc && directed) rc = upload_plan(n, rp_in.data(), p, v.plan_in);
-    for (auto [csr, plan] : {std::pair<const Csr *, Plan *>{&v.out, &v.plan_out}, {&v.in, &v.plan_in}}) {
-        if (rc || (plan == &v.plan_in && !directed)) break;
-        if (!(rc = dalloc(&plan->owner, (size_t)rp_out.back()))) launch_plan_owner(*csr, *plan, nullptr);
-    }
-    if (!rc) HIP_TRY(hipGetLastError());
-    if (!rc) HIP_TRY(hipStreamSynchronize(nullptr));
-    if (!directed) v.plan_in = v.plan_out;
+// New plans for the arcs of one view (one for both orientations of an
+// undirected graph); both stay empty on a failure.
+int make_plans(int32_t n, bool directed, const std::vector<int64_t> &rp_out, const std::vector<int64_t> &rp_in,
+               const TaskParams &p, const View &v, Plan &out, Plan &in) {
+    auto fill = [&](const std::vector<int64_t> &rp, const Csr &csr, Plan &plan) {
+        int rc = upload_plan(n, rp.data(), p, plan);
+        if (!rc && !(rc = dalloc(&plan.owner, (size_t)rp.back()))) launch_plan_owner(csr, plan, nullptr);
+        return rc;
+    };
+    int rc = fill(rp_out, v.out, out);
+    if (!rc && directed) rc = fill(rp_in, v.in, in);
+    if (!rc && (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess))
+        rc = fail(MFBC_EDEVICE, "the plan's row bytes could not be written");
+    if (rc) free_plans(out, in);
+    else if (!directed) in = out;
     return rc;
 }
 
 // Work decompositions of both views; knobs <= 0 take the default of the
-// view's own size.
+// view's own size.  The plans in use are replaced once all new ones are
+// there: a failure leaves the graph as it was.
 int plan_views(mfbc_graph *g, const TaskParams &knobs) {
     auto params = [&](bool core) {
         TaskParams p = core ? core_params(g->n, g->core.arcs, g->full.arcs) : default_params(g->n, g->full.arcs);
@@ -647,6 +656,32 @@ int plan_views(mfbc_graph *g, const TaskParams &knobs) {
         if (knobs.slice > 0) p.slice = knobs.slice;
         return p;
     };
+    Plan out, in, core_out, core_in;
+    int rc = make_plans(g->n, g->directed, g->h_rp_out, g->h_rp_in, params(false), g->full, out, in);
+    if (!rc && g->has_core)
+        rc = make_plans(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, params(true), g->core, core_out, core_in);
+    if (rc) {
+        free_plans(out, in);
+        return rc;
+    }
+    // the first plans of the products that run on the core (on every arc where
+    // there is none) are the library's own and stay
+    const bool keep = g->core.plan_out.tasks && !g->own_out.tasks;
+    if (keep) {
+        g->own_out = g->core.plan_out;
+        g->own_in = g->core.plan_in;
+    } else if (g->has_core) {
+        free_plans(g->core.plan_out, g->core.plan_in);
+    }
+    if (g->has_core || !keep) free_plans(g->full.plan_out, g->full.plan_in);
+    g->full.plan_out = out;
+    g->full.plan_in = in;
+    if (g->has_core) {
+        g->core.plan_out = core_out;
+        g->core.plan_in = core_in;
+    } else {
+        g->core = g->full;
+    }
     g->params = params(false);
     // slots of a decomposition with the plain row cut (or the caller's): what
     // mfbc_bc_noalloc counts, whatever the default cut is
@@ -662,13 +697,7 @@ int plan_views(mfbc_graph *g, const TaskParams &knobs) {
         g->scratch_slots = std::max(g->scratch_slots, t);
         if (!g->directed) break;
     }
-    const int rc = plan_view(g->n, g->directed, g->h_rp_out, g->h_rp_in, g->params, g->full);
-    if (!g->has_core) {
-        g->core = g->full;       // also after a failure: no stale pointers
-        return rc;
-    }
-    if (rc) return rc;
-    return plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, params(true), g->core);
+    return MFBC_OK;
 }
 
 // One block of device memory, handed out in parts and freed at the end of
@@ -802,7 +831,8 @@ int build_core(mfbc_graph *g, hipStream_t s) {
         g->h_core_rp_in = g->h_core_rp_out;
     }
     c.arcs = g->h_core_rp_out.back();
-    rc = plan_view(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs, g->full.arcs), c);
+    rc = make_plans(g->n, g->directed, g->h_core_rp_out, g->h_core_rp_in, core_params(g->n, c.arcs, g->full.arcs), c,
+                    c.plan_out, c.plan_in);
     if (rc) {
         free_view(c);
         return rc == MFBC_ENOMEM ? MFBC_OK : rc;
@@ -843,9 +873,7 @@ void free_graph_memory(mfbc_graph *g) {
     g->core = View{};
     g->has_core = false;
     free_view(g->full);
-    if (g->own_in.tasks != g->own_out.tasks) free_plan(g->own_in);
-    free_plan(g->own_out);
-    g->own_in = Plan{};
+    free_plans(g->own_out, g->own_in);
     dfree(g->perm);
     dfree(g->hub_dist);
     g->h_perm.clear();
@@ -1562,12 +1590,6 @@ int mfbc_set_plan(mfbc_graph *g, int32_t run_arcs, int32_t run_verts, int32_t he
     DeviceGuard dg(g->device);
     HIP_TRY(hipDeviceSynchronize());
     const int32_t old_slots = max_slots(g);
-    if (!g->own_out.tasks) {         // the library's own decomposition is kept
-        g->own_out = g->core.plan_out;
-        g->own_in = g->core.plan_in;
-        g->core.plan_out = g->core.plan_in = Plan{};
-        if (!g->has_core) g->full.plan_out = g->full.plan_in = Plan{};
-    }
     const int rc = plan_views(g, TaskParams{run_arcs, run_verts, heavy, slice});
     if (rc) return rc;
     // the partial buffers are sized by the slot count: regrow on next use

@@ -1,0 +1,130 @@
+"""The library's host code on the CPU (csrc/mfbc_api.cpp built with g++ over
+stand-ins for the HIP runtime and the kernel launchers, host/api_host.cpp):
+what a call leaves behind when an allocation fails on its way.  At every
+launch the stand-ins check that the plan and the workspace handed to the
+kernel hold what it reads and writes, so a kernel that would read or write
+out of range shows here and needs no GPU."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1609_07008_amd import graphgen as gg
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1609_07008_amd", "csrc")
+HOST = os.path.join(ROOT, "tests", "host")
+OK, EINVAL, ENOMEM, EDEVICE = 0, -1, -2, -3
+P, I32, I64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if not cxx:
+        pytest.skip("no g++")
+    so = str(tmp_path_factory.mktemp("api") / "libapi_host.so")
+    subprocess.run([cxx, "-O1", "-g", "-std=c++17", "-fPIC", "-shared", "-pthread",
+                    "-I", os.path.join(HOST, "hip_stub"), "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(HOST, "api_host.cpp"),
+                    *[os.path.join(CSRC, f) for f in ("mfbc_api.cpp", "graph.cpp", "order.cpp")], "-o", so],
+                   check=True)
+    return so
+
+
+@pytest.fixture()
+def lib(built):
+    x = ctypes.CDLL(built)
+    x.stub_live.restype = x.stub_peak.restype = ctypes.c_size_t
+    x.stub_faults.restype = x.stub_log.restype = x.mfbc_last_error.restype = ctypes.c_char_p
+    x.stub_fail_in.argtypes = [ctypes.c_long]
+    x.stub_cap.argtypes = [ctypes.c_size_t]
+    x.stub_watch.argtypes = [P]
+    x.mfbc_load_graph.argtypes = [I32, I64, P, P, P, ctypes.c_uint32, P, P]
+    x.mfbc_free_graph.argtypes = [P]
+    x.mfbc_set_plan.argtypes = [P, I32, I32, I32, I32]
+    x.mfbc_set_lanes.argtypes = [P, I32]
+    x.mfbc_forward.argtypes = [P, P, I32, P, P, P, P]
+    x.mfbc_backward.argtypes = [P, P, I32, P, P, P, P, P]
+    x.mfbc_fixpoint.argtypes = [P, I32, P, I32, P, P, P]
+    x.mfbc_bc.argtypes = [P, P, I64, I32, P, P]
+    x.mfbc_bc_noalloc.argtypes = [P, P, I64, I32, P, P]
+    x.mfbc_bc_many.argtypes = [I32, P, P, P, P, P, P, P]
+    x.stub_fail_in(-1)
+    x.stub_cap(1 << 62)
+    x.stub_products(3, 3)
+    x.stub_core(100)
+    x.stub_quad_fit(1 << 20)
+    x.stub_watch(None)
+    x.stub_clear()
+    return x
+
+
+def load(lib, g, directed=False):
+    rp, col = np.ascontiguousarray(g.row_ptr, np.int64), np.ascontiguousarray(g.col, np.int32)
+    w = None if g.w is None else np.ascontiguousarray(g.w, np.int32)
+    h = P()
+    rc = lib.mfbc_load_graph(g.n, col.size, rp.ctypes.data, col.ctypes.data, None if w is None else w.ctypes.data,
+                             2 if directed else 1, None, ctypes.byref(h))
+    return rc, h
+
+
+def sources(nb):
+    return np.arange(nb, dtype=np.int32)
+
+
+def every_call(lib, h, n, nb=130):
+    """One call of each kind whose products run on this handle's plans."""
+    src, one = sources(nb), ctypes.c_double(0)
+    out = ctypes.byref(one)          # the stand-ins write no results
+    rcs = [lib.mfbc_forward(h, src.ctypes.data, nb, out, out, None, None),
+           lib.mfbc_backward(h, src.ctypes.data, nb, out, out, out, None, None),
+           *[lib.mfbc_fixpoint(h, op, src.ctypes.data, nb, out, None, None) for op in range(4)],
+           lib.mfbc_bc(h, src.ctypes.data, nb, nb, out, None)]
+    return rcs
+
+
+KINDS = {
+    "weighted": (lambda: gg.rmat_graph(9, 16, 3, wrange=(1, 255)), False, 40),       # with a core
+    "unweighted": (lambda: gg.rmat_graph(9, 16, 3), False, 100),
+    "directed": (lambda: gg.directed_rmat_graph(9, 16, 3, wrange=(1, 255)), True, 40),
+}
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_a_failed_set_plan_leaves_the_graph_as_it_was(lib, kind):
+    """Every allocation of mfbc_set_plan in turn fails: ENOMEM, nothing leaked,
+    and every call on the handle still finds whole plans and a workspace that
+    holds their split rows; then the change goes through."""
+    make, directed, percent = KINDS[kind]
+    g = make()
+    lib.stub_core(percent)
+    rc, h = load(lib, g, directed)
+    assert rc == OK
+    for earlier in ((0, 0, 0, 0), (64, 5, 64, 32)):         # the library's own plans, then a caller's
+        if any(earlier):
+            assert lib.mfbc_set_plan(h, *earlier) == OK
+        assert every_call(lib, h, g.n) == [OK] * 7
+        held = lib.stub_live()
+        failed = 0
+        while True:
+            lib.stub_fail_in(failed)
+            rc = lib.mfbc_set_plan(h, 64, 3, 8, 2)          # many more slices than before
+            lib.stub_fail_in(-1)
+            if rc == OK:
+                break
+            assert rc == ENOMEM
+            assert lib.stub_live() == held, f"allocation {failed}"
+            assert every_call(lib, h, g.n) == [OK] * 7, f"allocation {failed}"
+            assert lib.stub_faults() == b"", f"allocation {failed}"
+            failed += 1
+        assert failed >= (3 if percent == 100 else 6)
+        assert every_call(lib, h, g.n) == [OK] * 7
+    assert lib.mfbc_set_plan(h, 0, 0, 0, 0) == OK
+    assert every_call(lib, h, g.n) == [OK] * 7
+    assert lib.stub_faults() == b""
+    lib.mfbc_free_graph(h)
+    assert lib.stub_live() == 0 and lib.stub_faults() == b""
