@@ -32,9 +32,9 @@ using namespace mfbc;
 // Calls are admitted by a fixed formula (ws_arrays) against kScratchBytes; the
 // array is larger, since the default row cut of a small graph takes up to
 // 4.7 MB more hub partials per group than the formula counts (rows cut into
-// slices of max(64, arcs / 4096) arcs, 768 B each), and a core's partials and
-// DAG masks up to 1.4 B per arc more than the masks of every arc, and path
-// counts in 16 bits a tenth of a one-group workspace.
+// slices of max(64, arcs / 4096) arcs, 768 B each), a core's partials and
+// DAG masks up to 1.4 B per arc more than the masks of every arc, path
+// counts in 16 bits a tenth of a one-group workspace, and a third bitmap.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
 constexpr size_t kScratchSize = (size_t)84 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchSize];
@@ -99,8 +99,8 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // carve them out of one block of memory.
 // (g == nullptr: every count is 0, for walks that need only the pointers.)
 // admit: the sizes mfbc_bc_noalloc admits calls by -- the stored DAG of every
-// arc, the hub partials of the plain row cut -- which depend on neither the
-// weights nor the default decomposition.
+// arc, the hub partials of the plain row cut, two activity bitmaps -- which
+// depend on neither the weights nor the default decomposition.
 template <typename F>
 void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool admit = false) {
     const size_t n = g ? (size_t)g->n : 0;
@@ -115,7 +115,7 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool admit = 
         f(ws.fsig[b], tile);
         f(ws.fbits[b], n * ncg);
     }
-    for (auto &b : ws.abits) f(b, nwords * ncg);
+    for (int b = 0; b < (admit ? 2 : 3); b++) f(ws.abits[b], nwords * ncg);
     f(ws.pd, slots);
     f(ws.pm, slots);
     f(ws.counters, kCounterWords);

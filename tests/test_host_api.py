@@ -128,3 +128,33 @@ def test_a_failed_set_plan_leaves_the_graph_as_it_was(lib, kind):
     assert lib.stub_faults() == b""
     lib.mfbc_free_graph(h)
     assert lib.stub_live() == 0 and lib.stub_faults() == b""
+
+
+def ring(n, half=4):
+    """Every vertex next to the `half` vertices on either side."""
+    u = np.repeat(np.arange(n), half)
+    return gg.csr_from_edges(n, u, (u + np.tile(np.arange(1, half + 1), n)) % n, None, f"ring{n}")
+
+
+def admitted(n, arcs, groups):
+    """The bytes that mfbc_bc_noalloc admits calls by (no row of these graphs
+    is split): 39 B a (column, vertex) or so, 8 B a (group, arc)."""
+    tile, nw = n * 64 * groups, (n + 31) // 32
+    sizes = [4 * tile, 8 * tile, *2 * [4 * tile, 8 * tile, 8 * n * groups, 4 * nw * groups], 4, 8, 16384, 16,
+             8 * n * groups, 8 * arcs * groups, 256 * groups, 2 * tile if groups > 1 else 4]
+    return sum(-(-x // 256) * 256 for x in sizes) <= 64 << 20
+
+
+@pytest.mark.parametrize("groups", [1, 2, 4])
+def test_noalloc_admits_by_its_formula(lib, groups):
+    """The largest ring that the formula admits runs, the next one is refused."""
+    n = 28_100 // groups
+    while not admitted(n, 8 * n, groups):
+        n -= 1
+    for n, want in ((n, OK), (n + 1, ENOMEM)):
+        rc, h = load(lib, ring(n))
+        assert rc == OK
+        src, out = sources(64 * groups), ctypes.byref(ctypes.c_double(0))
+        assert lib.mfbc_bc_noalloc(h, src.ctypes.data, src.size, src.size, out, None) == want, n
+        lib.mfbc_free_graph(h)
+    assert lib.stub_faults() == b""
