@@ -923,6 +923,24 @@ int64_t merged_batches(const mfbc_graph *g, int32_t batch, int ncg) {
     return std::max<int64_t>(kMaxLanes, (int64_t)fit);
 }
 
+// What products read of a graph, shared with g; the workspace, counters and
+// statistics stay the view's own.
+void share_graph(const mfbc_graph *g, mfbc_graph *to) {
+    to->device = g->device;
+    to->n = g->n;
+    to->arcs = g->arcs;
+    to->maxw = g->maxw;
+    to->weighted = g->weighted;
+    to->directed = g->directed;
+    to->sparse = g->sparse;
+    to->full = g->full;
+    to->core = g->core;
+    to->has_core = g->has_core;
+    to->mb = g->mb;
+    to->params = g->params;
+    to->perm = g->perm;
+}
+
 // Lane i of g (i = 0: g itself), created on first use; a view is refreshed
 // from g on every call (the plan may have changed).
 int lane_graph(mfbc_graph *g, int i, mfbc_graph **out) {
@@ -944,19 +962,7 @@ int lane_graph(mfbc_graph *g, int i, mfbc_graph **out) {
         }
     }
     if (!g->lane_stream[i]) HIP_TRY(hipStreamCreateWithFlags(&g->lane_stream[i], hipStreamNonBlocking));
-    sh->device = g->device;
-    sh->n = g->n;
-    sh->arcs = g->arcs;
-    sh->maxw = g->maxw;
-    sh->weighted = g->weighted;
-    sh->directed = g->directed;
-    sh->sparse = g->sparse;
-    sh->full = g->full;
-    sh->core = g->core;
-    sh->has_core = g->has_core;
-    sh->mb = g->mb;
-    sh->params = g->params;
-    sh->perm = g->perm;
+    share_graph(g, sh);
     sh->timing = g->timing;
     if (g->timing && !sh->ev[0]) {
         for (auto &e : sh->ev) HIP_TRY(hipEventCreate(&e));
@@ -1053,24 +1059,6 @@ struct WorkspaceSwap {
     ~WorkspaceSwap() { g->ws = saved; }
 };
 
-// The library's own decomposition of a graph's core in place of one set with
-// mfbc_set_plan, for the duration of a scope: run sizes tuned for the batched
-// form's workgroups are too coarse for products that spread over the device
-// (32 graphs of 200..6,000 vertices: 50 ms under them, 29 under its own).
-struct OwnPlan {
-    mfbc_graph *g;
-    Plan out, in;
-    explicit OwnPlan(mfbc_graph *gr) : g(gr), out(gr->core.plan_out), in(gr->core.plan_in) {
-        if (!g->own_out.tasks) return;
-        g->core.plan_out = g->own_out;
-        g->core.plan_in = g->own_in;
-    }
-    ~OwnPlan() {
-        g->core.plan_out = out;
-        g->core.plan_in = in;
-    }
-};
-
 // Whether the batched form's graphs run one after another on streams.  With T
 // the sum over its two-group jobs of the graph's arcs and vertices and M the
 // largest of them, the streams take about 230 us a graph and 2.2 ns an arc; the
@@ -1096,7 +1084,13 @@ bool many_underfilled(const std::vector<mfbc_graph *> &gs, const std::vector<int
 // The batched form on streams: the graphs one after another on up to four,
 // largest first, each with its sources in wide batches, so that a product
 // spreads over the whole device instead of the eight waves of a job.  The
-// state of the streams is carved from the batched form's scratch.
+// state of the streams is carved from the batched form's scratch.  Each graph
+// runs through a view of its handle, under the library's own decomposition of
+// its core where mfbc_set_plan replaced that (run sizes tuned for the
+// persistent launch's workgroups are too coarse for products that spread over
+// the device: 32 graphs of 200..6,000 vertices took 50 ms under them, 29 under
+// its own); the handle itself is only read, as by the persistent launch, so a
+// server may step on it meanwhile.
 constexpr size_t kManyLaneBytes = (size_t)512 << 20;
 
 int many_on_streams(const std::vector<mfbc_graph *> &gs, const std::vector<const int32_t *> &src,
@@ -1105,6 +1099,7 @@ int many_on_streams(const std::vector<mfbc_graph *> &gs, const std::vector<const
     *done = false;
     struct Item {
         mfbc_graph *g;
+        mfbc_graph view;
         std::vector<size_t> at;      // positions in the call (a graph may be listed twice)
         int ncg;                     // column groups of a batch
         double cost;
@@ -1115,25 +1110,30 @@ int many_on_streams(const std::vector<mfbc_graph *> &gs, const std::vector<const
         for (auto &x : items)
             if (x.g == gs[i]) it = &x;
         if (!it) {
-            items.push_back({gs[i], {}, 1, 0.0});
+            items.push_back({gs[i], {}, {}, 1, 0.0});
             it = &items.back();
+            share_graph(it->g, &it->view);
+            it->view.h_ctr = it->g->h_ctr;
+            if (it->g->own_out.tasks) {
+                it->view.core.plan_out = it->g->own_out;
+                it->view.core.plan_in = it->g->own_in;
+            }
         }
         it->at.push_back(i);
         it->cost += (double)ns[i] * (double)(gs[i]->core.arcs + gs[i]->n);
     }
     size_t lane_bytes = 0;
     for (auto &x : items) {
-        const OwnPlan own(x.g);
         int64_t most = 0;
         for (size_t i : x.at) most = std::max(most, ns[i]);
         const int all = bc_groups(most, INT32_MAX);
         int batches = 1;
         x.ncg = all;
-        while (x.ncg > 1 && ws_bytes(x.g, x.ncg, false) > kManyLaneBytes) {
+        while (x.ncg > 1 && ws_bytes(&x.view, x.ncg, false) > kManyLaneBytes) {
             batches++;
             x.ncg = (all + batches - 1) / batches;
         }
-        lane_bytes = std::max(lane_bytes, ws_bytes(x.g, x.ncg, false));
+        lane_bytes = std::max(lane_bytes, ws_bytes(&x.view, x.ncg, false));
     }
     lane_bytes = align256(lane_bytes);
     const int lanes = (int)std::min<size_t>({(size_t)kMaxLanes, items.size(), budget / std::max<size_t>(lane_bytes, 1)});
@@ -1161,16 +1161,13 @@ int many_on_streams(const std::vector<mfbc_graph *> &gs, const std::vector<const
             const size_t k = next++;
             if (k >= items.size()) break;
             Item &x = items[k];
-            const OwnPlan own(x.g);
-            WorkspaceSwap sw(x.g);
-            carve_workspace(x.g, x.ncg, base + (size_t)i * lane_bytes, x.g->ws);
+            carve_workspace(&x.view, x.ncg, base + (size_t)i * lane_bytes, x.view.ws);
             for (size_t at : x.at) {
                 if (rc) break;
-                const mfbc_stats before = x.g->stats;
-                rc = bc_batches(x.g, src[at], ns[at], x.ncg * kWave, bc_groups(ns[at], x.ncg * kWave), out[at], ls[i]);
-                fwd += (unsigned long long)x.g->stats.fwd_products;
-                bwd += (unsigned long long)x.g->stats.bwd_products;
-                x.g->stats = before;
+                rc = bc_batches(&x.view, src[at], ns[at], x.ncg * kWave, bc_groups(ns[at], x.ncg * kWave), out[at],
+                                ls[i]);
+                fwd += (unsigned long long)x.view.stats.fwd_products;
+                bwd += (unsigned long long)x.view.stats.bwd_products;
             }
         }
         if (rc) {

@@ -158,3 +158,35 @@ def test_noalloc_admits_by_its_formula(lib, groups):
         assert lib.mfbc_bc_noalloc(h, src.ctypes.data, src.size, src.size, out, None) == want, n
         lib.mfbc_free_graph(h)
     assert lib.stub_faults() == b""
+
+
+def many(lib, graphs, nb, config=None):
+    """mfbc_bc_many over loaded graphs, nb sources each; config: block_threads,
+    blocks, job_width."""
+    k = len(graphs)
+    src, out = sources(nb), ctypes.c_double(0)
+    cfg = np.array(config, np.int32) if config else None
+    return lib.mfbc_bc_many(k, (P * k)(*graphs), (P * k)(*[src.ctypes.data] * k), (I64 * k)(*[nb] * k),
+                            (P * k)(*[ctypes.addressof(out)] * k), cfg.ctypes.data if config else None, None, None)
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_batched_form_on_streams_only_reads_the_handles(lib, kind):
+    """A server may step on a graph while another thread has it in a batched
+    call: the handle's plans and workspace stay what they are throughout."""
+    make, directed, percent = KINDS[kind]
+    lib.stub_core(percent)
+    hs = [load(lib, make(), directed)[1] for _ in range(3)]
+    assert every_call(lib, hs[0], 0) == [OK] * 7
+    for plan in (None, (256, 64, 64, 32)):
+        if plan:
+            assert lib.mfbc_set_plan(hs[0], *plan) == OK
+        lib.stub_watch(hs[0])
+        assert many(lib, hs + hs[:1], 200) == OK         # (one graph listed twice)
+        assert b"quad_product" in lib.stub_log() and b"bc_many" not in lib.stub_log()
+        assert lib.stub_faults() == b""
+        lib.stub_watch(None)
+        lib.stub_clear()
+    assert every_call(lib, hs[0], 0) == [OK] * 7
+    for h in hs:
+        lib.mfbc_free_graph(h)
