@@ -365,7 +365,9 @@ int mfbc_graph_info(const mfbc_graph *g, int32_t *n, int64_t *n_arcs,
  * Few or large graphs, which would leave most workgroups idle, run one after
  * another on up to four streams of the library in wide batches, under the
  * library's own work decomposition (config and mfbc_set_plan shape the
- * persistent launch alone).  Per graph the result equals mfbc_bc(graphs[i],
+ * persistent launch alone); a config whose blocks are fewer than fill the
+ * device (the default number) always gets the persistent launch, on that many
+ * workgroups.  Per graph the result equals mfbc_bc(graphs[i],
  * d_sources[i], h_n_sources[i], job_width, d_bc[i]) up to rounding (parts are
  * summed in a fixed order, so repeated calls with one configuration are
  * bitwise identical).

@@ -1644,12 +1644,13 @@ int mfbc_bc_many(int32_t n_graphs, mfbc_graph *const *graphs, const int32_t *con
     int rc;
     for (int32_t i = 0; i < n_graphs; i++)
         if ((rc = check_sources(gs[(size_t)i], src[(size_t)i], ns[(size_t)i], s))) return rc;
-    int blocks = config && config->blocks > 0 ? config->blocks : 0;
-    if (blocks == 0) {
-        hipDeviceProp_t prop;
-        HIP_TRY(hipGetDeviceProperties(&prop, dev));
-        blocks = (2048 / block_threads) * prop.multiProcessorCount;   // 8 waves per SIMD
-    }
+    hipDeviceProp_t prop;
+    HIP_TRY(hipGetDeviceProperties(&prop, dev));
+    const int full = (2048 / block_threads) * prop.multiProcessorCount;   // 8 waves per SIMD
+    int blocks = config && config->blocks > 0 ? config->blocks : full;
+    // fewer workgroups than fill the device: the caller leaves the rest of it to
+    // others, which the streams would take
+    const bool shared = blocks < full;
     int n_max = 1, slots_max = 1;
     int64_t arcs_max = 1;
     for (auto *g : gs) {
@@ -1668,7 +1669,7 @@ int mfbc_bc_many(int32_t n_graphs, mfbc_graph *const *graphs, const int32_t *con
     blocks = std::min(blocks, cap);
     unsigned long long tot[2] = {0, 0};
     bool done = false;
-    if (many_underfilled(gs, ns) && (rc = many_on_streams(gs, src, ns, out, budget, ws, s, &done, tot))) return rc;
+    if (!shared && many_underfilled(gs, ns) && (rc = many_on_streams(gs, src, ns, out, budget, ws, s, &done, tot))) return rc;
     // one persistent launch per arc encoding (unweighted, packed, separate)
     for (int mode = 0; mode < 3 && !done; mode++) {
         std::vector<mfbc_graph *> g2;

@@ -190,3 +190,19 @@ def test_batched_form_on_streams_only_reads_the_handles(lib, kind):
     assert every_call(lib, hs[0], 0) == [OK] * 7
     for h in hs:
         lib.mfbc_free_graph(h)
+
+
+def test_a_limit_on_the_workgroups_is_kept(lib):
+    """Fewer workgroups than fill the device (2048 threads on each of 256 CUs)
+    ask for the persistent launch on that many; else few graphs run on streams."""
+    hs = [load(lib, KINDS["unweighted"][0]())[1] for _ in range(3)]
+    for config, blocks in (((512, 37, 64), 37), ((256, 2047, 128), 2047), ((512, 1023, 0), 1023)):
+        lib.stub_clear()
+        assert many(lib, hs, 200, config) == OK
+        assert lib.stub_log() == b"bc_many(%d) " % blocks
+    for config in (None, (512, 1024, 128), (256, 2048, 64), (512, 0, 64)):
+        lib.stub_clear()
+        assert many(lib, hs, 200, config) == OK
+        assert b"bc_many" not in lib.stub_log()
+    for h in hs:
+        lib.mfbc_free_graph(h)
