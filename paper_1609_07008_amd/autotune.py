@@ -141,27 +141,35 @@ def many_bucket(n: int) -> str:
     return "n<=2^10" if n <= 1024 else ("n<=2^12" if n <= 4096 else "n>2^12")
 
 
+def _persistent(threads: int, per_cu: int, width: int) -> dict:
+    """The launch shape as bc_many is to be timed under it: with one workgroup
+    fewer than fill the device (2048 threads per CU), for a call with as many as
+    that may run on streams instead, where neither shape nor plan counts."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return dict(block_threads=threads, blocks=min(per_cu * cus, 2048 // threads * cus - 1), job_width=width)
+
+
 def tune_many(dgs, srcs, reps: int = 1, cache: dict = None, verbose=False):
     """Pick the batched form's launch (threads, workgroups per CU, sources
     per job) on (a sample of) its graphs, then the run sizes of each size
     class: the class's graphs alone, in the chosen launch, under each plan."""
     import torch
     from . import mfbc
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
     outs = [torch.empty(d.n, dtype=torch.float64, device="cuda") for d in dgs]
     for d in dgs:
         d.set_plan()
     res = {}
     for width in MANY_WIDTHS:
         for threads, per_cu in MANY_CANDIDATES:
-            cfg = dict(block_threads=threads, blocks=per_cu * cus, job_width=width)
+            cfg = _persistent(threads, per_cu, width)
             key = (threads, per_cu, width)
             res[key] = _time(lambda: mfbc.bc_many(dgs, srcs, outs=outs, **cfg), reps)
             if verbose:
                 print(f"[tune] many threads={threads} per_cu={per_cu} job_width={width}: "
                       f"{res[key]:.3f} s", file=sys.stderr, flush=True)
     best = min(res, key=res.get)
-    cfg = dict(block_threads=best[0], blocks=best[1] * cus, job_width=best[2])
+    cfg = _persistent(*best)
     plans = {}
     classes = {}
     for i, d in enumerate(dgs):

@@ -206,3 +206,25 @@ def test_a_limit_on_the_workgroups_is_kept(lib):
         assert b"bc_many" not in lib.stub_log()
     for h in hs:
         lib.mfbc_free_graph(h)
+
+
+def test_the_tuner_times_the_persistent_launch_alone(monkeypatch):
+    """tune_many's launch shapes and plans shape the persistent launch only: every
+    timed call asks for it, whatever its graphs."""
+    import types
+
+    import torch
+
+    from paper_1609_07008_amd import autotune, mfbc
+    calls = []
+    empty = torch.empty
+    monkeypatch.setattr(torch, "empty", lambda *a, device=None, **k: empty(*a, **k))
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda *a: None)
+    monkeypatch.setattr(torch.cuda, "get_device_properties",
+                        lambda *a: types.SimpleNamespace(multi_processor_count=256))
+    monkeypatch.setattr(mfbc, "bc_many", lambda *a, outs=None, **cfg: calls.append(cfg))
+    graphs = [types.SimpleNamespace(n=n, set_plan=lambda **k: None) for n in (300, 3000, 9000)]
+    cache = {}
+    autotune.tune_many(graphs, [None] * 3, cache=cache)
+    assert len(calls) > 20 and all(c["blocks"] * c["block_threads"] < 2048 * 256 for c in calls)
+    assert cache["many"]["per_cu"] * cache["many"]["block_threads"] <= 2048      # the shape itself is kept
