@@ -164,10 +164,12 @@ int mfbc_bc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources,
 /*
  * mfbc_set_lanes -- how many batches of one mfbc_bc call run at once (a
  * tuning knob; results differ only in floating-point summation order).
- *   lanes  1..4, or 0 (the default), by the arcs * column groups of a batch:
+ *   lanes  1..4, or 0 (the default), by the arcs that the products of a batch
+ *          read (those that can lie on a shortest path) * its column groups:
  *          up to 2^21 four batches, or as many as keep the state within 256
  *          MB, run as one wide batch; up to 2^24 four run at once; else one at
- *          a time.
+ *          a time.  Batches run together by default only as far as their
+ *          state stays within 48 GiB and fits the device.
  * Each lane holds its own workspace (see the workspace note above).
  * Errors: EINVAL (lanes outside [0, 4]).
  */

@@ -916,11 +916,23 @@ int bc_batches(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32
 //    only partly (unweighted R-MAT scale 16, 2,048 sources in batches of 512:
 //    18.4 ms, 19.5 as one wide batch);
 //  * above: one after another.
+// The state of batches that run together without being asked for stays within
+// kLaneBytes (a sixth of a device's 288 GB; four lanes of 256 sources at n =
+// 2^20 hold 42 GB): it is kept until the graph is freed.
+constexpr double kLaneBytes = 48.0 * (1 << 30);
+
+double column_bytes(const mfbc_graph *g) { return 39.0 * g->n + (double)g->core.arcs * 8.0 / kWave; }
+
+// Batches of `ncg` groups whose state fits kLaneBytes, 1..kMaxLanes.
+int lanes_within(const mfbc_graph *g, int ncg) {
+    const double fit = kLaneBytes / (column_bytes(g) * kWave * ws_groups(ncg));
+    return std::max(1, (int)std::min<double>(kMaxLanes, fit));
+}
+
 int64_t merged_batches(const mfbc_graph *g, int32_t batch, int ncg) {
     if ((double)g->core.arcs * (double)ncg > (double)(1 << 21)) return 1;
-    const double column = 39.0 * g->n + (double)g->core.arcs * 8.0 / kWave;
-    const double fit = (double)(256 << 20) / column / (double)batch;
-    return std::max<int64_t>(kMaxLanes, (int64_t)fit);
+    const double fit = (double)(256 << 20) / column_bytes(g) / (double)batch;
+    return std::max<int64_t>(lanes_within(g, ncg), (int64_t)fit);
 }
 
 // What products read of a graph, shared with g; the workspace, counters and
@@ -987,15 +999,21 @@ void add_stats(mfbc_stats &a, const mfbc_stats &b) {
 // Algorithm 3 with batch b on lane b % S: lane 0 on the caller's stream, the
 // others on their own streams after the caller's prior work; each lane's
 // host loop runs on its own thread; lambda = the lanes' parts, summed in lane
-// order (so a call is deterministic for a given lane count).
+// order (so a call is deterministic for a given lane count).  `fewer`: lanes
+// whose workspace does not fit are left out, down to the first.
 int bc_lanes(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t batch, int ncg,
-             int S, double *d_bc, hipStream_t s) {
+             int S, bool fewer, double *d_bc, hipStream_t s) {
     mfbc_graph *lg[kMaxLanes] = {};
     hipStream_t ls[kMaxLanes] = {};
     int rc;
     for (int i = 0; i < S; i++) {
         if ((rc = lane_graph(g, i, &lg[i]))) return rc;
-        if ((rc = ensure_workspace(lg[i], ncg))) return rc;
+        rc = ensure_workspace(lg[i], ncg);
+        if (rc == MFBC_ENOMEM && fewer && i > 0) {
+            S = i;
+            break;
+        }
+        if (rc) return rc;
         ls[i] = i == 0 ? s : g->lane_stream[i];
     }
     if (!g->lane_start) HIP_TRY(hipEventCreateWithFlags(&g->lane_start, hipEventDisableTiming));
@@ -1443,10 +1461,12 @@ int mfbc_bc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t 
     const int ncg = bc_groups(n_sources, batch);
     const int64_t nbat = (n_sources + batch - 1) / batch;
     const double work = (double)g->core.arcs * (double)ncg;
-    const int lanes = g->lanes ? g->lanes : (work > (double)(1 << 21) && work <= (double)(1 << 24) ? kMaxLanes : 1);
+    const int lanes =
+        g->lanes ? g->lanes : (work > (double)(1 << 21) && work <= (double)(1 << 24) ? lanes_within(g, ncg) : 1);
     if (lanes > 1 && nbat > 1) {
         if ((rc = check_sources(g, d_sources, n_sources, s))) return rc;
-        return bc_lanes(g, d_sources, n_sources, batch, ncg, (int)std::min<int64_t>(lanes, nbat), d_bc, s);
+        return bc_lanes(g, d_sources, n_sources, batch, ncg, (int)std::min<int64_t>(lanes, nbat), g->lanes == 0, d_bc,
+                        s);
     }
     const int64_t wide = g->lanes ? 1 : std::min(nbat, merged_batches(g, batch, ncg));
     if (wide > 1) {

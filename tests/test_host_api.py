@@ -228,3 +228,43 @@ def test_the_tuner_times_the_persistent_launch_alone(monkeypatch):
     autotune.tune_many(graphs, [None] * 3, cache=cache)
     assert len(calls) > 20 and all(c["blocks"] * c["block_threads"] < 2048 * 256 for c in calls)
     assert cache["many"]["per_cu"] * cache["many"]["block_threads"] <= 2048      # the shape itself is kept
+
+
+def test_default_lanes_take_what_fits(lib):
+    """Where batches run at once by default, a lane whose workspace does not fit
+    is left out; a lane count that was asked for is met or refused."""
+    g = ring(1 << 15, 16)                                   # 2^20 arcs: four lanes at four groups
+    src, out = sources(800), ctypes.byref(ctypes.c_double(0))
+    lane = 0
+    for fit in (4, 0, 1, 2, 3):
+        rc, h = load(lib, g)
+        assert rc == OK
+        start = lib.stub_live()
+        lib.stub_cap(start + (2 * fit + 1) * lane // 2 if lane else 1 << 62)
+        want = OK if fit else ENOMEM
+        assert [lib.mfbc_bc(h, src.ctypes.data, src.size, 200, out, None) for _ in range(2)] == [want] * 2, fit
+        held = lib.stub_live() - start
+        lane = lane or held // 4
+        assert held == fit * lane
+        if fit < 4:
+            assert lib.mfbc_set_lanes(h, 4) == OK
+            assert lib.mfbc_bc(h, src.ctypes.data, src.size, 200, out, None) == ENOMEM
+        lib.stub_cap(1 << 62)
+        lib.mfbc_free_graph(h)
+        assert lib.stub_live() == 0 and lib.stub_faults() == b""
+
+
+@pytest.mark.parametrize("edges", [1 << 20, 1 << 16])
+def test_default_lanes_stay_within_their_share(lib, edges):
+    """n = 2^20 in batches of 448 columns (21 GB a batch): two at once on streams
+    or, where arcs are few, in one wide batch; not four."""
+    n, batch = 1 << 20, 448
+    u = np.arange(edges)
+    rc, h = load(lib, gg.csr_from_edges(n, u, (u + 1) % n, None, "path"))
+    assert rc == OK
+    src, out = sources(4 * batch), ctypes.byref(ctypes.c_double(0))
+    lib.stub_reset_peak()
+    assert lib.mfbc_bc(h, src.ctypes.data, src.size, batch, out, None) == OK
+    assert round(lib.stub_peak() / (39 * n * 512)) == 2     # 39 B a (column, vertex), eight groups
+    lib.mfbc_free_graph(h)
+    assert lib.stub_faults() == b""
