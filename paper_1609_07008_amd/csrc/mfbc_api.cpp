@@ -13,9 +13,10 @@
 #include <atomic>
 #include <cstdio>
 #include <cstring>
+#include <exception>
+#include <functional>
 #include <mutex>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <type_traits>
 #include <utility>
@@ -996,6 +997,22 @@ void add_stats(mfbc_stats &a, const mfbc_stats &b) {
     for (int k = 0; k < 9; k++) ad[k] += bd[k];
 }
 
+// lane(0) here and lane(1) .. lane(count - 1) on threads of their own; a lane
+// whose thread cannot be started runs here after lane(0).
+template <typename F>
+void run_lanes(int count, const F &lane) {
+    std::thread th[kMaxLanes];
+    int started = 1;
+    try {
+        for (; started < count; started++) th[started] = std::thread(std::cref(lane), started);
+    } catch (const std::exception &) {
+    }
+    lane(0);
+    for (int i = started; i < count; i++) lane(i);
+    for (auto &t : th)
+        if (t.joinable()) t.join();
+}
+
 // Algorithm 3 with batch b on lane b % S: lane 0 on the caller's stream, the
 // others on their own streams after the caller's prior work; each lane's
 // host loop runs on its own thread; lambda = the lanes' parts, summed in lane
@@ -1039,10 +1056,7 @@ int bc_lanes(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32_t
         rcs[i] = r;
         if (r) msgs[i] = mfbc_last_error();
     };
-    std::vector<std::thread> th;
-    for (int i = 1; i < S; i++) th.emplace_back(lane, i);
-    lane(0);
-    for (auto &t : th) t.join();
+    run_lanes(S, lane);
     for (int i = 0; i < S; i++)
         if (rcs[i]) return fail(rcs[i], msgs[i]);
     launch_lambda_reduce_lanes(lg, S, ncg, d_bc, s);
@@ -1195,14 +1209,7 @@ int many_on_streams(const std::vector<mfbc_graph *> &gs, const std::vector<const
         }
         rcs[i] = rc;
     };
-    std::vector<std::thread> th;
-    try {
-        for (int i = 1; i < lanes; i++) th.emplace_back(lane, i);
-    } catch (const std::system_error &) {
-        // fewer threads: the lanes that run take every graph
-    }
-    lane(0);
-    for (auto &t : th) t.join();
+    run_lanes(lanes, lane);
     for (int i = 0; i < lanes; i++)
         if (rcs[i]) return fail(rcs[i], msgs[i]);
     products[0] += fwd;

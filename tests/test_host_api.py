@@ -37,7 +37,11 @@ def built(tmp_path_factory):
 
 @pytest.fixture()
 def lib(built):
-    x = ctypes.CDLL(built)
+    return bind(built)
+
+
+def bind(so):
+    x = ctypes.CDLL(so)
     x.stub_live.restype = x.stub_peak.restype = ctypes.c_size_t
     x.stub_faults.restype = x.stub_log.restype = x.mfbc_last_error.restype = ctypes.c_char_p
     x.stub_fail_in.argtypes = [ctypes.c_long]
@@ -269,3 +273,32 @@ def test_default_lanes_stay_within_their_share(lib, edges):
     assert round(lib.stub_peak() / (39 * n * 512)) == 2     # 39 B a (column, vertex), eight groups
     lib.mfbc_free_graph(h)
     assert lib.stub_faults() == b""
+
+
+NO_THREADS = """
+import resource, sys
+sys.path.insert(0, {root!r})
+from tests.test_host_api import *
+lib = bind({so!r})
+h = load(lib, ring(1 << 15, 16))[1]
+hs = [load(lib, ring(2000, 4))[1] for _ in range(3)]
+src, out = sources(800), ctypes.byref(ctypes.c_double(0))
+resource.setrlimit(resource.RLIMIT_AS, (24 << 30, 24 << 30))
+print(lib.mfbc_bc(h, src.ctypes.data, src.size, 200, out, None), many(lib, hs, 200),
+      lib.stub_log().count(b"bwd_count"), lib.stub_faults())
+"""
+
+
+def test_lanes_whose_threads_cannot_start_run_all_the_same(built):
+    """A process that cannot start a thread (stacks of 32 GiB within 24 GiB of
+    address space): four batches and three graphs one after another, no abort."""
+    import resource
+    import sys
+    hard = resource.getrlimit(resource.RLIMIT_STACK)[1]
+    if hard not in (-1, resource.RLIM_INFINITY) and hard < 32 << 30:
+        pytest.skip("stack sizes are limited here")
+    r = subprocess.run([sys.executable, "-c", NO_THREADS.format(root=ROOT, so=built)], capture_output=True, text=True,
+                       env=dict(os.environ, OPENBLAS_NUM_THREADS="1", OMP_NUM_THREADS="1"),
+                       preexec_fn=lambda: resource.setrlimit(resource.RLIMIT_STACK, (32 << 30, hard)))
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert r.stdout.split("\n")[-2] == "0 0 7 b''", r.stdout
