@@ -99,11 +99,17 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // order: f(pointer, element count).  Used both to allocate the arrays and to
 // carve them out of one block of memory.
 // (g == nullptr: every count is 0, for walks that need only the pointers.)
+// tau_words: as Workspace::tau_words (ws_tau_words, unless that does not fit).
 // admit: the sizes mfbc_bc_noalloc admits calls by -- the stored DAG of every
 // arc, the hub partials of the plain row cut, two activity bitmaps -- which
 // depend on neither the weights nor the default decomposition.
+size_t ws_tau_words(int ncg, bool least) {
+    if (least) return ncg >= 2 ? (size_t)ncg / 2 : 0;
+    return ncg <= 2 ? 1 : 2 * (((size_t)ncg + 3) / 4);
+}
+
 template <typename F>
-void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool admit = false) {
+void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, size_t tau_words, F &&f, bool admit = false) {
     const size_t n = g ? (size_t)g->n : 0;
     const size_t tile = n * kWave * (size_t)ncg;
     const size_t nwords = (n + 31) / 32;
@@ -123,10 +129,9 @@ void ws_arrays(const mfbc_graph *g, Workspace &ws, int ncg, F &&f, bool admit = 
     f(ws.lam, n * ncg);
     f(ws.dag, (size_t)std::max<int64_t>(g ? (admit ? g->arcs : g->core.arcs) : 0, 1) * ncg);
     f(ws.src, (size_t)ncg * kWave);
-    // the paired counting product's tau in 16 bits, or path counts in 16 bits (two
-    // words a lane from three groups on, as in quad.hip)
-    if (admit) f(ws.tau2, ncg >= 2 ? tile / 2 : (size_t)1);
-    else f(ws.tau2, n * kWave * (size_t)(ncg <= 2 ? 1 : 2 * ((ncg + 3) / 4)));
+    // the paired counting product's tau in 16 bits (`least`: what that takes), or
+    // path counts in 16 bits (two words a lane from three groups on, as in quad.hip)
+    f(ws.tau2, n * kWave * tau_words);
 }
 
 // Column groups the workspace holds for a batch of `ncg` groups: batches of
@@ -138,7 +143,8 @@ int ws_groups(int ncg) { return ncg <= 1 ? 1 : (ncg + 1) & ~1; }
 size_t ws_bytes(const mfbc_graph *g, int ncg, bool admit) {
     Workspace tmp;
     size_t off = 0;
-    ws_arrays(g, tmp, ws_groups(ncg), [&](auto *&p, size_t count) {
+    ncg = ws_groups(ncg);
+    ws_arrays(g, tmp, ncg, ws_tau_words(ncg, admit), [&](auto *&p, size_t count) {
         (void)p;
         off = align256(off + std::max<size_t>(count, 1) * sizeof(*p));
     }, admit);
@@ -146,7 +152,7 @@ size_t ws_bytes(const mfbc_graph *g, int ncg, bool admit) {
 }
 
 void free_workspace(Workspace &ws) {
-    if (!ws.external) ws_arrays(nullptr, ws, 0, [](auto *&p, size_t) { dfree(p); });
+    if (!ws.external) ws_arrays(nullptr, ws, 0, 0, [](auto *&p, size_t) { dfree(p); });
     dfree(ws.trace_relax);
     dfree(ws.quad_base);
     ws = Workspace{};
@@ -201,20 +207,27 @@ int upload_plan(int32_t n, const int64_t *h_rp, const TaskParams &prm, Plan &pla
     return MFBC_OK;
 }
 
-// Grow the workspace to hold a batch of `ncg` column groups.
+// Grow the workspace to hold a batch of `ncg` column groups.  Where it does not
+// fit with path counts in 16 bits, it holds the rest: such a batch runs in 32.
 int ensure_workspace(mfbc_graph *g, int ncg) {
     Workspace &ws = g->ws;
     ncg = ws_groups(ncg);
     if (ws.ncg >= ncg && !ws.external) return MFBC_OK;
     free_workspace(ws);
     int rc = MFBC_OK;
-    ws_arrays(g, ws, ncg, [&](auto *&p, size_t count) {
-        if (!rc) rc = dalloc(&p, count);
-    });
-    if (rc) {
+    size_t tau = 0;
+    for (bool least : {false, true}) {
+        if (least && (rc != MFBC_ENOMEM || tau == ws_tau_words(ncg, true))) break;
+        tau = ws_tau_words(ncg, least);
+        rc = MFBC_OK;
+        ws_arrays(g, ws, ncg, tau, [&](auto *&p, size_t count) {
+            if (!rc) rc = dalloc(&p, count);
+        });
+        if (!rc) break;
         free_workspace(ws);
-        return rc;
     }
+    if (rc) return rc;
+    ws.tau_words = (int)tau;
     ws.ncg = ncg;
     ws.flags = (int32_t *)(ws.counters + kRingWords);
     return MFBC_OK;
@@ -388,15 +401,19 @@ constexpr int64_t kQuadArcs = 1 << 18;
 // Algorithm 1, or the (min, a + w) fixpoint without multiplicities, in 16 bits
 // (d_sources nullable: already in ws.src): on every arc with bounds, on the
 // core without.  *fits becomes false, with nothing written, if the frontier
-// outlives the products whose entries fit.
+// outlives the products whose entries fit, or the state has no room.
 int run_quad(mfbc_graph *g, bool core, bool count, int ncg, int nb, const int32_t *d_sources, int32_t *products,
              bool *fits, hipStream_t s) {
     const View &vw = core ? g->core : g->full;
     const int words = core || ncg <= 2 ? 1 : 2;
     const int most = core || g->arcs >= kQuadArcs ? quad_products(g, count) : 0;
-    *fits = most > 0;
+    *fits = most > 0 && (!count || (ncg + 2 * words - 1) / (2 * words) * words <= g->ws.tau_words);
     if (!*fits) return MFBC_OK;
     int rc = ensure_quad(g, ncg, words, !core);
+    if (rc == MFBC_ENOMEM) {
+        *fits = false;
+        return MFBC_OK;
+    }
     if (rc) return rc;
     launch_quad_init(g, vw, count, ncg, nb, d_sources, s);
     const double arc_bytes = g->weighted ? 8.0 : 4.0;
@@ -1074,7 +1091,8 @@ void carve_workspace(const mfbc_graph *g, int ncg, char *base, Workspace &ws) {
     ws = Workspace{};
     const int groups = ws_groups(ncg);
     size_t off = 0;
-    ws_arrays(g, ws, groups, [&](auto *&p, size_t count) {
+    ws.tau_words = (int)ws_tau_words(groups, false);
+    ws_arrays(g, ws, groups, (size_t)ws.tau_words, [&](auto *&p, size_t count) {
         p = (std::remove_reference_t<decltype(p)>)(base + off);
         off = align256(off + std::max<size_t>(count, 1) * sizeof(*p));
     });

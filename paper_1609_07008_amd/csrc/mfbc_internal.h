@@ -116,6 +116,7 @@ struct Workspace {
     uint32_t *tau2 = nullptr;          // tau per pair of groups, 16 bits a group [cg/2][n][64]
                                        // (read by the paired counting product); where T itself is
                                        // in 16 bits, its path counts
+    int tau_words = 0;                 // words of a lane and vertex in tau2
     unsigned long long *trace_relax = nullptr;  // trace: relaxations per product
     int trace_len = 0;
     char *quad_base = nullptr;         // memory behind `quad`, for batches of up to quad_ncg groups

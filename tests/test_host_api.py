@@ -302,3 +302,35 @@ def test_lanes_whose_threads_cannot_start_run_all_the_same(built):
                        preexec_fn=lambda: resource.setrlimit(resource.RLIMIT_STACK, (32 << 30, hard)))
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.split("\n")[-2] == "0 0 7 b''", r.stdout
+
+
+@pytest.mark.parametrize("nb", [64, 384])
+@pytest.mark.parametrize("percent", [100, 40])
+def test_calls_without_room_for_16_bits_run_in_32(lib, nb, percent):
+    """A device that holds the state of 32-bit products and not the 16-bit path
+    counts or bounds beside it: the calls run, as they did before those."""
+    lib.stub_core(percent)
+    rc, h = load(lib, gg.rmat_graph(13, 32, 3, wrange=(1, 255)))          # more than 2^18 arcs
+    src, out = sources(nb), ctypes.byref(ctypes.c_double(0))
+    calls = {
+        "forward": lambda: lib.mfbc_forward(h, src.ctypes.data, nb, out, out, None, None),
+        "sssp": lambda: lib.mfbc_fixpoint(h, 0, src.ctypes.data, nb, out, None, None),
+        "bc": lambda: lib.mfbc_bc(h, src.ctypes.data, nb, nb, out, None),
+    }
+    start = lib.stub_live()
+    assert calls["bc"]() == OK and b"quad_product" in lib.stub_log()
+    whole = lib.stub_live() - start
+    # one word a lane less: none is left of one group's, three of six groups' four,
+    # as many as the products on a core take
+    least = whole - (1 << 13) * 64 * 4 + (4 if nb == 64 else 0)
+    for cap, forms in ((whole, (False, False, True)), (least, (False, False, nb > 64)), (least - 4096, None)):
+        for (name, call), form in zip(calls.items(), forms or (None,) * 3):
+            lib.mfbc_free_graph(h)
+            rc, h = load(lib, gg.rmat_graph(13, 32, 3, wrange=(1, 255)))
+            lib.stub_clear()
+            lib.stub_cap(lib.stub_live() + cap)
+            assert call() == (ENOMEM if form is None else OK), (name, cap)
+            assert (b"quad_product" in lib.stub_log()) == bool(form), (name, cap)
+            lib.stub_cap(1 << 62)
+    assert lib.stub_faults() == b""
+    lib.mfbc_free_graph(h)
