@@ -336,15 +336,22 @@ int bad_source(mfbc_graph *g, const int32_t *d_sources, int64_t count, hipStream
 // Trace (d_rows non-null or h_relax non-null): frontier membership of F_j
 // after every product j <= max_products, as vertex bitmaps per column
 // (d_rows + (j-1) * nb * words), and the relaxations of every product.
-int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d_sources, bool trace, uint64_t *d_rows, int64_t *h_nnz,
-                int64_t *h_relax, int max_products, int32_t *products, hipStream_t s) {
-    launch_fwd_init(g, ncg, nb, d_sources, s);
+// from: the products that ran in 16 bits (run_quad), whose state is in place.
+struct Begun {
+    int j = 0;               // products run
+    int64_t prev = 0;        // entries of the last one's frontier
+};
+
+int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d_sources, const Begun &from, bool trace,
+                uint64_t *d_rows, int64_t *h_nnz, int64_t *h_relax, int max_products, int32_t *products,
+                hipStream_t s) {
+    if (!from.j) launch_fwd_init(g, ncg, nb, d_sources, s);
     if (trace) launch_trace_fwd(g, ncg, nb, 0, nullptr, s);
     const double arc_bytes = g->weighted ? 8.0 : 4.0;
     const size_t words = ((size_t)g->n + 63) / 64;
     mfbc_stats &st = g->stats;
-    int64_t prev = nb;           // the first frontier: one entry per source column
-    int j = 0, last = 0;
+    int64_t prev = from.j ? from.prev : nb;      // the first frontier: one entry per source column
+    int j = from.j, last = 0;
     while (!last) {
         if (j > g->n + 1) return fail(MFBC_EDEVICE, "forward products did not converge");
         for (int i = 0; i < kWindow; i++) {
@@ -392,18 +399,19 @@ int run_forward(mfbc_graph *g, const View &vw, int ncg, int nb, const int32_t *d
 }
 
 // Below this many arcs mfbc_forward and the fixpoint stay in 32 bits: a task's
-// fixed cost (bounds, live columns) shows there.  Distances and path counts of
-// 256 sources, ms in 32 / 16 bits: uniform n = 10,000 of degree 10 1.13 / 1.51,
-// weighted R-MAT scale 12 0.77 / 0.93, 14 1.50 / 1.47, 16 3.69 / 2.12, 18 (200
-// sources) 10.5 / 5.3.
+// fixed cost (bounds, live columns) shows there.  256 sources on weighted R-MAT
+// graphs, ms in 32 / 16 bits: path counts at scale 12 0.85 / 0.95, 13 0.94 /
+// 1.04, 14 1.53 / 1.40, 16 3.68 / 1.99, 18 (200 sources) 10.0 / 4.5; distances
+// 0.67 / 0.69, 0.84 / 1.00, 1.28 / 1.22, 2.69 / 1.64, 6.6 / 2.5.
 constexpr int64_t kQuadArcs = 1 << 18;
 
 // Algorithm 1, or the (min, a + w) fixpoint without multiplicities, in 16 bits
 // (d_sources nullable: already in ws.src): on every arc with bounds, on the
-// core without.  *fits becomes false, with nothing written, if the frontier
-// outlives the products whose entries fit, or the state has no room.
+// core without.  *fits becomes false if the state has no room, or if the
+// frontier outlives the products whose entries fit: then *begun says how many
+// ran, and the state is left as the next product in 32 bits reads it.
 int run_quad(mfbc_graph *g, bool core, bool count, int ncg, int nb, const int32_t *d_sources, int32_t *products,
-             bool *fits, hipStream_t s) {
+             bool *fits, Begun *begun, hipStream_t s) {
     const View &vw = core ? g->core : g->full;
     const int words = core || ncg <= 2 ? 1 : 2;
     const int most = core || g->arcs >= kQuadArcs ? quad_products(g, count) : 0;
@@ -418,13 +426,14 @@ int run_quad(mfbc_graph *g, bool core, bool count, int ncg, int nb, const int32_
     launch_quad_init(g, vw, count, ncg, nb, d_sources, s);
     const double arc_bytes = g->weighted ? 8.0 : 4.0;
     mfbc_stats &st = g->stats;
-    const mfbc_stats before = st;
     int64_t prev = nb;
     int j = 0, last = 0;
     while (!last) {
         if (j + kWindow > most) {
             *fits = false;
-            g->stats = before;
+            launch_quad_widen(g, vw, count, ncg, j, s);
+            begun->j = j;
+            begun->prev = prev;
             return MFBC_OK;
         }
         for (int i = 0; i < kWindow; i++) launch_quad_product(g, vw, count, ncg, j + 1 + i, s, window_events(g, i, true));
@@ -521,12 +530,15 @@ int run_backward(mfbc_graph *g, const View &vw, int ncg, int nb, bool tau16, int
 }
 
 // One batch of Algorithm 3: the forward products in 16 bits where they fit (two
-// groups to a word, the layout that the counting product reads), else in 32.
+// groups to a word, the layout that the counting product reads), else, or from
+// the first one that does not, in 32.
 int run_batch(mfbc_graph *g, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
     int rc;
     bool tau16 = false;
-    if ((rc = run_quad(g, true, true, ncg, nb, d_sources, nullptr, &tau16, s))) return rc;
-    if (!tau16 && (rc = run_forward(g, g->core, ncg, nb, d_sources, false, nullptr, nullptr, nullptr, 0, nullptr, s)))
+    Begun begun;
+    if ((rc = run_quad(g, true, true, ncg, nb, d_sources, nullptr, &tau16, &begun, s))) return rc;
+    if (!tau16 && (rc = run_forward(g, g->core, ncg, nb, d_sources, begun, false, nullptr, nullptr, nullptr, 0, nullptr,
+                                    s)))
         return rc;
     return run_backward(g, g->core, ncg, nb, tau16, nullptr, s);
 }
@@ -563,7 +575,8 @@ int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d
     }
     g->stats = mfbc_stats{};
     bool fits = false;
-    if (!trace && (rc = run_quad(g, false, true, ncg, nb, d_sources, h_products, &fits, s))) return rc;
+    Begun begun;
+    if (!trace && (rc = run_quad(g, false, true, ncg, nb, d_sources, h_products, &fits, &begun, s))) return rc;
     if (fits) {
         g->stats.batches = 1;
         launch_quad_rows(g, true, ncg, nb, d_dist, d_sigma, s);
@@ -571,7 +584,8 @@ int forward_impl(mfbc_graph *g, const int32_t *d_sources, int32_t nb, int32_t *d
         HIP_TRY(hipStreamSynchronize(s));
         return MFBC_OK;
     }
-    if ((rc = run_forward(g, g->full, ncg, nb, d_sources, trace, d_rows, h_nnz, h_relax, max_products, h_products, s)))
+    if ((rc = run_forward(g, g->full, ncg, nb, d_sources, begun, trace, d_rows, h_nnz, h_relax, max_products, h_products,
+                          s)))
         return rc;
     g->stats.batches = 1;
     launch_export_forward(g, ncg, nb, d_dist, d_sigma, s);
@@ -1387,10 +1401,11 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
     if ((rc = ensure_workspace(g, ncg))) return rc;
     g->stats = mfbc_stats{};
     const bool bits = bits_fit(g, op);
+    Begun begun;
     if (op == MFBC_OP_SSSP && !bits) {
         bool fits = false;
         int32_t products = 0;
-        if ((rc = run_quad(g, false, false, ncg, nb, d_sources, &products, &fits, s))) return rc;
+        if ((rc = run_quad(g, false, false, ncg, nb, d_sources, &products, &fits, &begun, s))) return rc;
         if (fits) {
             g->stats.batches = 1;
             if (h_products) *h_products = products;
@@ -1401,12 +1416,12 @@ int mfbc_fixpoint(mfbc_graph *g, int32_t op, const int32_t *d_sources, int32_t n
         }
     }
     if (bits) launch_bits_init(g, ncg, nb, d_sources, s);
-    else launch_mono_init(g, op, ncg, nb, d_sources, s);
+    else if (!begun.j) launch_mono_init(g, op, ncg, nb, d_sources, s);
     int planes = 0;              // planes of the product number cleared so far
     const double arc_bytes = g->weighted && op != MFBC_OP_BFS ? 8.0 : 4.0;
     mfbc_stats &st = g->stats;
-    int64_t prev = nb;
-    int j = 0, last = 0;
+    int64_t prev = begun.j ? begun.prev : nb;
+    int j = begun.j, last = 0;
     // windows of products with one counter read-back each, as in MFBF
     while (!last) {
         if (j > g->n + 1) return fail(MFBC_EDEVICE, "fixpoint products did not converge");

@@ -257,6 +257,8 @@ void launch_quad_init(mfbc_graph *g, const View &vw, bool count, int ncg, int nb
                       hipStream_t s);
 void launch_quad_product(mfbc_graph *g, const View &vw, bool count, int ncg, int j, hipStream_t s,
                          hipEvent_t *ev);
+// After product j: the state as the 32-bit product j + 1 reads it.
+void launch_quad_widen(mfbc_graph *g, const View &vw, bool count, int ncg, int j, hipStream_t s);
 void launch_quad_rows(mfbc_graph *g, bool count, int ncg, int nb, int32_t *dist, double *sigma, hipStream_t s);
 
 // ---- shortest-path core (core.hip) ----

@@ -12,8 +12,8 @@
 //    with Q = 2 one instruction serves 256 columns.  m = 2^mb - 1 means "or
 //    more": the value is in the binary64 array, and sums that reach it are
 //    taken again in binary64, over the row's arcs in order.  The encoding is
-//    exact.  A call whose frontier outlives the products that fit starts over
-//    in 32 bits (quad_products).  T in this layout is what the paired counting
+//    exact.  A call whose frontier outlives the products that fit
+//    (quad_products) goes on in 32 bits from there (k_quad_widen).  T in this layout is what the paired counting
 //    product of a centrality call reads, so no copy of it is made.  T's
 //    multiplicities are kept the same way, 16 bits with the binary64 array behind
 //    those that do not fit: a kept entry writes 6 bytes where it wrote 12, and
@@ -717,6 +717,93 @@ __global__ __launch_bounds__(kBlock) void k_quad_sigma(const uint32_t *t, const 
     }
 }
 
+// The batch's state after product j in the layouts of the 32-bit products, for
+// product j + 1: T, path counts and, where COUNT, packed frontier tuples with
+// their escaped multiplicities (FwdPull), else frontier distances (MonoPull).
+// One wave per row of a wave's groups; the rows come from a copy, since the wide
+// arrays lie where the 16-bit ones did.  Bound by the writes, 12 to 24 B an
+// entry: 5 us for 256 columns of 3,280 vertices.  Starting over in 32 bits
+// instead, ms for 256 sources on chains of cliques of 82 vertices with weights
+// to 255: path counts 11.8, 9.0 so (201 products); centrality 12.2 and 10.0; with
+// one weight, ties everywhere, 8.9 and 6.1 (80 products), 8.9 and 6.1.
+struct WidenArgs {
+    const uint32_t *t, *f;       // copies, [q][n][64][Q]
+    const uint32_t *sig;
+    const uint32_t *bits;        // F_j's bitmaps, [q][nwords]
+    int n, nwords, nq, ncg;
+    int mb16, mb;                // bits of a multiplicity, as read and as written
+    int32_t *tdist;
+    double *tsig, *fsig;         // fsig: F_j's, where the 16-bit form's escapes are already
+    uint32_t *fw;                // F_j: [pair][n][64][2], one group [n][64]
+};
+
+template <int Q, bool COUNT>
+__global__ __launch_bounds__(kBlock) void k_quad_widen(WidenArgs a) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const size_t row = (size_t)blockIdx.x * kWavesPerBlock + (size_t)uni((int)(threadIdx.x >> 6)), n = (size_t)a.n;
+    if (row >= n * (size_t)a.nq) return;
+    const int q = (int)(row / n), v = (int)(row - (size_t)q * n);
+    const bool act = (a.bits[(size_t)q * a.nwords + (v >> 5)] >> (v & 31)) & 1u;
+    const Lane<Q> t = load_lane<Q>(a.t, row, lane);
+    Lane<Q> f, s;
+#pragma unroll
+    for (int k = 0; k < Q; k++) f.w[k] = s.w[k] = kNone32;
+    if (act) f = load_lane<Q>(a.f, row, lane);
+    if constexpr (COUNT) s = load_lane<Q>(a.sig, row, lane);
+    constexpr uint32_t kAbsent = COUNT ? kSent : (uint32_t)kInf;
+    const uint32_t m16 = COUNT ? (1u << a.mb16) - 1u : 0u, m32 = COUNT ? (1u << a.mb) - 1u : 0u;
+#pragma unroll
+    for (int k = 0; k < Q; k++) {
+        uint32_t w[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int cg = (q * Q + k) * 2 + h;
+            w[h] = kAbsent;
+            if (cg >= a.ncg) continue;
+            const size_t i = ((size_t)cg * n + (size_t)v) * kWave + lane;
+            const uint32_t d = half_of(t.w[k], h), x = half_of(f.w[k], h);
+            a.tdist[i] = d == kNone16 ? kInf : (int32_t)d;
+            if constexpr (COUNT) {
+                const uint32_t c = half_of(s.w[k], h);
+                if (d != kNone16 && c != kSig16Far) a.tsig[i] = (double)c;
+                if (x != kNone16) {
+                    const double m = (x & m16) != m16 ? (double)(x & m16) : a.fsig[i];
+                    const uint32_t ms = m <= (double)m32 ? (uint32_t)m : 0u;
+                    if (!ms) a.fsig[i] = m;
+                    w[h] = ((x >> a.mb16) << a.mb) | ms;
+                }
+            } else if (x != kNone16) {
+                w[h] = x;
+            }
+        }
+        if (!act) continue;
+        const size_t pair = (size_t)(q * Q + k);
+        if (a.ncg == 1) a.fw[(size_t)v * kWave + lane] = w[0];
+        else if (2 * (int)pair < a.ncg) ((uint2 *)a.fw)[(pair * n + (size_t)v) * kWave + lane] = make_uint2(w[0], w[1]);
+    }
+}
+
+__global__ void k_quad_copy(const uint32_t *t, const uint32_t *f, uint32_t *t2, uint32_t *f2, size_t words) {
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += stride) {
+        t2[i] = t[i];
+        f2[i] = f[i];
+    }
+}
+
+// F_j's bitmaps from one per Q pairs to one per pair, in place (from the last
+// pair down, a pair's own plane has been read when it is written); the other two
+// buffers cleared.
+__global__ void k_quad_widen_bits(uint32_t *bits, uint32_t *other0, uint32_t *other1, int nwords, int npairs, int Q) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nwords) return;
+    for (int p = npairs - 1; p >= 0; p--) {
+        bits[(size_t)p * nwords + i] = bits[(size_t)(p / Q) * nwords + i];
+        other0[(size_t)p * nwords + i] = 0u;
+        other1[(size_t)p * nwords + i] = 0u;
+    }
+}
+
 int grid_for(size_t work, int per, size_t cap = 0x7fffffff) {
     return (int)std::max<size_t>(1, std::min<size_t>((work + per - 1) / per, cap));
 }
@@ -830,6 +917,35 @@ void quad_product(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s, 
     if (ev && ev[2]) (void)hipEventRecord(ev[2], s);
 }
 
+template <int Q, bool COUNT, bool B>
+void quad_widen(mfbc_graph *g, const View &vw, int ncg, int j, hipStream_t s) {
+    Workspace &ws = g->ws;
+    const QuadArgs a = quad_args(g, vw, ncg, j);
+    const size_t rows = (size_t)a.nq * g->n, words = rows * kWave * Q;
+    // the multiplicities of F_{j-1} are done with: room for both copies
+    uint32_t *t2 = (uint32_t *)ws.fsig[(j & 1) ^ 1], *f2 = t2 + words;
+    hipLaunchKernelGGL(k_quad_copy, dim3(grid_for(words, 1024, 16384)), dim3(256), 0, s, (const uint32_t *)a.t,
+                       (const uint32_t *)a.f_n, t2, f2, words);
+    WidenArgs w{};
+    w.t = t2;
+    w.f = f2;
+    w.sig = a.sig;
+    w.bits = a.bits_n;
+    w.n = a.n;
+    w.nwords = a.nwords;
+    w.nq = a.nq;
+    w.ncg = ncg;
+    w.mb16 = a.mbn;
+    w.mb = g->mb;
+    w.tdist = ws.tdist;
+    w.tsig = ws.tsig;
+    w.fsig = ws.fsig[j & 1];
+    w.fw = (uint32_t *)ws.fdist[j & 1];
+    hipLaunchKernelGGL((k_quad_widen<Q, COUNT>), dim3(grid_for(rows, kWavesPerBlock)), dim3(kBlock), 0, s, w);
+    hipLaunchKernelGGL(k_quad_widen_bits, dim3(grid_for(a.nwords, 256)), dim3(256), 0, s, a.bits_n,
+                       ws.abits[(j + 1) % 3], ws.abits[(j + 2) % 3], a.nwords, (ncg + 1) / 2, Q);
+}
+
 template <int Q, bool COUNT>
 void quad_rows_out(mfbc_graph *g, int ncg, int nb, int32_t *dist, double *sigma, hipStream_t s) {
     const uint32_t *t = (const uint32_t *)g->ws.tdist;
@@ -844,14 +960,15 @@ void quad_rows_out(mfbc_graph *g, int ncg, int nb, int32_t *dist, double *sigma,
 }  // namespace
 
 // Products whose entries fit 16 bits, in whole windows; 0 where so few do
-// that a call would often start over in 32 bits.  Distances need j * maxw <
-// 65535, multiplicities two bits besides: weights up to 255 fit 56 products
-// with multiplicities (most graphs take 10 to 25), 256 without.
-// A graph of short rows (grids, paths) may take any number of products and
-// gains little (uniform n = 10,000 of degree 10, 900 sources: 5.3 ms of
-// centrality in 32 bits, 5.0 in 16; a grid of 30 by 30 with weights to 255, 62
-// products: 2.1 in 32 bits, 2.6 with the 56 that fit taken twice), so it has
-// to fit whole: no shortest path has more arcs than vertices.
+// that most of a call would run in 32 bits all the same.  Distances need j *
+// maxw < 65535, multiplicities two bits besides: weights up to 255 fit 56
+// products with multiplicities (most graphs take 10 to 25), 256 without.  A
+// graph of short rows (grids, paths) may take any number of products and has
+// to fit whole (no shortest path has more arcs than vertices).  Centrality of
+// 256 sources, ms in 32 bits throughout / in 16 as far as they go: a grid of 30
+// by 30 with weights to 255, 62 products, 1.76 / 1.76; of 100 by 100, 211
+// products, 11.6 / 11.7; uniform of degree 10, n = 10,000, 900 sources 5.1 /
+// 4.9, n = 100,000 8.1 / 6.1.
 int quad_products(const mfbc_graph *g, bool count) {
     constexpr int kLeast = 40;
     const int64_t most = count ? ((int64_t)1 << 14) - 1 : 65535;
@@ -898,6 +1015,9 @@ void launch_quad_init(mfbc_graph *g, const View &vw, bool count, int ncg, int nb
 void launch_quad_product(mfbc_graph *g, const View &vw, bool count, int ncg, int j, hipStream_t s,
                          hipEvent_t *ev) {
     MFBC_QUAD(quad_product, g, vw, ncg, j, s, ev);
+}
+void launch_quad_widen(mfbc_graph *g, const View &vw, bool count, int ncg, int j, hipStream_t s) {
+    MFBC_QUAD(quad_widen, g, vw, ncg, j, s);
 }
 void launch_quad_rows(mfbc_graph *g, bool count, int ncg, int nb, int32_t *dist, double *sigma, hipStream_t s) {
     if (g->ws.quad.words == 1 && count) quad_rows_out<1, true>(g, ncg, nb, dist, sigma, s);

@@ -295,6 +295,9 @@ void launch_quad_product(mfbc_graph *g, const View &v, bool count, int ncg, int 
     check("quad_product", g, v, ncg, count);
     produced(g, j, j < products);
 }
+void launch_quad_widen(mfbc_graph *g, const View &v, bool count, int ncg, int, hipStream_t) {
+    check("quad_widen", g, v, ncg, count);
+}
 void launch_quad_rows(mfbc_graph *, bool, int, int, int32_t *, double *, hipStream_t) {}
 
 bool core_worth_trying(const mfbc_graph *g) { return g->weighted && core_percent < 100; }

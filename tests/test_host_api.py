@@ -334,3 +334,28 @@ def test_calls_without_room_for_16_bits_run_in_32(lib, nb, percent):
             lib.stub_cap(1 << 62)
     assert lib.stub_faults() == b""
     lib.mfbc_free_graph(h)
+
+
+def test_products_that_ran_in_16_bits_are_not_run_again(lib):
+    """A frontier that outlives the products whose entries fit (56 here): the
+    call goes on in 32 bits from there, in every batch."""
+    rc, h = load(lib, gg.rmat_graph(13, 32, 3, wrange=(1, 255)))          # more than 2^18 arcs
+    lib.stub_quad_fit(56)
+    src, out = sources(200), ctypes.byref(ctypes.c_double(0))
+    count = ctypes.c_int32(0)
+    for fwd in (56, 57, 100):
+        lib.stub_products(fwd, 3)
+        wide = 0 if fwd == 56 else -(-(fwd - 56) // 8) * 8
+        for batches, name, call in (
+                (1, b"fwd", lambda: lib.mfbc_forward(h, src.ctypes.data, 200, out, out, ctypes.byref(count), None)),
+                (1, b"mono", lambda: lib.mfbc_fixpoint(h, 0, src.ctypes.data, 200, out, ctypes.byref(count), None)),
+                (3, b"fwd", lambda: lib.mfbc_bc(h, src.ctypes.data, 200, 70, out, None))):
+            lib.stub_clear()
+            lib.mfbc_set_lanes(h, 1)
+            assert call() == OK
+            log = lib.stub_log()
+            assert log.count(b"quad_product") == 56 * batches and log.count(name + b"_product") == wide * batches
+            assert log.count(b"quad_widen") == (batches if wide else 0)
+            assert count.value == fwd
+    assert lib.stub_faults() == b""
+    lib.mfbc_free_graph(h)
