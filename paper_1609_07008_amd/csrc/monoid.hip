@@ -9,11 +9,11 @@
 // the generic pull product of pull.h -- the same function MFBF's forward
 // product instantiates -- with MonoPull as its policy.  Instances:
 //   SSSP    int32, (+) = min, f(a, w) = a + w          shortest-path distances
-//   BFS     int32, (+) = min, f(a, w) = a + 1          hop levels
 //   Widest  int32, (+) = max, f(a, w) = min(a, w)      bottleneck capacities
 //   Resist  float, (+) = min, f(a, w) = a + 1/w        least sum of 1/w along a
 //           path (binary32, every operation IEEE round-to-nearest)
-// Unlike MFBF no multiplicity is carried, so a tie does not re-enter the
+// Hop levels, and every algebra where all weights are 1, run on bit masks
+// (bits.hip).  Unlike MFBF no multiplicity is carried, so a tie does not re-enter the
 // frontier: an entry joins frontier j exactly when product j improved it
 // (strictly, in the order of (+)).
 //
@@ -58,15 +58,6 @@ struct OpSssp {
     __device__ static V absent() { return kInf; }
     __device__ static V seed() { return 0; }
     __device__ static V act(V x, int w) { return x + w; }
-    __device__ static V plus(V x, V y) { return min(x, y); }
-    __device__ static bool better(V x, V y) { return x < y; }
-};
-
-struct OpBfs {
-    using V = int32_t;
-    __device__ static V absent() { return kInf; }
-    __device__ static V seed() { return 0; }
-    __device__ static V act(V x, int) { return x + 1; }
     __device__ static V plus(V x, V y) { return min(x, y); }
     __device__ static bool better(V x, V y) { return x < y; }
 };
@@ -312,7 +303,10 @@ int mono_mode(const Csr &c) { return c.pk ? 1 : (c.w ? 2 : 0); }
 template <class Op, int W, bool C>
 void launch_pull(int mode, int grid, hipStream_t s, const MonoArgs &a) {
     switch (mode) {
-        case 0: hipLaunchKernelGGL((k_mono_pull<Op, 0, W, C>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 0:              // unit weights: the sums that bits.hip does not hold alone (bits_fit)
+            if constexpr (std::is_same_v<Op, OpResist>)
+                hipLaunchKernelGGL((k_mono_pull<Op, 0, W, C>), dim3(grid), dim3(kBlock), 0, s, a);
+            break;
         case 1: hipLaunchKernelGGL((k_mono_pull<Op, 1, W, C>), dim3(grid), dim3(kBlock), 0, s, a); break;
         default: hipLaunchKernelGGL((k_mono_pull<Op, 2, W, C>), dim3(grid), dim3(kBlock), 0, s, a); break;
     }
@@ -403,7 +397,6 @@ bool mono_op_known(int op) {
 void launch_mono_init(mfbc_graph *g, int op, int ncg, int nb, const int32_t *d_sources, hipStream_t s) {
     switch (op) {
         case MFBC_OP_SSSP: mono_init<OpSssp>(g, ncg, nb, d_sources, s); break;
-        case MFBC_OP_BFS: mono_init<OpBfs>(g, ncg, nb, d_sources, s); break;
         case MFBC_OP_WIDEST: mono_init<OpWidest>(g, ncg, nb, d_sources, s); break;
         default: mono_init<OpResist>(g, ncg, nb, d_sources, s); break;
     }
@@ -412,7 +405,6 @@ void launch_mono_init(mfbc_graph *g, int op, int ncg, int nb, const int32_t *d_s
 void launch_mono_product(mfbc_graph *g, int op, int ncg, int j, hipStream_t s, hipEvent_t *ev) {
     switch (op) {
         case MFBC_OP_SSSP: mono_product<OpSssp>(g, ncg, j, s, ev); break;
-        case MFBC_OP_BFS: mono_product<OpBfs>(g, ncg, j, s, ev); break;
         case MFBC_OP_WIDEST: mono_product<OpWidest>(g, ncg, j, s, ev); break;
         default: mono_product<OpResist>(g, ncg, j, s, ev); break;
     }
