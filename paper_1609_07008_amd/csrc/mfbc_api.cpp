@@ -849,7 +849,8 @@ int build_core(mfbc_graph *g, hipStream_t s) {
         to = from;
     }
     // kept as the columns' offsets in the bounds of quad.hip, core or not
-    if (!dalloc(&g->hub_dist, n)) launch_core_hub(to, g->n, g->hub_dist, s);
+    const bool bounds = g->arcs >= kQuadArcs && (quad_products(g, true) > 0 || quad_products(g, false) > 0);
+    if (bounds && !dalloc(&g->hub_dist, n)) launch_core_hub(to, g->n, g->hub_dist, s);
     View c;
     rc = core_csr(g, g->full.out, g->full.plan_out, to, from, keep, cnt, c.out, g->h_core_rp_out, s);
     if (!rc && c.out.rp && g->directed)

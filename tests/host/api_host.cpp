@@ -308,7 +308,10 @@ void launch_core_mark(const Csr &c, const Plan &, const int32_t *, const int32_t
     for (size_t v = 0; v < n; v++) cnt[v] = (int32_t)((c.rp[v + 1] - c.rp[v]) * core_percent / 100);
 }
 void launch_core_zero(int32_t *, int, hipStream_t) {}
-void launch_core_hub(const int32_t *, int, int32_t *, hipStream_t) {}
+void launch_core_hub(const int32_t *, int, int32_t *, hipStream_t) {
+    std::lock_guard<std::mutex> lock(mu);
+    log_ += "core_hub ";
+}
 void launch_core_compact(int32_t, const Csr &, const uint8_t *, const Csr &, hipStream_t) {}
 
 }  // namespace mfbc

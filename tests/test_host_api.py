@@ -359,3 +359,17 @@ def test_products_that_ran_in_16_bits_are_not_run_again(lib):
             assert count.value == fwd
     assert lib.stub_faults() == b""
     lib.mfbc_free_graph(h)
+
+
+@pytest.mark.parametrize("scale,fit,kept", [(9, 56, False), (13, 56, True), (13, 0, False)])
+def test_load_keeps_column_offsets_where_they_are_read(lib, scale, fit, kept):
+    """The distances to one landmark serve the bounds of the 16-bit products on
+    every arc: graphs of 2^18 arcs and more whose weights leave room for them."""
+    lib.stub_quad_fit(fit)
+    for percent in (40, 99):                                # with a core, and where one was tried
+        lib.stub_core(percent)
+        lib.stub_clear()
+        rc, h = load(lib, gg.rmat_graph(scale, 32, 3, wrange=(1, 255)))
+        assert rc == OK and (b"core_hub" in lib.stub_log()) == kept
+        assert every_call(lib, h, 0) == [OK] * 7 and lib.stub_faults() == b""
+        lib.mfbc_free_graph(h)
