@@ -34,8 +34,11 @@
  *     T and two frontier buffers, which the backward state reuses -- plus
  *     8 B per (group of 64 columns, arc) for the shortest-path DAG that the
  *     counting product stores for the backward products (1 GiB at 2^25 arcs
- *     and 256 columns).  It grows to the largest batch seen and is freed
- *     with the graph; ENOMEM if it does not fit.
+ *     and 256 columns; of a weighted graph only the arcs that can lie on a
+ *     shortest path count).  It grows to the largest batch seen and is freed
+ *     with the graph; ENOMEM if it does not fit.  mfbc_bc may run several
+ *     batches together and then holds the state of all of them
+ *     (mfbc_set_lanes bounds that, and says how).
  *   - hip_stream is a hipStream_t (NULL = the default stream).  Calls are
  *     ordered on that stream and return after their outputs are complete
  *     (they synchronise on the stream to read frontier sizes: products are
@@ -95,6 +98,16 @@ typedef struct mfbc_graph mfbc_graph;
  *            caller's order, and results equal those of MFBC_KEEP_ORDER up
  *            to the summation order of floating-point sums.
  *   out      receives the handle.
+ * A weighted graph whose arcs' rows hold 16 arcs and more on average is also
+ * searched for the arcs that can lie on a shortest path: distances over at
+ * most six arcs from (directed: and to) 64 vertices, on hip_stream, then one
+ * pass over the arcs.  Where at most three quarters remain, the handle keeps
+ * them as a second CSR with plans of its own (4 B an arc, or 8 where column
+ * and weight do not pack into 32 bits, 1 B of plan an arc, 8 B a vertex and
+ * orientation); centrality and dependencies run on it.  The search takes 0.3
+ * to 0.5 ms on graphs of 100,000 arcs, 2 ms of 17 at 1.8 million, 18 ms of 780
+ * at 31 million, and while it runs 768 B a vertex (directed: 1 KiB) and 1 B an
+ * arc; a graph for which that memory is short is loaded without.
  * Errors: EINVAL (malformed CSR, weight <= 0, asymmetric undirected input),
  * EOVERFLOW (n * max weight >= 2^31 - 1), ENOMEM, EDEVICE.
  */
@@ -149,9 +162,9 @@ int mfbc_backward(mfbc_graph *g, const int32_t *d_sources, int32_t nb,
  *   d_bc[n]        device out, overwritten.
  *   The batches are independent (Algorithm 3 sums their contributions), so
  *   where their products are small several run as one wide batch, one launch
- *   and one read-back for all of them; with a lane count set (mfbc_set_lanes)
- *   that many run at once on separate streams instead, each lane with its own
- *   workspace; lane 0 uses hip_stream, the others library-owned streams
+ *   and one read-back for all of them; where they are larger, or a lane count
+ *   is set (mfbc_set_lanes), several run at once on separate streams, each
+ *   lane with its own workspace; lane 0 uses hip_stream, the others library-owned streams
  *   ordered after the work already on hip_stream.  Lambda is summed in a
  *   fixed order, so repeated calls with the same lane count are bitwise
  *   identical.
@@ -206,19 +219,23 @@ int mfbc_bc_requests(mfbc_graph *g, const int32_t *d_sources, const int64_t *h_f
  * (code under stream capture, tight serving loops, harnesses that forbid
  * hipMalloc): same arguments, results and errors as mfbc_bc, but the call
  * allocates nothing.  The batch state lives in a static scratch area of
- * 64 MiB per device, part of the library's code object (every GPU the library
+ * 84 MiB per device, part of the library's code object (every GPU the library
  * runs on holds it until the process ends); the graph's own workspace is not
  * used or changed.  Sources are checked on the device.
- *   Limit: the state of one batch of min(batch, n_sources) sources must fit
- *   the scratch -- about 39 B per (source column, vertex), columns counted in
- *   whole groups of 64 (an even number of groups when there are two or more),
- *   plus 8 B per (group, arc) and the graph's hub partials; a larger request
- *   fails with MFBC_ENOMEM before any device work (n = 1024 with batches of
- *   256 fits; n = 65536 with batches of 512 does not).
+ *   Limit: a call is admitted if the state of one batch of min(batch,
+ *   n_sources) sources takes at most 64 MiB -- about 39 B per (source column,
+ *   vertex), columns counted in whole groups of 64 (an even number of groups
+ *   when there are two or more), plus 8 B per (group, arc) and, where rows are
+ *   cut as mfbc_set_plan says (by default above 1024 arcs into slices of 512),
+ *   their partials; a larger request fails with MFBC_ENOMEM before any device
+ *   work (n = 1024 with batches of 256 fits; n = 65536 with batches of 512 does
+ *   not).  The rest of the scratch covers what the products hold beyond that.
+ *   Should it not, for one group of 64 columns under a plan with very many
+ *   slices, the call fails with MFBC_ENOMEM, too, before any device work.
  *   Every call on a device uses that device's one scratch area and leaves its
  *   contents behind: calls that overlap on one device (other threads, other
  *   streams) race and must be serialised by the caller.
- * Errors: as mfbc_bc (ENOMEM when the batch state exceeds the scratch).
+ * Errors: as mfbc_bc (ENOMEM as above).
  */
 int mfbc_bc_noalloc(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources,
                     int32_t batch, double *d_bc, void *hip_stream);
@@ -394,7 +411,7 @@ int mfbc_graph_info(const mfbc_graph *g, int32_t *n, int64_t *n_arcs,
  * The library keeps a grow-only workspace per device for this call, shared
  * by every call on that device: calls on one device must not overlap (one
  * host thread at a time), and the graphs of a call follow the one-thread rule
- * above for its duration.
+ * above for its duration; a server on one of them may step meanwhile.
  * Errors: EINVAL, ENOMEM, EOVERFLOW, EDEVICE.
  */
 typedef struct mfbc_many_config {

@@ -81,11 +81,10 @@ def _time(fn, reps: int) -> float:
     return best
 
 
-LANE_CANDIDATES = (0, 1, 2, 4)       # 0: several batches as one wide one
+LANE_CANDIDATES = (0, 1, 2, 4)       # 0: the library's own choice
 # lanes are tuned only where one product of a batch is small next to the
-# device (arcs x column groups below this): on large products concurrent
-# batches only share the memory bandwidth, and each kernel's own duration --
-# the denominator of its roofline figure -- would stretch
+# device (arcs x column groups below this); above, the library's choice
+# stands, by the arcs that its products read
 LANE_TUNE_MAX = 1 << 25
 
 

@@ -940,15 +940,25 @@ int bc_batches(mfbc_graph *g, const int32_t *d_sources, int64_t n_sources, int32
 
 // How the batches of one mfbc_bc call run when no lane count is set (a
 // column depends on its own column of every product alone, Section 3), by the
-// arcs times column groups of one batch:
+// core's arcs times the column groups of one batch:
 //  * up to 2^21, where a product is mostly latency: as one wide batch of four,
 //    or of as many as keep the state within 256 MB, so a small graph's whole
-//    source list shares each launch and read-back (n = 1,024 of degree 8, all
-//    sources in batches of 64: 3.95 ms on four streams, 1.04 as one batch);
+//    source list shares each launch and read-back;
 //  * up to 2^24: on four streams, each product large enough to fill the device
-//    only partly (unweighted R-MAT scale 16, 2,048 sources in batches of 512:
-//    18.4 ms, 19.5 as one wide batch);
-//  * above: one after another.
+//    only partly;
+//  * above: one after another, since the others gain little there for four
+//    times the state.
+// ms apart / on four streams / as one wide batch of four:
+//   2^13    n = 1,024 of degree 8, 1,024 in batches of 64    9.6 / 2.9 / 2.8 (1.0 all in one)
+//   2^19.2  weighted R-MAT scale 16, 1,024 in 256            6.2 / 3.6 / 3.9
+//   2^20.8  unweighted R-MAT scale 16, 256 in 64             4.2 / 2.4 / 2.0
+//   2^21.2  weighted R-MAT scale 18, 1,024 in 256           13.9 / 11.1 / 11.6
+//   2^22.9  unweighted R-MAT scale 18, 256 in 64             8.6 / 7.7 / 5.9
+//   2^23.3  weighted R-MAT scale 20, 1,024 in 256           37.0 / 32.4 / 33.2
+//   2^23.8  unweighted R-MAT scale 16, 2,048 in 512         13.9 / 11.9 / 12.3
+//   2^24.9  unweighted R-MAT scale 18, 1,024 in 256         21.8 / 21.3 / 20.6
+// (batches of one group would rather be wide at 2^23, too; the rule does not
+// look at the groups alone.)
 // The state of batches that run together without being asked for stays within
 // kLaneBytes (a sixth of a device's 288 GB; four lanes of 256 sources at n =
 // 2^20 hold 42 GB): it is kept until the graph is freed.
@@ -1130,12 +1140,13 @@ struct WorkspaceSwap {
 // persistent launch the time of its largest job (eight waves: 1.5 us an
 // of M) or, with every workgroup busy, 2.8 ns an arc.  Measured, streams /
 // persistent, in ms:
-//   3 graphs of 300                     0.9 / 1.9    32 of 200..6,000       29 / 94
-//   8 of 200..1,000                     2.1 / 9.2    24 of 200..20,000     209 / 410
-//   16 of 1,000..1,200, degree 40..64   5.2 / 19     64 of 200..20,000     344 / 496
-//   40 of 200..2,000                     11 / 28     96 of 4,000..6,000    364 / 471
-//   100 of 200..3,000                    38 / 57     200 of 200..1,000      46 / 22
-//   64 of 1,000..1,200, degree 4..8     24.5 / 24.2
+//   3 graphs of 300                     0.9 / 2.0    32 of 200..6,000       27 / 98
+//   8 of 200..1,000                     2.2 / 9.3    24 of 200..20,000     200 / 413
+//   16 of 1,000..1,200, degree 40..64   4.9 / 19     64 of 200..20,000     330 / 498
+//   40 of 200..2,000                     11 / 28     96 of 4,000..6,000    351 / 472
+//   100 of 200..3,000                    38 / 58     200 of 200..1,000      46 / 23
+//   64 of 1,000..1,200, degree 4..8      26 / 24.5   100 of 200..1,000      23 / 17
+//   150 of 200..2,000                    42 / 42
 bool many_underfilled(const std::vector<mfbc_graph *> &gs, const std::vector<int64_t> &ns) {
     double total = 0, most = 0;
     for (size_t i = 0; i < gs.size(); i++) {

@@ -304,7 +304,8 @@ def bc_many(graphs, sources, block_threads: int = 0, blocks: int = 0, job_width:
 
     ``graphs``: DeviceGraph list; ``sources``: one int32 source list (numpy
     or CUDA tensor) per graph; ``job_width``: sources per job, 64 or 128
-    (0 = 64).  Returns a list of float64[n_i] tensors.
+    (0 = 64); ``blocks``: fewer than fill the device ask for the persistent
+    launch on that many workgroups.  Returns a list of float64[n_i] tensors.
     """
     import torch
     lib = load_library()
