@@ -1716,9 +1716,9 @@ int mfbc_bc_many(int32_t n_graphs, mfbc_graph *const *graphs, const int32_t *con
     int rc;
     for (int32_t i = 0; i < n_graphs; i++)
         if ((rc = check_sources(gs[(size_t)i], src[(size_t)i], ns[(size_t)i], s))) return rc;
-    hipDeviceProp_t prop;
-    HIP_TRY(hipGetDeviceProperties(&prop, dev));
-    const int full = (2048 / block_threads) * prop.multiProcessorCount;   // 8 waves per SIMD
+    int cus = 0;
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int full = (2048 / block_threads) * cus;       // 8 waves per SIMD
     int blocks = config && config->blocks > 0 ? config->blocks : full;
     // fewer workgroups than fill the device: the caller leaves the rest of it to
     // others, which the streams would take

@@ -174,8 +174,8 @@ hipError_t hipGetDevice(int *d) {
     return hipSuccess;
 }
 hipError_t hipSetDevice(int) { return hipSuccess; }
-hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) {
-    p->multiProcessorCount = 256;
+hipError_t hipDeviceGetAttribute(int *value, hipDeviceAttribute_t, int) {
+    *value = 256;
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }

@@ -14,9 +14,7 @@ enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2 };
 enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2 };
 typedef struct stubStream *hipStream_t;
 typedef struct stubEvent *hipEvent_t;
-struct hipDeviceProp_t {
-    int multiProcessorCount;
-};
+enum hipDeviceAttribute_t { hipDeviceAttributeMultiprocessorCount = 63 };
 constexpr unsigned hipStreamNonBlocking = 1, hipEventDisableTiming = 2;
 
 const char *hipGetErrorString(hipError_t);
@@ -32,7 +30,7 @@ hipError_t hipMemsetAsync(void *p, int value, size_t bytes, hipStream_t);
 hipError_t hipGetSymbolAddress(void **p, const void *symbol);
 hipError_t hipGetDevice(int *device);
 hipError_t hipSetDevice(int device);
-hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int device);
+hipError_t hipDeviceGetAttribute(int *value, hipDeviceAttribute_t, int device);
 hipError_t hipDeviceSynchronize();
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned flags);
 hipError_t hipStreamDestroy(hipStream_t);
