@@ -4,6 +4,8 @@
 // amount, and checks, at every launch, that the plan and the workspace handed
 // to a kernel hold what that kernel reads and writes.  Built as a shared
 // library and driven from test_host_api.py.
+#include <sys/mman.h>
+
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -17,6 +19,7 @@ using namespace mfbc;
 
 namespace {
 
+constexpr size_t kMapped = (size_t)64 << 20;
 std::mutex mu;
 std::map<char *, size_t> blocks;         // live "device" allocations
 size_t live = 0, peak = 0, cap = (size_t)1 << 62;
@@ -122,8 +125,14 @@ hipError_t hipMalloc(void **p, size_t bytes) {
     *p = nullptr;
     if (fail_in >= 0 && fail_in-- == 0) return hipErrorOutOfMemory;
     if (live + bytes > cap) return hipErrorOutOfMemory;
-    // the memory is never touched in full: mapped on demand
-    if (!(*p = calloc(1, bytes ? bytes : 1))) return hipErrorOutOfMemory;
+    // large blocks are never touched in full: address space alone
+    if (bytes >= kMapped) {
+        *p = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+        if (*p == MAP_FAILED) *p = nullptr;
+    } else {
+        *p = calloc(1, bytes ? bytes : 1);
+    }
+    if (!*p) return hipErrorOutOfMemory;
     blocks[(char *)*p] = bytes;
     live += bytes;
     peak = std::max(peak, live);
@@ -137,8 +146,9 @@ hipError_t hipFree(void *p) {
         return hipSuccess;
     }
     live -= it->second;
+    if (it->second >= kMapped) munmap(p, it->second);
+    else free(p);
     blocks.erase(it);
-    free(p);
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) {
